@@ -152,8 +152,8 @@ struct gesmc_ctx {
     uint32_t bucket_avg = 3 * kLdsCap / 4;  // partition means fall in (avg / 2, avg]
     uint32_t sort_cap = kLdsCap;
     int fast_rounds = 2;
-    // GESMC_OPT_FAST_ROUNDS never set: a plain call runs adapt_rounds
-    // multi-workgroup rounds, taken from the previous plain call's rounds
+    // GESMC_OPT_FAST_ROUNDS never set: see decision_rounds (adapt_rounds is
+    // taken from the previous plain call)
     bool fast_rounds_auto = true;
     int adapt_rounds = 2;
     uint32_t round_limit = 0;  // decision rounds per superstep before GESMC_E_ROUNDS (0: none)
@@ -181,6 +181,7 @@ struct gesmc_ctx {
     uint32_t *tu_tag[3] = {nullptr, nullptr, nullptr};
     unsigned long long *tu_key[3] = {nullptr, nullptr, nullptr};
     uint2 *info = nullptr;
+    Winners wn{nullptr, nullptr};  // of the superstep being enqueued (inside a tuple buffer)
     // radix bookkeeping: per-tile digit counts / run bases of both levels, chunk sums
     uint64_t cap_counts1 = 0, cap_counts2 = 0, cap_partial = 0;
     uint32_t *counts1 = nullptr, *counts2 = nullptr, *partial = nullptr;
@@ -876,6 +877,15 @@ TuplePack tuple_pack(const gesmc_ctx *c, const Plan &p, uint32_t nslots, uint64_
     return pk;
 }
 
+// The winner records of a superstep (8 bytes per target): in the tuple keys
+// of the buffer that holds neither the partitioned tuples nor the resolve's
+// scratch.
+Winners winners(gesmc_ctx *c, int parts, int scratch) {
+    uint32_t *w = reinterpret_cast<uint32_t *>(c->tu_key[3 - parts - scratch]);
+    c->wn = Winners{w, w + c->cap_tu};
+    return c->wn;
+}
+
 gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots, uint32_t dup_bit,
                                    GraphErr ge = GraphErr{nullptr, 0, nullptr}, const EmitSource *emit = nullptr,
                                    uint64_t vend = 0, uint64_t dend = 0, const EmitOut *eo = nullptr,
@@ -906,7 +916,7 @@ gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots,
         GESMC_TRY(launch(c, s, KID_RESOLVE, nslots, k_resolve<true>,
                          dim3(persistent_blocks(c, k_resolve<true>, rlds, np)), dim3(kBlock), rlds, c->tu_tag[parts],
                          c->tu_key[parts], c->tu_tag[scratch], c->tu_key[scratch], (int)p.b2, poff, np, c->sort_cap,
-                         c->info, c->err, dup_bit, c->ctr_step, ge, pk));
+                         c->info, c->err, dup_bit, c->ctr_step, ge, pk, winners(c, parts, scratch)));
         return GESMC_OK;
     }
     if (emit)
@@ -924,8 +934,28 @@ gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots,
     GESMC_TRY(launch(c, s, KID_RESOLVE, nslots, k_resolve<false>,
                      dim3(persistent_blocks(c, k_resolve<false>, rlds, np)), dim3(kBlock), rlds, c->tu_tag[parts],
                      c->tu_key[parts], c->tu_tag[scratch], c->tu_key[scratch], (int)p.bbits, poff, np, c->sort_cap,
-                     c->info, c->err, dup_bit, c->ctr_step, ge, TuplePack{0, 0, 0, 0, 0, 0}));
+                     c->info, c->err, dup_bit, c->ctr_step, ge, TuplePack{0, 0, 0, 0, 0, 0},
+                     winners(c, parts, scratch)));
     return GESMC_OK;
+}
+
+// Multi-workgroup list rounds before the finisher while
+// GESMC_OPT_FAST_ROUNDS is unset: kRoundsHubs after a plain call whose first
+// round left more than kRoundsHubsAbove switches of a superstep undecided
+// (adapt_rounds), else none below kRoundsFromSwitches switches (the few that
+// are left cost the finisher less than an empty launch of 3 us: 41 at m =
+// 1.1e5) and kRoundsPlain from there on.  Hub graphs need 6 to 9 rounds
+// whatever their size, and a pass of the finisher takes kChainFinish switches:
+// n = 2^19, gamma = 2.05, 72,000 undecided, ms per superstep at 0, 2, 8 and
+// 64 rounds: 1.56, 0.39, 0.34, 0.47; n = 20000, gamma = 2.01, 5,700 undecided:
+// 0.30, 0.22, 0.22, 0.35.
+constexpr uint64_t kRoundsHubsAbove = 8 * kChainFinish;
+constexpr int kRoundsPlain = 2, kRoundsHubs = 6;
+constexpr uint32_t kRoundsFromSwitches = 1u << 16;
+int decision_rounds(const gesmc_ctx *c, uint32_t ell) {
+    if (!c->fast_rounds_auto) return c->fast_rounds;
+    if (c->adapt_rounds > kRoundsPlain) return c->adapt_rounds;
+    return ell < kRoundsFromSwitches ? 0 : kRoundsPlain;
 }
 
 // One superstep with the partitioned resolution (state in buffer 0).
@@ -982,19 +1012,21 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
     GESMC_TRY(launch(c, s, KID_DECIDE_CHAIN1, p.ell, k_decide_chain, dim3(gd), dim3(kBlock), 0, si, sk, p.ell,
                      c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)nullptr,
                      (const uint32_t *)nullptr, c->ulist[0], &c->ucount[0], (uint32_t *)nullptr, c->bslot + ge,
-                     c->ctr_step, cls, nc));
+                     c->ctr_step, cls, nc, c->wn, (const uint4 *)nullptr, 0u));
     const uint32_t rblocks = std::max<uint32_t>(1, std::min<uint32_t>(ceil_div(p.ell, kBlock), c->num_cus * 4));
     int j = 0;
-    for (; j < c->fast_rounds; ++j) {
+    const int fast = decision_rounds(c, p.ell);
+    for (; j < fast; ++j) {
         GESMC_TRY(launch(c, s, KID_DECIDE_CHAIN, 0, k_decide_chain, dim3(rblocks), dim3(kBlock), 0, si, sk, p.ell,
                          c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)c->ulist[j % 2],
                          (const uint32_t *)&c->ucount[j % 3], c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3],
-                         &c->ucount[(j + 2) % 3], (uint4 *)nullptr, c->ctr_step, cls, NextCounts{}));
+                         &c->ucount[(j + 2) % 3], (uint4 *)nullptr, c->ctr_step, cls, NextCounts{},
+                         c->wn, (const uint4 *)c->bslot, j == 0 ? ge + gd : 0u));
     }
-    GESMC_TRY(launch(c, s, KID_FINISH_CHAIN, 0, k_finish_chain, dim3(1), dim3(kFinishBlock), 0, si, sk, p.ell,
+    GESMC_TRY(launch(c, s, KID_FINISH_CHAIN, 0, k_finish_chain, dim3(1), dim3(kChainFinish), 0, si, sk, p.ell,
                      c->info, c->st, c->idx[0], c->key[0], c->ulist[j % 2], &c->ucount[j % 3],
-                     c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3], (const uint4 *)c->bslot, ge + gd,
-                     c->ctr_step, c->err, c->round_limit, cls));
+                     c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3], (const uint4 *)c->bslot, j ? 0u : ge + gd,
+                     c->ctr_step, c->err, c->round_limit, cls, c->wn));
     if (bs && bs->acc)
         GESMC_TRY(launch(c, s, KID_MISC, 0, k_graph_stats, dim3(ceil_div(p.ell, kStatsChunk)), dim3(kBlock), 0,
                          (const uint8_t *)c->st, bs->gr, bs->ngraphs, p.ell, bs->acc));
@@ -1190,14 +1222,6 @@ gesmc_status run_small_impl(gesmc_ctx *c, hipStream_t s, const uint64_t *d_in, u
     return GESMC_OK;
 }
 
-// Adaptive multi-workgroup rounds of plain calls: after a call whose
-// supersteps took more than kAdaptRoundsAbove decision rounds, the next
-// plain call of the context runs kAdaptRoundsMany (power-law gamma = 2.01,
-// n = 2^20: 2.4e8 -> 3.4e8 attempts/s), else kAdaptRoundsFew (each extra
-// round is a launch, most of them empty on graphs without hubs).
-constexpr uint64_t kAdaptRoundsAbove = 16;
-constexpr int kAdaptRoundsMany = 128, kAdaptRoundsFew = 2;
-
 gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t *d_out, uint64_t m64, uint32_t n,
                       uint64_t seed, uint32_t t0, uint32_t r, uint32_t pl, gesmc_stats *stats,
                       gesmc_step_stats *steps, uint8_t *d_outcome, uint32_t cls = 0) {
@@ -1231,13 +1255,6 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
         (m <= kMidMax || (m <= kCmpMax && n <= kCmpMaxN)))
         return run_small_impl(c, s, d_in, d_out, m, n, seed, t0, r, pl, stats);
     GESMC_TRY(ensure_capacity(c, m, cls != 0 && !(cls & CLS_MULTI)));
-    // the multi-workgroup decision rounds of this call (restored on return)
-    struct FastRounds {
-        gesmc_ctx *c;
-        int saved;
-        ~FastRounds() { c->fast_rounds = saved; }
-    } fast_rounds_guard{c, c->fast_rounds};
-    if (c->fast_rounds_auto) c->fast_rounds = c->adapt_rounds;
     GESMC_TRY(ensure_counters(c, r));
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     c->tuple_bytes = 0;
@@ -1300,12 +1317,9 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
     const gesmc_status st = map_err(*c->h_err);
     if (st != GESMC_OK) return st;
     if (c->fast_rounds_auto && m >= 2 && r > 0) {
-        // supersteps with long dependency chains (hub edges) finish faster
-        // with many multi-workgroup rounds before the one-workgroup finisher;
-        // short ones would only pay empty launches
-        uint64_t maxr = 0;
-        for (uint32_t q = 0; q < r; ++q) maxr = std::max<uint64_t>(maxr, c->h_ctr[q].rounds);
-        c->adapt_rounds = maxr > kAdaptRoundsAbove ? kAdaptRoundsMany : kAdaptRoundsFew;
+        uint64_t left = 0;
+        for (uint32_t q = 0; q < r; ++q) left = std::max<uint64_t>(left, c->h_ctr[q].undecided_round1);
+        c->adapt_rounds = left > kRoundsHubsAbove ? kRoundsHubs : kRoundsPlain;
     }
     const uint64_t att = (m >= 2) ? p.ell : 0;
     if (steps) {

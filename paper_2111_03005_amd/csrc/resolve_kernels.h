@@ -34,7 +34,24 @@ namespace gesmc {
 
 // per-target record: x = eraser (kNoEraser / kStays / switch), y = predecessor (k' << 1 | h') or kNoPred
 constexpr uint32_t kNoPred = 0xFFFFFFFFu;
-constexpr uint32_t kWalked = 0xFFFFFFFEu;  // a resumed walk that reached the chain's end
+constexpr uint32_t kWalked = 0xFFFFFFFEu;  // every predecessor rejected (a walk that reached the chain's end)
+__device__ __forceinline__ bool chain_end(uint32_t p) { return p >= kWalked; }  // kWalked or kNoPred
+
+// The legal inserter of each key.  A key gains at most one legal inserter in
+// a superstep: once inserted it stays (a position is a source once), and
+// inserters before its eraser saw it present.  head[s] (s a target record
+// with a predecessor) names the record of the key's first inserter, and
+// win[head] receives the legal inserter if that is a later one (the first
+// one's own status tells otherwise).  A switch whose nearest undecided
+// predecessor still waits is then rejected as soon as any earlier inserter
+// is legal, so the rounds follow the dependency depth instead of the length
+// of a hub key's inserter chain: on Pld([1..16000], 2.05), n = 2^19, a
+// superstep's rounds fell from about 300 to 8 and the call (10 supersteps)
+// from 8.9 to 3.8 ms.
+struct Winners {
+    uint32_t *head, *win;  // per target record 2k+h; written by k_resolve where a predecessor exists
+};
+constexpr uint32_t kNoWinner = 0xFFFFFFFFu;
 constexpr uint32_t kListEnd = 0xFFFFu;  // end of a cell list in k_resolve (slots are < 2^16)
 constexpr uint32_t kEpochNone = 0xFFFFu;  // k_resolve: no list partition yet (epochs are 0 .. 0xFFFE)
 #ifndef GESMC_RESOLVE_LISTS
@@ -284,12 +301,12 @@ __device__ __forceinline__ void flag_duplicate(unsigned long long key, uint32_t 
 }
 
 // Writes the records of the tuple at sorted position p, given the position
-// of the first tuple of its key.  A second ERASE tuple means the edge occurs
-// twice: dup_bit is raised (and the graph flagged in a batch).
-__device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, uint32_t p, uint32_t first,
-                                            uint32_t prev_tag, unsigned long long key, uint32_t f,
-                                            const TuplePack &pk, uint2 *info, uint32_t *err, uint32_t dup_bit,
-                                            const GraphErr &ge) {
+// of the first tuple of its key and the smallest INSERT tag of its key.  A
+// second ERASE tuple means the edge occurs twice: dup_bit is raised (and the graph flagged in a batch).
+__device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, uint32_t first_ins, uint32_t p,
+                                            uint32_t first, uint32_t prev_tag, unsigned long long key, uint32_t f,
+                                            const TuplePack &pk, uint2 *info, const Winners &wn, uint32_t *err,
+                                            uint32_t dup_bit, const GraphErr &ge) {
     const bool ins = (tag & kTagInsert) != 0;
     if (!ins) {
         if (p != first) flag_duplicate(key, f, pk, err, dup_bit, ge);
@@ -300,13 +317,19 @@ __device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, ui
     uint32_t pred = (p > first && (prev_tag & kTagInsert)) ? (prev_tag & ~kTagInsert) : kNoPred;
     if (eraser == kNoEraser && pred == kNoPred) return;
     uint32_t slot = tag & ~kTagInsert;
+    uint32_t head = first_ins & ~kTagInsert;
     if (pk.local) {  // graph-local tags (all of one key): back to batch-wide switch ids
         const uint32_t kbase = ge.gr[graph_of_tuple(key, f, pk, ge)].poff >> 1;
         slot += 2 * kbase;
+        head += 2 * kbase;
         if (eraser != kStays && eraser != kNoEraser) eraser += kbase;
         if (pred != kNoPred) pred += 2 * kbase;
     }
     info[slot] = make_uint2(eraser, pred);
+    if (pred != kNoPred) {
+        wn.head[slot] = head;
+        wn.win[head] = kNoWinner;  // every inserter after the first writes the same value
+    }
 }
 
 // One workgroup per fine partition (grid-stride if the grid is smaller).
@@ -324,7 +347,8 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                                                     unsigned long long *__restrict__ sc_key, int pbits,
                                                     const uint32_t *__restrict__ part_off, uint32_t np, uint32_t cap,
                                                     uint2 *__restrict__ info, uint32_t *__restrict__ err,
-                                                    uint32_t dup_bit, StepCounters *ctr, GraphErr ge, TuplePack pk) {
+                                                    uint32_t dup_bit, StepCounters *ctr, GraphErr ge, TuplePack pk,
+                                                    Winners wn) {
     extern __shared__ uint32_t lds[];
     constexpr uint32_t kCells = 1u << kCellBits;
     uint32_t *cell = lds;
@@ -407,8 +431,11 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                         b = x;
                 }
                 const auto tag_at = [&](uint32_t x) { return tag_of_code((uint32_t)(ak[x] & code_mask), pk.kb); };
-                resolve_one(tag_at(p), tag_at(a), p, a, p > 0 ? tag_at(p - 1) : 0u, kp, f, pk, info, err, dup_bit,
-                            ge);
+                const uint32_t tp = tag_at(p), ta = tag_at(a);
+                // a group holds one ERASE tuple at most (two are an input error)
+                const uint32_t fi = (ta & kTagInsert) ? ta : a < p ? tag_at(a + 1) : tp;
+                resolve_one(tp, ta, (fi & kTagInsert) ? fi : tp, p, a, p > 0 ? tag_at(p - 1) : 0u, kp, f, pk, info,
+                            wn, err, dup_bit, ge);
             }
             if (tid == 0) atomicAdd(&ctr->fallback_buckets, 1ull);
             __syncthreads();
@@ -467,7 +494,9 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                     else
                         b = x;
                 }
-                resolve_one(at[p], at[a], p, a, p > 0 ? at[p - 1] : 0u, kp, f, pk, info, err, dup_bit, ge);
+                const uint32_t fi = (at[a] & kTagInsert) ? at[a] : a < p ? at[a + 1] : at[p];
+                resolve_one(at[p], at[a], (fi & kTagInsert) ? fi : at[p], p, a, p > 0 ? at[p - 1] : 0u, kp, f, pk,
+                            info, wn, err, dup_bit, ge);
             }
             if (tid == 0) atomicAdd(&ctr->fallback_buckets, 1ull);
             __syncthreads();
@@ -514,19 +543,21 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 if (p >= c) continue;
                 const unsigned long long kx = c_key[q];
                 const uint32_t tx = c_tag[q];
-                uint32_t first_tag = tx, prev_tag = 0;
+                uint32_t first_tag = tx, first_ins = tx, prev_tag = 0;
                 bool before = false;
                 for (uint32_t y = cell[r_cell[q]] & 0xFFFFu; y != kListEnd; y = nxt[y]) {
                     const unsigned long long wy = sK[y];
                     if (y == p || (kPacked ? (wy & ~code_mask) : wy) != kx) continue;
                     const uint32_t ty = kPacked ? tag_of_code((uint32_t)(wy & code_mask), pk.kb) : sT[y];
                     first_tag = min(first_tag, ty);
+                    if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     if (ty < tx || (ty == tx && y < p)) {
                         prev_tag = before ? max(prev_tag, ty) : ty;
                         before = true;
                     }
                 }
-                resolve_one(tx, first_tag, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, err, dup_bit, ge);
+                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, wn, err, dup_bit,
+                            ge);
             }
         } else if (c > 0) {  // counting sort into cell order
             for (uint32_t q = tid; q < kCells; q += kBlock) cell[q] = 0;
@@ -571,18 +602,20 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 const uint32_t me = a + r_rank[q];
                 const unsigned long long kx = c_key[q];
                 const uint32_t tx = c_tag[q];
-                uint32_t first_tag = tx, prev_tag = 0;
+                uint32_t first_tag = tx, first_ins = tx, prev_tag = 0;
                 bool before = false;
                 for (uint32_t y = a; y < b; ++y) {
                     if (y == me || sK[y] != kx) continue;
                     const uint32_t ty = sT[y];
                     first_tag = min(first_tag, ty);
+                    if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     if (ty < tx || (ty == tx && y < me)) {
                         prev_tag = before ? max(prev_tag, ty) : ty;
                         before = true;
                     }
                 }
-                resolve_one(tx, first_tag, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, err, dup_bit, ge);
+                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, wn, err, dup_bit,
+                            ge);
             }
         }
         // the next partition's loads are issued before the barrier that ends
@@ -603,8 +636,13 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
 // record's predecessor link (`self`), so later walks through this switch
 // skip them.  Any value so written skips only decided-rejected inserters of
 // the same target, so concurrent writers are harmless.
-__device__ __forceinline__ int judge_target_chain(uint2 *info, uint2 rec, uint32_t self, uint32_t k,
-                                                  const uint8_t *st) {
+//
+// from (nullable): the walk resumes at *from (kNoPred: the first predecessor,
+// rec.y) and leaves there the predecessor it waits for: decided predecessors
+// never change, so a repeated judgement of the same switch walks each link
+// once.
+__device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn, uint2 rec, uint32_t self, uint32_t k,
+                                                  const uint8_t *st, uint32_t *from = nullptr) {
     int v = V_OK;
     const uint32_t e = rec.x;
     if (e != kNoEraser) {
@@ -618,61 +656,17 @@ __device__ __forceinline__ int judge_target_chain(uint2 *info, uint2 rec, uint32
     // earlier inserters of the same target, nearest first; switch ids strictly
     // decrease along the chain (checked, so a corrupt record cannot loop)
     uint32_t p = rec.y, below = k;
-    int out = v;
-    while (p != kNoPred) {
-        const uint32_t pk = p >> 1;
-        if (pk >= below) return V_ILLEGAL;
-        if (e != kNoEraser && pk < e) {  // inserted while the target was still there
-            p = kNoPred;
-            break;
-        }
-        const uint8_t sp = load_status(st, pk);
-        if (sp == ST_LEGAL) {
-            out = V_ILLEGAL;
-            break;
-        }
-        if (sp == ST_UNDECIDED) {
-            out = V_WAIT;
-            break;
-        }
-        below = pk;
-        p = info[p].y;
-    }
-    if (p != rec.y) info[self].y = p;
-    return out;
-}
-
-// judge_target_chain that resumes its predecessor walk at *from (kNoPred:
-// the first predecessor, rec.y) and leaves there the predecessor it waits
-// for: decided predecessors never change, so a repeated judgement of the
-// same switch walks each link once.
-__device__ __forceinline__ int judge_target_resume(uint2 *info, uint2 rec, uint32_t self, uint32_t k,
-                                                   const uint8_t *st, uint32_t *from) {
-    int v = V_OK;
-    const uint32_t e = rec.x;
-    if (e != kNoEraser) {
-        if (e == kStays || e >= k) return V_ILLEGAL;
-        const uint8_t se = load_status(st, e);
-        if (se == ST_UNDECIDED)
-            v = V_WAIT;
-        else if (se != ST_LEGAL)
-            return V_ILLEGAL;
-    }
-    // *from: kNoPred (not started), kWalked (nothing left) or a predecessor
-    uint32_t p = rec.y, below = k;
-    if (*from == kWalked) {
-        p = kNoPred;
-    } else if (*from != kNoPred) {
+    if (from && *from != kNoPred) {
         p = *from;
-        below = (p >> 1) + 1;
+        if (!chain_end(p)) below = (p >> 1) + 1;
     }
     const uint32_t p0 = p;
     int out = v;
-    while (p != kNoPred) {
+    while (!chain_end(p)) {
         const uint32_t pk = p >> 1;
         if (pk >= below) return V_ILLEGAL;
         if (e != kNoEraser && pk < e) {  // inserted while the target was still there
-            p = kNoPred;
+            p = kWalked;
             break;
         }
         const uint8_t sp = load_status(st, pk);
@@ -681,29 +675,50 @@ __device__ __forceinline__ int judge_target_resume(uint2 *info, uint2 rec, uint3
             break;
         }
         if (sp == ST_UNDECIDED) {
-            out = V_WAIT;
+            // an inserter before it may have won already
+            const uint32_t h = wn.head[self];
+            out = load_status(st, h >> 1) == ST_LEGAL ||
+                          __hip_atomic_load(wn.win + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kNoWinner
+                      ? V_ILLEGAL
+                      : V_WAIT;
             break;
         }
         below = pk;
-        p = info[p].y;
+        const uint32_t q = info[p].y;
+        p = chain_end(q) ? kWalked : q;
     }
-    if (p != p0) info[self].y = p;  // the shortcut of judge_target_chain
-    *from = p == kNoPred ? kWalked : p;
+    if (p != p0) info[self].y = p;
+    if (from) *from = p == kNoPred ? kWalked : p;
     return out;
 }
 
-// Decides switch k from its two target records; the pair's records (ij, ee)
-// are passed in so that callers can issue every load of the switch at once.
-__device__ __forceinline__ bool decide_switch_chain(uint32_t k, uint4 recs, uint2 ij, ulonglong2 ee, uint2 *info,
-                                                    uint8_t *st, uint32_t *out_idx, unsigned long long *out_key,
-                                                    BlockCounts *bc, uint32_t cls) {
-    const int v = max(judge_target_chain(info, make_uint2(recs.x, recs.y), 2 * k, k, st),
-                      judge_target_chain(info, make_uint2(recs.z, recs.w), 2 * k + 1, k, st));
+// Leaves the legal switch k as the winner of its targets' keys (records recs).
+__device__ __forceinline__ void post_winner(const Winners &wn, uint4 recs, uint32_t k) {
+    if (recs.y != kNoPred)
+        __hip_atomic_store(wn.win + wn.head[2 * k], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (recs.w != kNoPred)
+        __hip_atomic_store(wn.win + wn.head[2 * k + 1], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Verdict on switch k from its two target records.
+__device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 *info, const Winners &wn,
+                                                  const uint8_t *st, uint2 *from = nullptr) {
+    return max(judge_target_chain(info, wn, make_uint2(recs.x, recs.y), 2 * k, k, st, from ? &from->x : nullptr),
+               judge_target_chain(info, wn, make_uint2(recs.z, recs.w), 2 * k + 1, k, st, from ? &from->y : nullptr));
+}
+
+// Carries out verdict v on switch k; true if it has to wait.  The pair's
+// records (ij, ee) are passed in so that callers can issue every load of the
+// switch at once.
+__device__ __forceinline__ bool commit_switch_chain(int v, uint32_t k, uint4 recs, uint2 ij, ulonglong2 ee,
+                                                    const Winners &wn, uint8_t *st, uint32_t *out_idx,
+                                                    unsigned long long *out_key, BlockCounts *bc, uint32_t cls) {
     if (v == V_WAIT) return true;
     reinterpret_cast<uint2 *>(out_idx)[k] = ij;
     if (v == V_OK) {
         const Targets T = switch_targets_cls(ee.x, ee.y, ij.x < ij.y, cls);
         reinterpret_cast<ulonglong2 *>(out_key)[k] = make_ulonglong2(T.A, T.B);
+        post_winner(wn, recs, k);
         st[k] = ST_LEGAL;
         atomicAdd(&bc->legal, 1u);
     } else {
@@ -732,8 +747,15 @@ struct NextCounts {
     int bbits;
 };
 
+// Undecided switches staged per workgroup of k_decide_chain: the switches of
+// one 4096-record tile.
+constexpr uint32_t kWaitStage = kTileLarge / 2;
+static_assert(kWaitStage >= kTileSmall / 2 && kWaitStage % kBlock == 0, "stage flushes cover whole trips");
+
 // Round 1 (list == nullptr: every switch) or a later round over a list.
-// With nc.counts (round 1 only), each workgroup takes whole tiles of
+// With fold, also sums the nfold per-block counts of the emit and of round 1
+// (256 a workgroup: the finisher's one workgroup took 5 us for the 10,240 of a
+// large graph).  With nc.counts (round 1 only), each workgroup takes whole tiles of
 // nc.tile / 2 switches and also writes their counts.
 __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restrict__ s_idx,
                                                          const unsigned long long *__restrict__ s_key, uint32_t ell,
@@ -746,11 +768,44 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
                                                          uint32_t *__restrict__ next_count,
                                                          uint32_t *__restrict__ zero_count,
                                                          uint4 *__restrict__ bslot, StepCounters *ctr,
-                                                         uint32_t cls, NextCounts nc) {
+                                                         uint32_t cls, NextCounts nc, Winners wn,
+                                                         const uint4 *__restrict__ fold, uint32_t nfold) {
     __shared__ BlockCounts bc;
     __shared__ uint32_t hs[1u << kMaxCoarseBits];
-    if (threadIdx.x == 0) bc = BlockCounts{0, 0, 0, 0};
+    __shared__ uint32_t s_wait[kWaitStage], s_nwait, s_wbase, s_total;
+    if (threadIdx.x == 0) {
+        bc = BlockCounts{0, 0, 0, 0};
+        s_nwait = s_total = 0;
+    }
     __syncthreads();
+    // Undecided switches are staged in LDS and leave with one device atomic
+    // per kWaitStage switches: an atomic per wave on the one list counter
+    // (and one on its tally) serialises memory-side, and on graphs whose
+    // switches depend on each other nearly every wave holds an undecided one.
+    auto stage_undecided = [&](bool want, uint32_t k) {
+        const unsigned long long mask = __ballot(want);
+        if (mask == 0) return;
+        const uint32_t leader = __ffsll((long long)mask) - 1;
+        uint32_t base = 0;
+        if (__lane_id() == leader) base = atomicAdd(&s_nwait, (uint32_t)__popcll(mask));
+        base = __shfl(base, leader);
+        if (want) s_wait[base + __popcll(mask & ((1ull << __lane_id()) - 1ull))] = k;
+    };
+    // every thread of the workgroup; at most kWaitStage switches since the last call
+    auto flush_undecided = [&]() {
+        __syncthreads();
+        const uint32_t c = s_nwait;
+        __syncthreads();  // read by every wave before the next trip may stage again
+        if (c == 0) return;
+        if (threadIdx.x == 0) {
+            s_wbase = atomicAdd(next_count, c);
+            s_total += c;
+        }
+        __syncthreads();
+        for (uint32_t q = threadIdx.x; q < c; q += kBlock) next_list[s_wbase + q] = s_wait[q];
+        if (threadIdx.x == 0) s_nwait = 0;
+        __syncthreads();
+    };
     // the counter cleared here is the one the round after next fills
     if (zero_count && blockIdx.x == 0 && threadIdx.x == 0) *zero_count = 0;
     auto decide_one = [&](uint32_t k, bool *wait, uint2 *ij_out) {
@@ -759,9 +814,18 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
         const uint2 ij = reinterpret_cast<const uint2 *>(s_idx)[k];
         const ulonglong2 ee = reinterpret_cast<const ulonglong2 *>(s_key)[k];
         *ij_out = ij;
-        if (sk == ST_UNDECIDED) *wait = decide_switch_chain(k, recs, ij, ee, info, st, out_idx, out_key, &bc, cls);
+        if (sk == ST_UNDECIDED)
+            *wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, st), k, recs, ij, ee, wn, st, out_idx,
+                                        out_key, &bc, cls);
     };
     const uint32_t n = list ? min(*count, ell) : ell;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nfold; q += gridDim.x * kBlock) {
+        const uint4 v = fold[q];
+        if (v.x) atomicAdd(&bc.legal, v.x);
+        if (v.y) atomicAdd(&bc.loop, v.y);
+        if (v.z) atomicAdd(&bc.exists, v.z);
+        if (v.w) atomicAdd(&bc.pl, v.w);
+    }
     if (nc.counts) {
         const uint32_t nd = 1u << nc.dbits, dmask = nd - 1, half = nc.tile / 2;
         // tiles of the next step's positions (a batch's prefix may shrink: the
@@ -788,11 +852,11 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
                         atomicAdd(&hs[digit(ij.y, 2 * k)], 1u);
                     }
                 }
-                append_undecided(wait, k, next_list, next_count, &ctr->undecided_round1);
+                stage_undecided(wait, k);
             }
             if ((nc.m & 1u) && threadIdx.x == 0 && (nc.m - 1) / nc.tile == w)  // the idle record of odd m
                 atomicAdd(&hs[digit(s_idx[nc.m - 1], nc.m - 1)], 1u);
-            __syncthreads();
+            flush_undecided();
             if (w < ncount)
                 for (uint32_t d = threadIdx.x; d < nd; d += kBlock) nc.counts[(size_t)w * nd + d] = hs[d];
             __syncthreads();
@@ -809,9 +873,11 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
                 uint2 ij;
                 if (k < ell) decide_one(k, &wait, &ij);
             }
-            append_undecided(wait, k, next_list, next_count, list ? nullptr : &ctr->undecided_round1);
+            stage_undecided(wait, k);
+            if ((r + 1) % (kWaitStage / kBlock) == 0 || r + 1 == trips) flush_undecided();
         }
     }
+    if (!list && threadIdx.x == 0 && s_total) atomicAdd(&ctr->undecided_round1, (unsigned long long)s_total);
     if (bslot)
         store_counts(&bc, bslot + blockIdx.x);
     else
@@ -820,18 +886,21 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
 }
 
 // Remaining rounds in one workgroup; the next round's list counter is cleared
-// by the round that fills it.  After kSweepAfter rounds with switches still
+// by the round that fills it.  Every pass of the workgroup over kChainFinish
+// switches of the list counts as a round (a later pass of the same sweep over
+// the list already sees what the earlier ones decided).  After kSweepAfter rounds with switches still
 // undecided (long dependency chains: hub edges that many switches erase and
 // insert), the rest is decided by a sweep in ascending switch id: a switch
 // depends on smaller ids only, so chunks of kSweepChunk ids are taken in
 // order, each repeated until it holds no undecided switch; earlier chunks
 // are then final and only chains inside a chunk cost repeats.  Each repeat
 // counts as a round.
+constexpr int kChainFinish = 512;
 constexpr uint32_t kSweepAfter = 8;
 constexpr uint32_t kSweepChunk = 1024;
 constexpr uint32_t kSweepWords = 16384;  // chunk marks: ids below 2^29 (m < 2^30)
 
-__global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *__restrict__ s_idx,
+__global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *__restrict__ s_idx,
                                                                const unsigned long long *__restrict__ s_key,
                                                                uint32_t ell, uint2 *info,
                                                                uint8_t *st, uint32_t *__restrict__ out_idx,
@@ -840,7 +909,7 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
                                                                uint32_t *count_b, const uint4 *__restrict__ bslot,
                                                                uint32_t nbslot, StepCounters *ctr,
                                                                uint32_t *__restrict__ err, uint32_t round_limit,
-                                                               uint32_t cls) {
+                                                               uint32_t cls, Winners wn) {
     __shared__ BlockCounts bc;
     __shared__ uint32_t s_n;
     const uint32_t tid = threadIdx.x;
@@ -856,14 +925,14 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
         }
     }
     __syncthreads();
-    {  // fold the per-block counts of the emit and first-round kernels (eight loads in flight)
+    if (nbslot) {  // fold the per-block counts of the emit and first round (no list round did; eight loads in flight)
         constexpr uint32_t kFold = 8;
         uint4 acc = make_uint4(0, 0, 0, 0);
-        for (uint32_t q0 = tid; q0 < nbslot; q0 += kFold * kFinishBlock) {
+        for (uint32_t q0 = tid; q0 < nbslot; q0 += kFold * kChainFinish) {
             uint4 v[kFold];
 #pragma unroll
             for (uint32_t j = 0; j < kFold; ++j) {
-                const uint32_t q = q0 + j * kFinishBlock;
+                const uint32_t q = q0 + j * kChainFinish;
                 v[j] = q < nbslot ? bslot[q] : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
@@ -885,19 +954,29 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
         if (tid == 0) *cnxt = 0;
         __threadfence();
         __syncthreads();
-        const uint32_t trips = (n + kFinishBlock - 1) / kFinishBlock;
+        const uint32_t trips = (n + kChainFinish - 1) / kChainFinish;
         for (uint32_t r = 0; r < trips; ++r) {
-            const uint32_t q = r * kFinishBlock + tid;
-            bool wait = false;
+            const uint32_t q = r * kChainFinish + tid;
+            bool wait = false, todo = false;
             uint32_t k = 0;
+            uint4 recs = make_uint4(0, 0, 0, 0);
+            int v = V_WAIT;
             if (q < n) {
                 k = cur[q];
-                if (k < ell && st[k] == ST_UNDECIDED)
-                    wait = decide_switch_chain(k, reinterpret_cast<const uint4 *>(info)[k],
-                                               reinterpret_cast<const uint2 *>(s_idx)[k],
-                                               reinterpret_cast<const ulonglong2 *>(s_key)[k], info, st, out_idx,
-                                               out_key, &bc, cls);
+                todo = k < ell && st[k] == ST_UNDECIDED;
+                if (todo) {
+                    recs = reinterpret_cast<const uint4 *>(info)[k];
+                    v = judge_switch_chain(k, recs, info, wn, st);
+                }
             }
+            // a pass judges by what earlier passes decided, so its round count
+            // does not depend on which wave runs first
+            __syncthreads();
+            if (todo)
+                wait = commit_switch_chain(v, k, recs, reinterpret_cast<const uint2 *>(s_idx)[k],
+                                           reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx, out_key,
+                                           &bc, cls);
+            __syncthreads();
             append_undecided(wait, k, nxt, cnxt);
         }
         __threadfence();
@@ -906,7 +985,7 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
             const uint32_t nn = min(*cnxt, ell);
             if (nn >= n) atomicOr(err, ERR_INTERNAL);  // the smallest undecided switch always decides
             s_n = nn >= n ? 0 : nn;
-            const unsigned long long done = atomicAdd(&ctr->rounds, 1ull) + 1;
+            const unsigned long long done = atomicAdd(&ctr->rounds, (unsigned long long)trips) + trips;
             if (round_limit && s_n > 0 && done >= round_limit) {
                 atomicOr(err, ERR_ROUNDS);
                 s_n = 0;
@@ -926,13 +1005,13 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
         __shared__ uint32_t s_wait, s_done, s_stop;
         __shared__ unsigned long long s_rounds;
         const uint32_t nwords = ((ell + kSweepChunk - 1) / kSweepChunk + 31) / 32;
-        for (uint32_t w = tid; w < nwords; w += kFinishBlock) s_chunks[w] = 0;
+        for (uint32_t w = tid; w < nwords; w += kChainFinish) s_chunks[w] = 0;
         if (tid == 0) {
             s_rounds = atomicAdd(&ctr->rounds, 0ull);
             s_stop = 0;
         }
         __syncthreads();
-        for (uint32_t q = tid; q < n; q += kFinishBlock) {
+        for (uint32_t q = tid; q < n; q += kChainFinish) {
             const uint32_t k = cur[q];
             if (k < ell) atomicOr(&s_chunks[(k / kSweepChunk) >> 5], 1u << ((k / kSweepChunk) & 31));
         }
@@ -944,7 +1023,7 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
                 const uint32_t c = w * 32 + (uint32_t)(__ffs(bits) - 1);
                 bits &= bits - 1;
                 const uint32_t kb = c * kSweepChunk, ke = min(kb + kSweepChunk, ell);
-                constexpr uint32_t kPer = kSweepChunk / kFinishBlock;
+                constexpr uint32_t kPer = kSweepChunk / kChainFinish;
                 uint2 from[kPer];  // resume points of the two predecessor walks
 #pragma unroll
                 for (uint32_t j = 0; j < kPer; ++j) from[j] = make_uint2(kNoPred, kNoPred);
@@ -957,30 +1036,16 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_chain(const uint32_t *_
                     uint32_t waits = 0, dones = 0;
 #pragma unroll
                     for (uint32_t j = 0; j < kPer; ++j) {
-                        const uint32_t k = kb + tid + j * kFinishBlock;
+                        const uint32_t k = kb + tid + j * kChainFinish;
                         if (k >= ke || load_status(st, k) != ST_UNDECIDED) continue;
                         const uint4 recs = reinterpret_cast<const uint4 *>(info)[k];
-                        const int v =
-                            max(judge_target_resume(info, make_uint2(recs.x, recs.y), 2 * k, k, st, &from[j].x),
-                                judge_target_resume(info, make_uint2(recs.z, recs.w), 2 * k + 1, k, st, &from[j].y));
-                        if (v == V_WAIT) {
+                        if (commit_switch_chain(judge_switch_chain(k, recs, info, wn, st, &from[j]), k, recs,
+                                                reinterpret_cast<const uint2 *>(s_idx)[k],
+                                                reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx,
+                                                out_key, &bc, cls))
                             ++waits;
-                            continue;
-                        }
-                        ++dones;
-                        const uint2 ij = reinterpret_cast<const uint2 *>(s_idx)[k];
-                        const ulonglong2 ee = reinterpret_cast<const ulonglong2 *>(s_key)[k];
-                        reinterpret_cast<uint2 *>(out_idx)[k] = ij;
-                        if (v == V_OK) {
-                            const Targets T = switch_targets_cls(ee.x, ee.y, ij.x < ij.y, cls);
-                            reinterpret_cast<ulonglong2 *>(out_key)[k] = make_ulonglong2(T.A, T.B);
-                            st[k] = ST_LEGAL;
-                            atomicAdd(&bc.legal, 1u);
-                        } else {
-                            reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
-                            st[k] = ST_EXISTS;
-                            atomicAdd(&bc.exists, 1u);
-                        }
+                        else
+                            ++dones;
                     }
                     if (waits) atomicAdd(&s_wait, waits);
                     if (dones) atomicAdd(&s_done, dones);
