@@ -344,10 +344,19 @@ __global__ void k_pld_even(const unsigned long long *__restrict__ C, uint32_t nv
 __global__ __launch_bounds__(kBlock) void k_hh_stats(const uint32_t *__restrict__ deg, uint32_t n,
                                                      uint32_t *__restrict__ dmax,
                                                      unsigned long long *__restrict__ sum) {
+    // one pair of device atomics per workgroup: a pair per wave (16,000 waves
+    // at n = 2^20) on the two addresses took 194 us
+    __shared__ uint32_t b_mx;
+    __shared__ unsigned long long b_s;
+    if (threadIdx.x == 0) {
+        b_mx = 0;
+        b_s = 0;
+    }
+    __syncthreads();
     uint32_t mx = 0;
     unsigned long long s = 0;
     const uint32_t stride = gridDim.x * kBlock;
-    for (uint32_t v = blockIdx.x * kBlock + threadIdx.x; v < n; v += stride) {
+    for (uint64_t v = blockIdx.x * kBlock + threadIdx.x; v < n; v += stride) {
         const uint32_t d = deg[v];
         mx = max(mx, d);
         s += d;
@@ -357,8 +366,13 @@ __global__ __launch_bounds__(kBlock) void k_hh_stats(const uint32_t *__restrict_
         s += __shfl_down(s, o, 64);
     }
     if ((threadIdx.x & 63u) == 0) {
-        atomicMax(dmax, mx);
-        atomicAdd(sum, s);
+        atomicMax(&b_mx, mx);
+        atomicAdd(&b_s, s);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        atomicMax(dmax, b_mx);
+        atomicAdd(sum, b_s);
     }
 }
 
@@ -387,7 +401,7 @@ __global__ __launch_bounds__(64) void k_hh_place(const uint32_t *__restrict__ de
                                                  uint32_t D, uint32_t nb, const unsigned long long *__restrict__ Moff,
                                                  uint32_t *__restrict__ O) {
     extern __shared__ uint32_t hh_c[];
-    const uint32_t b = blockIdx.x, lane = threadIdx.x;
+    const uint32_t b = blockIdx.x, lane = threadIdx.x, dbits = 32u - (uint32_t)__clz((int)D);
     for (uint32_t d = lane; d <= D; d += 64) hh_c[d] = (uint32_t)Moff[(size_t)(D - d) * nb + b];
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
@@ -396,18 +410,22 @@ __global__ __launch_bounds__(64) void k_hh_place(const uint32_t *__restrict__ de
         const uint64_t v = v0 + lane;
         const bool in = v < hi;
         const uint32_t d = in ? deg[v] : 0xFFFFFFFFu;
-        uint32_t rank = 0, after = 0;
-        for (uint32_t j = 0; j < 64; ++j) {
-            const uint32_t dj = __shfl(d, j, 64);
-            rank += (j < lane && dj == d) ? 1u : 0u;
-            after += (j > lane && dj == d) ? 1u : 0u;
+        // the lanes of the same degree: one ballot per degree bit
+        uint64_t same = __ballot(in);
+        for (uint32_t q = 0; q < dbits; ++q) {
+            const bool bit = (d >> q) & 1u;
+            const uint64_t bal = __ballot(bit);
+            same &= bit ? bal : ~bal;
         }
+        const uint64_t below = (1ull << lane) - 1ull;
+        const uint32_t rank = (uint32_t)__popcll(same & below);
+        const bool last = (same & ~below) == (1ull << lane);
         uint32_t base = 0;
         if (in) base = hh_c[d];
         __builtin_amdgcn_wave_barrier();
         if (in && base + rank < n) {
             O[base + rank] = (uint32_t)v;
-            if (after == 0) hh_c[d] = base + rank + 1;  // the last lane of its degree in this round
+            if (last) hh_c[d] = base + rank + 1;  // the last lane of its degree in this round
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -431,109 +449,175 @@ __global__ __launch_bounds__(kBlock) void k_hh_bounds(const unsigned long long *
 // The steps, one wavefront.  E (D + 2 words, from k_hh_bounds) is copied to
 // LDS; status[0] = steps taken, status[1] = 1 if not graphical (2: an
 // inconsistent state, an internal error).
+//
+// While the run of positions of the largest residual d is longer than d
+// (E[d] > s + d), a step only takes the run's last d positions and its own
+// off it: a = s + 1, b = E[d], k = d, then E[d] -= d and s += 1.  All steps
+// for which that still holds -- step j needs E[d] - j d > s + j + d -- are
+// logged at once, 64 a trip, so a level of residuals costs one such bulk and
+// a step or two across its boundary; only the few positions whose residual is
+// larger than their run's length (hubs) are taken one by one.  One step at a
+// time the kernel was a chain of 190 ns per vertex: n = 2^20, Pld([5..1024],
+// 2.5) took 193 ms, now 0.98.
+//
+// The single steps for d > 64 move the values x + 1 .. d of E down by one.
+// Seen from z = y + s those values do not move at all (a covered position
+// loses one residual while s gains one), so the values above the boundary x
+// stay in a ring U indexed by y + s, the ones up to x in L indexed by y, and
+// a step touches only the values between the old and the new boundary.
+constexpr uint32_t kHhRing = 16384;  // > kHhMaxDeg + 1
+static_assert(kHhRing > kHhMaxDeg + 65, "U holds the values x + 1 .. d + 1 of one step");
+inline size_t hh_steps_lds_bytes(uint32_t D) { return (size_t)((D > 64 ? D : 64) + 2 + kHhRing) * 4; }
+
 __global__ __launch_bounds__(64) void k_hh_steps(const uint32_t *__restrict__ E0, uint32_t D, uint32_t n,
                                                  HhStep *__restrict__ log, uint32_t *__restrict__ status) {
-    extern __shared__ uint32_t E[];
+    extern __shared__ uint32_t hh_e[];
+    uint32_t *L = hh_e;  // values y <= x (max(D, 64) + 2 words)
+    uint32_t *U = L + (max(D, 64u) + 2);  // values y > x at (y + s) % kHhRing
     const uint32_t lane = threadIdx.x;
     const uint32_t ylast = max(D, 64u) + 1;  // lanes of the register phase read E[1 .. 64]
-    for (uint32_t y = lane; y <= ylast; y += 64) E[y] = y == 0 ? 0xFFFFFFFFu : (y <= D + 1 ? E0[y] : 0u);
+    for (uint32_t y = lane; y <= ylast; y += 64) L[y] = y == 0 ? 0xFFFFFFFFu : (y <= D + 1 ? E0[y] : 0u);
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
-    uint32_t s = 0, off = 0, dcur = D, fail = 0;
-    HhStep mine{0, 0, 0, 0};  // the step (s & 63) == lane of the current group
-    auto flush = [&](uint32_t upto) {  // writes the log entries of steps [upto & ~63, upto)
-        const uint32_t g = (upto - 1) & ~63u;
-        if (g + lane < upto) log[g + lane] = mine;
+    uint32_t s = 0, off = 0, fail = 0;
+    uint32_t d = D;  // no residual is larger
+    uint32_t x = max(D, 64u);  // values above it are in U
+    auto val = [&](uint32_t y) -> uint32_t { return y <= x ? L[y] : U[(y + s) % kHhRing]; };
+    auto bulk = [&](uint32_t ed, uint32_t q) {  // steps s .. s + q - 1 off the run of d that ends at ed
+        for (uint32_t j = lane; j < q; j += 64) log[s + j] = HhStep{s + j + 1, ed - j * d, d, off + j * d};
     };
-    // ---- steps while the largest residual exceeds 64: E in LDS ----
+    // ---- steps while the largest residual exceeds 64 ----
     // (a positive residual at position s means s < E[1] <= n; the checks on
     // s keep a corrupt state from writing past the log)
-    while (dcur > 64) {
+    while (d > 64) {
         if (s >= n) {
             fail = 2;
             break;
         }
-        // d = the largest y <= dcur with E[y] > s
-        uint32_t d = 0;
-        for (uint32_t top = dcur; top >= 1;) {
-            const uint32_t y = top >= lane ? top - lane : 0u;
-            const bool ok = y >= 1 && E[y] > s;
-            const uint64_t bal = __ballot(ok);
+        // d = the largest y <= d with E[y] > s
+        for (uint32_t top = d;;) {
+            const uint32_t y = top - lane;  // top > 64: y >= 1
+            const uint64_t bal = __ballot(val(y) > s);
             if (bal) {
                 d = top - (uint32_t)__ffsll((long long)bal) + 1;
                 break;
             }
-            top = top > 64 ? top - 64 : 0;
+            if (top <= 128) {  // the next 64 values end at 64 or below
+                d = 64;
+                break;
+            }
+            top -= 64;
         }
-        dcur = d;
-        if (d <= 64) break;  // the register phase takes this step
-        if (E[1] <= s + d) {  // fewer than d other positions of positive residual
+        if (d <= 64) break;  // the register phase takes this step (E gathered below)
+        const uint32_t ed = val(d);
+        if (ed > s + d) {
+            const uint32_t q = min((ed - s - d - 1) / (d + 1) + 1, n - s);
+            bulk(ed, q);
+            if (x < d) {  // boundary back to d
+                for (uint32_t y = x + 1 + lane; y < d + 1; y += 64) L[y] = U[(y + s) % kHhRing];
+                __builtin_amdgcn_wave_barrier();
+            }
+            x = d;
+            if (lane == 0) L[d] = ed - q * d;
+            off += q * d;
+            s += q;
+            __builtin_amdgcn_wave_barrier();
+            continue;
+        }
+        if (val(1) <= s + d) {  // fewer than d other positions of positive residual
             fail = 1;
             break;
         }
-        // x = the largest y <= d with E[y] > s + d (E[1] > s + d holds)
-        uint32_t lo = 1, hi = d;
-        while (hi > lo) {
-            const uint32_t st = (hi - lo + 64) / 64;
-            const uint32_t y = lo + lane * st;
-            const bool ok = y <= hi && E[y] > s + d;
-            const uint64_t bal = __ballot(ok);
-            const uint32_t top = 63u - (uint32_t)__clzll((long long)bal);
-            lo = lo + top * st;
-            hi = min(hi, lo + st - 1);
+        // x1 = the largest y < d with E[y] > s + d (E[d] is not, E[1] is):
+        // looked for from the last boundary on, 64 values a trip
+        uint32_t x1 = 0;
+        {
+            uint32_t y0 = min(x, d - 1);  // a value at or above the boundary's trip
+            if (val(y0) > s + d) {  // upwards: values fall with y
+                for (;;) {
+                    const uint32_t y = y0 + lane;
+                    const uint64_t bal = __ballot(y < d && val(y) > s + d);
+                    x1 = y0 + 63u - (uint32_t)__clzll((long long)bal);
+                    if (bal != ~0ull) break;
+                    if (x1 + 1 >= d) break;
+                    y0 = x1;  // holds, so the next trip's ballot is not empty
+                }
+            } else {  // downwards
+                for (;;) {
+                    const uint32_t y = y0 > lane ? y0 - lane : 1u;  // (E[1] holds)
+                    const uint64_t bal = __ballot(val(y) > s + d);
+                    if (bal) {
+                        x1 = y0 - ((uint32_t)__ffsll((long long)bal) - 1);
+                        break;
+                    }
+                    y0 -= 64;  // y0 > 64: lane 63 would have held E[1] otherwise
+                }
+            }
         }
-        const uint32_t x = lo;
-        const uint32_t a = max(E[x + 1], s + 1), b = E[x], k = s + d + 1 - a;
-        // E[y] <- max(E[y + 1], s + 1) for x < y <= d, in rising chunks
-        for (uint32_t y0 = x + 1; y0 <= d; y0 += 64) {
-            const uint32_t y = y0 + lane;
-            const uint32_t nv = y <= d ? max(E[y + 1], s + 1) : 0u;
-            __builtin_amdgcn_wave_barrier();
-            if (y <= d) E[y] = nv;
-            __builtin_amdgcn_wave_barrier();
+        const uint32_t ex1 = val(x1 + 1), b = val(x1);
+        const uint32_t a = max(ex1, s + 1), k = s + d + 1 - a;
+        // move the boundary from x to x1
+        if (x1 < x) {
+            for (uint32_t y = x1 + 1 + lane; y <= x; y += 64) U[(y + s) % kHhRing] = L[y];
+        } else {
+            for (uint32_t y = x + 1 + lane; y <= x1; y += 64) L[y] = U[(y + s) % kHhRing];
         }
-        if (lane == 0) E[x] = b - k;
         __builtin_amdgcn_wave_barrier();
-        if (lane == (s & 63u)) mine = HhStep{a, b, k, off};
+        x = x1;
+        if (lane == 0) {
+            L[x] = b - k;
+            log[s] = HhStep{a, b, k, off};
+            U[(d + 1 + s) % kHhRing] = 0;  // the next step's E[d]: only taken positions (E[d + 1] <= s)
+        }
+        __builtin_amdgcn_wave_barrier();
         off += d;
         ++s;
-        if ((s & 63u) == 0) flush(s);
+        // E[y] <- max(E[y + 1], s) for x < y <= d: the ring keeps the value, and
+        // where it is below s the positions are taken either way
     }
     // ---- the rest: lane l holds E[l + 1] ----
-    if (!fail && dcur > 0) {
-        uint32_t e = E[lane + 1];
+    if (!fail && d > 0) {
+        uint32_t e = val(lane + 1);
         for (;;) {
-            const uint32_t d = (uint32_t)__popcll(__ballot(e > s));
-            if (d == 0) break;
+            const uint32_t dd = (uint32_t)__popcll(__ballot(e > s));
+            if (dd == 0) break;
             if (s >= n) {
                 fail = 2;
                 break;
             }
-            const uint32_t x = (uint32_t)__popcll(__ballot(e > s + d));
-            if (x == 0) {
+            d = dd;
+            const uint32_t ed = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)(d - 1));  // E[d]
+            if (ed > s + d) {
+                const uint32_t q = min((ed - s - d - 1) / (d + 1) + 1, n - s);
+                bulk(ed, q);
+                if (lane == d - 1) e = ed - q * d;
+                off += q * d;
+                s += q;
+                continue;
+            }
+            const uint32_t x1 = (uint32_t)__popcll(__ballot(e > s + d));
+            if (x1 == 0) {
                 fail = 1;
                 break;
             }
-            // x and d are uniform: single-lane reads; E[x + 1] is lane x's
-            const uint32_t ex1 = x < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)e, (int)x) : 0u;
-            const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)(x - 1));  // E[x]
+            // x1 and d are uniform: single-lane reads; E[x1 + 1] is lane x1's
+            const uint32_t ex1 = x1 < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)e, (int)x1) : 0u;
+            const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)(x1 - 1));  // E[x1]
             const uint32_t a = max(ex1, s + 1), k = s + d + 1 - a;
             // E[y + 1] from the next lane: DPP wave_shl:1 (lane i reads lane
             // i + 1; every lane active), lane 63 takes E[65] = empty
             const uint32_t down = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)e, 0x130, 0xF, 0xF, false);
             const uint32_t nxt = lane < 63 ? down : 0u;
             const uint32_t y = lane + 1;
-            if (y > x && y <= d)
+            if (y > x1 && y <= d)
                 e = max(nxt, s + 1);
-            else if (y == x)
+            else if (y == x1)
                 e = b - k;
-            if (lane == (s & 63u)) mine = HhStep{a, b, k, off};
+            if (lane == 0) log[s] = HhStep{a, b, k, off};
             off += d;
             ++s;
-            if ((s & 63u) == 0) flush(s);
         }
     }
-    if (s & 63u) flush(s);
     if (lane == 0) {
         status[0] = s;
         status[1] = fail;

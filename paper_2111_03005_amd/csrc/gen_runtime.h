@@ -178,7 +178,8 @@ gesmc_status gen_hh_impl(gesmc_ctx *c, void *stream, uint32_t n, const uint32_t 
     GESMC_TRY(dev_alloc(c, (void **)&sblk.base, 256));
     uint32_t *w = (uint32_t *)sblk.base;  // [0] max degree, [2..3] sum
     GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(1), dim3(64), 0, w, (uint64_t)8));
-    GESMC_TRY(launch(c, s, KID_GEN, n, k_hh_stats, dim3(grid_stride_blocks(c, n)), dim3(kBlock), 0, d_deg, n, w,
+    const uint32_t stat_blocks = std::min<uint32_t>(grid_stride_blocks(c, n), (uint32_t)c->num_cus);
+    GESMC_TRY(launch(c, s, KID_GEN, n, k_hh_stats, dim3(stat_blocks), dim3(kBlock), 0, d_deg, n, w,
                      (unsigned long long *)(w + 2)));
     uint32_t hw[4] = {0, 0, 0, 0};
     GESMC_TRY(check_hip(hipMemcpyAsync(hw, w, 16, hipMemcpyDeviceToHost, s), "hipMemcpyAsync"));
@@ -226,7 +227,7 @@ gesmc_status gen_hh_impl(gesmc_ctx *c, void *stream, uint32_t n, const uint32_t 
                      (const unsigned long long *)Moff, O));
     GESMC_TRY(launch(c, s, KID_GEN, 0, k_hh_bounds, dim3(ceil_div(D + 2, kBlock)), dim3(kBlock), 0,
                      (const unsigned long long *)Moff, D, nb, E0));
-    const size_t step_lds = (size_t)(std::max<uint32_t>(D, 64) + 2) * 4;
+    const size_t step_lds = hh_steps_lds_bytes(D);
     GESMC_TRY(launch(c, s, KID_GEN_HH_STEPS, m, k_hh_steps, dim3(1), dim3(64), step_lds, (const uint32_t *)E0, D, n,
                      log, status));
     uint32_t hs[2] = {0, 0};

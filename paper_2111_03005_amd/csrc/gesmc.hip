@@ -2180,6 +2180,8 @@ gesmc_status gesmc_create(int hip_device, gesmc_ctx **out) {
     set_scatter_lds_limits<kTileLarge>();
     for (const void *f : {(const void *)k_resolve<false>, (const void *)k_resolve<true>})
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resolve_lds_bytes(kLdsCap));
+    (void)hipFuncSetAttribute((const void *)k_hh_steps, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)hh_steps_lds_bytes(kHhMaxDeg));
     (void)hipGetLastError();
     if (hipMemset(c->small, 0, words * 4) != hipSuccess ||
         hipHostMalloc((void **)&c->h_err, 64, hipHostMallocDefault) != hipSuccess ||

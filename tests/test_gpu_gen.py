@@ -145,3 +145,27 @@ def test_powerlaw_pipeline_full_size(ctx):
     deg = oracle.gen_pld(n, 2.5, 5, 1024, seed)[0]
     want = oracle.gen_relabel(oracle.gen_havel_hakimi(deg), n, seed)
     assert np.array_equal(got, want)
+
+
+def _hh_cases():
+    rng = np.random.default_rng(5)
+    yield "regular 64", np.full(3000, 64)
+    yield "regular 65", np.full(3000, 65)
+    yield "regular, run shorter than the degree", np.full(200, 150)
+    yield "63 64 65 66", np.repeat([63, 64, 65, 66], 500)
+    yield "two levels across 64", np.concatenate([np.full(90, 700), np.full(4000, 3)])
+    yield "hubs over a long run", np.concatenate([np.arange(400, 900), np.full(5000, 70), np.full(9000, 1)])
+    yield "falling staircase", np.repeat(np.arange(260, 10, -10), 11)
+    yield "near complete", rng.integers(380, 399, 400)
+    yield "one step short of graphical", np.concatenate([np.full(100, 140), np.full(60, 50)])
+    yield "largest degree the state takes", np.concatenate([np.full(3, 16000), np.full(20001, 2)])
+
+
+@pytest.mark.parametrize("label,deg", list(_hh_cases()), ids=lambda v: v if isinstance(v, str) else "")
+def test_havel_hakimi_runs_and_boundaries(ctx, label, deg):
+    """Runs of equal residuals longer and shorter than the residual, on both
+    sides of the 64 values the registers hold, against the oracle."""
+    deg = np.asarray(deg, dtype=np.uint32)
+    if deg.sum() % 2:
+        deg[-1] += 1
+    check_hh(ctx, deg, label)
