@@ -488,12 +488,22 @@ uint32_t scan_chunk(uint32_t ntiles) {
     return ch;
 }
 
+// Passes of at most kOneLevelBits bucket bits run in one level: a second one
+// costs three launches, and the records of so few buckets sit in L2 / MALL,
+// where short runs per digit do no harm.
+#ifndef GESMC_ONE_LEVEL_BITS
+#define GESMC_ONE_LEVEL_BITS 10
+#endif
+constexpr uint32_t kOneLevelBits = GESMC_ONE_LEVEL_BITS;
+static_assert(kOneLevelBits <= kMaxCoarseBits, "one level's digits");
+
 // Digit bits of the first level: an even split of B (so both levels write
 // runs of similar length; from 17 bits on, an odd B gives the first level
 // the smaller half, whose scatter then writes longer runs per digit, unless
 // `ceil_half`: batch permutations, whose first level stages more per record,
 // keep the larger half), or at most `cap` bits if the option sets one.
-uint32_t level1_bits(uint32_t B, uint32_t cap, bool ceil_half = false) {
+uint32_t level1_bits(uint32_t B, uint32_t cap, bool ceil_half = false, bool one_level = true) {
+    if (cap == 0 && one_level && B <= kOneLevelBits) return B;
     if (cap == 0) return std::min<uint32_t>(kMaxCoarseBits, B >= 17 && !ceil_half ? B / 2 : (B + 1) / 2);
     // the second level keeps at most kMaxLevelBits (its LDS counters)
     return std::min<uint32_t>(B, std::max<uint32_t>(cap, B > kMaxLevelBits ? B - kMaxLevelBits : 0));
@@ -539,6 +549,17 @@ Plan make_plan(const gesmc_ctx *c, uint32_t m) {
     p.tile = tile_for(m);
     p.ntiles1 = std::max<uint32_t>(1, ceil_div(m, p.tile));
     return p;
+}
+
+// One-level passes whose tiles' counts a workgroup sums itself instead of
+// three scan launches before it (k_scatter's self_off): as long as a thread
+// reads at most kSelfScanRows rows of counts.
+#ifndef GESMC_SELF_SCAN_ROWS
+#define GESMC_SELF_SCAN_ROWS 128
+#endif
+constexpr uint32_t kSelfScanRows = GESMC_SELF_SCAN_ROWS;
+bool scan_in_scatter(const Plan &p) {
+    return p.b2 == 0 && (uint64_t)p.ntiles1 * p.ncoarse <= (uint64_t)kSelfScanRows * kBlock;
 }
 
 // LDS of k_scatter: counters, staged indices (none for packed tuple
@@ -698,12 +719,16 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
                          dim3(persistent_blocks(c, k_tile_counts<kSrc1, kTile, true>, (size_t)nd1 * 4, p.ntiles1)),
                          dim3(kBlock), (size_t)nd1 * 4, src_i, src_k, t, k0, k1, shift1, (int)p.b1, 0u, n,
                          (const uint32_t *)nullptr, (const uint32_t *)nullptr, c->counts1, ba1));
-    GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colsum, dim3(nchunks), dim3(scan_threads), 0, c->counts1, p.ntiles1,
-                     (int)p.b1, chunk, c->partial));
-    GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colscan_top, dim3(1), dim3(kTopThreads), 0, c->partial, nchunks, (int)p.b1,
-                     c->coarse_off, c->tile_first, (uint32_t)kTile2));
-    GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colapply, dim3(nchunks), dim3(scan_threads), 0, c->counts1, p.ntiles1,
-                     (int)p.b1, chunk, c->partial, c->coarse_off));
+    if (scan_in_scatter(p)) {
+        ba1.self_off = c->coarse_off;
+    } else {
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colsum, dim3(nchunks), dim3(scan_threads), 0, c->counts1, p.ntiles1,
+                         (int)p.b1, chunk, c->partial));
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colscan_top, dim3(1), dim3(kTopThreads), 0, c->partial, nchunks,
+                         (int)p.b1, c->coarse_off, c->tile_first, (uint32_t)kTile2));
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colapply, dim3(nchunks), dim3(scan_threads), 0, c->counts1, p.ntiles1,
+                         (int)p.b1, chunk, c->partial, c->coarse_off));
+    }
     const int lvl1_out = p.b2 > 0 ? mid : dst;
     const size_t lds1 =
         scatter_lds_bytes(p.b1, kTile, kSrc1 == kSrcBatch, !src_emits_packed<kSrc1>(), ba1.dig_in_key == 0);
@@ -861,13 +886,16 @@ TuplePack tuple_pack(const gesmc_ctx *c, const Plan &p, uint32_t nslots, uint64_
     const int vb = width_below(vend), db = width_below(std::min(dend, vend)), w = vb + db;
     int kb = std::max(1, width_below(2ull * (nslots / 4) + 1));  // 2 ell < 2^kb, so ell < 2^kb - 1
     int local = 0;
-    if ((w - (int)p.b1 + kb + 1 > 64 || c->pack_tuples == 2) && mmax > 0) {
+    // the hash bits a first level of two would drop decide also where one level
+    // drops more: which calls pack does not depend on the number of passes
+    const int drop = (int)std::min(p.b1, level1_bits(p.bbits, c->level1_cap, false, false));
+    if ((w - drop + kb + 1 > 64 || c->pack_tuples == 2) && mmax > 0) {
         // a batch (mmax: its largest even record count): tags local to each
         // graph, codes below mmax, so its switches k < mmax / 2 < 2^kb - 1
         kb = std::max(1, width_below(mmax + 1));
         local = 1;
     }
-    if (w > 62 || w - (int)p.b1 + kb + 1 > 64 || w - (int)p.bbits < kCellBits) return pk;
+    if (w > 62 || w - drop + kb + 1 > 64 || w - (int)p.bbits < kCellBits) return pk;
     pk.w = w;
     pk.db = db;
     pk.kb = kb;

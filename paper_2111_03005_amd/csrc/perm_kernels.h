@@ -188,6 +188,10 @@ struct SrcArgs {
     // most 8 digit bits; the scatter then stages each record's digit in the
     // edge key's top byte (zero in such keys) instead of a digit array
     uint32_t dig_in_key;
+    // one-level passes over few tiles: the tiles' raw counts are in `offs` and
+    // every workgroup sums its own run bases (scan_in_scatter on the host);
+    // the first tile also writes the bucket offsets here
+    uint32_t *self_off;
 };
 
 template <int kSrc>
@@ -682,9 +686,49 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
                 c_aux[q] = (src_reads_aux<kSrc>() && in) ? ba.aux_in[ts.begin + p] : 0u;
             }
         }
-        for (uint32_t d = tid; d < nd; d += kThreads) {
-            cnt[d] = 0;
-            base[d] = offs[(size_t)w * nd + d];
+        if (kOne && ba.self_off) {
+            // digit d's records before this tile, and all of them: the tiles'
+            // counts are read 16 rows at a time (kThreads / nd threads share a
+            // digit's rows), then the digits' totals are scanned
+            const uint32_t share = nd < (uint32_t)kThreads ? (uint32_t)kThreads / nd : 1u;
+            const uint32_t rows = (nt + share - 1) / share;
+            for (uint32_t d = tid; d < nd; d += kThreads) {
+                cnt[d] = 0;
+                start[d] = 0;
+            }
+            lds_barrier();
+            const uint32_t part = nd < (uint32_t)kThreads ? tid / nd : 0u;
+            const uint32_t r0 = min(part * rows, nt), r1 = min(r0 + rows, nt);
+            for (uint32_t d = nd < (uint32_t)kThreads ? tid % nd : tid; d < nd; d += kThreads) {
+                uint32_t all = 0, before = 0;
+                for (uint32_t r = r0; r < r1; r += 16) {
+                    uint32_t x[16];
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) x[j] = r + j < r1 ? offs[(size_t)(r + j) * nd + d] : 0u;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        all += x[j];
+                        before += r + j < w ? x[j] : 0u;
+                    }
+                }
+                atomicAdd(&start[d], all);
+                atomicAdd(&cnt[d], before);
+            }
+            lds_barrier();
+            for (uint32_t d = tid; d < nd; d += kThreads) base[d] = cnt[d];
+            lds_barrier();
+            const uint32_t total = block_exclusive_scan<kThreads>(start, nd, tmp);
+            for (uint32_t d = tid; d < nd; d += kThreads) {
+                if (w == 0) ba.self_off[d] = start[d];
+                base[d] += start[d];
+                cnt[d] = 0;
+            }
+            if (w == 0 && tid == 0) ba.self_off[nd] = total;
+        } else {
+            for (uint32_t d = tid; d < nd; d += kThreads) {
+                cnt[d] = 0;
+                base[d] = offs[(size_t)w * nd + d];
+            }
         }
         if (tid == 0) s_total = 0;
         lds_barrier();

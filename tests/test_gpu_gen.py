@@ -153,12 +153,12 @@ def _hh_cases():
     yield "regular 65", np.full(3000, 65)
     yield "regular, run shorter than the degree", np.full(200, 150)
     yield "63 64 65 66", np.repeat([63, 64, 65, 66], 500)
-    yield "two levels across 64", np.concatenate([np.full(90, 700), np.full(4000, 3)])
+    yield "two levels across 64", np.concatenate([np.full(90, 700), np.full(25000, 3)])
     yield "hubs over a long run", np.concatenate([np.arange(400, 900), np.full(5000, 70), np.full(9000, 1)])
     yield "falling staircase", np.repeat(np.arange(260, 10, -10), 11)
     yield "near complete", rng.integers(380, 399, 400)
     yield "one step short of graphical", np.concatenate([np.full(100, 140), np.full(60, 50)])
-    yield "largest degree the state takes", np.concatenate([np.full(3, 16000), np.full(20001, 2)])
+    yield "largest degree the state takes", np.concatenate([np.full(3, 16000), np.full(20001, 3)])
 
 
 @pytest.mark.parametrize("label,deg", list(_hh_cases()), ids=lambda v: v if isinstance(v, str) else "")
