@@ -384,16 +384,17 @@ gesmc_status gesmc_server_info_get(gesmc_server *srv, gesmc_server_info *out);
  * code of switch k0 + q at d_outcome[q] (1 accepted, 2 loop, 3 target
  * present).  stats (host, nullable).  m < 2 copies the canonicalised input
  * (no two distinct indices exist).  Errors as for gesmc_run, d_out untouched.
- * Runs on one workgroup of the device per call: ES-MC has supersteps of
- * about sqrt(m) switches (Sec. 3), a latency-bound chain.
+ * Graphs of 4096 edges and more run in windows of up to 2^19 switches over the
+ * whole device, smaller ones on one workgroup in supersteps of about sqrt(m)
+ * switches (Sec. 3).
  */
 typedef struct gesmc_es_stats {
     uint64_t attempts, legal, rej_loop, rej_exists;
-    uint64_t supersteps;  /* ParES supersteps: runs of switches without a shared edge index, at
-                             most 1024 switches each                                          */
-    uint64_t rounds_sum;  /* decision rounds over all supersteps                              */
+    uint64_t supersteps;  /* ParES supersteps: windows, or on one workgroup runs of switches
+                             without a shared edge index, at most 1024 switches each           */
+    uint64_t rounds_sum;  /* decision rounds (a window: passes) over all supersteps            */
     uint32_t rounds_max;  /* most rounds in one superstep                                     */
-    uint32_t epochs;      /* launches (the edge set is rebuilt between them)                  */
+    uint32_t epochs;      /* times the edge set was built                                     */
     double ms_device;
 } gesmc_es_stats;
 

@@ -242,13 +242,15 @@ struct EsTuples {
 // Switches k = kbeg .. kend - 1 of one graph (one workgroup, kEsThreads
 // threads).  E, slot_of and H are the graph's edge list, slots and edge set
 // (mask = slot count - 1).  outcome (nullable) receives the outcome code of
-// switch k at outcome[k - kbase].
+// switch k at outcome[k - kbase].  unsettled (nullable): run only if it is set.
 __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__restrict__ E,
                                                          uint32_t *__restrict__ slot_of,
                                                          unsigned long long *__restrict__ H, uint32_t mask,
                                                          uint32_t m, uint32_t s0, uint32_t s1, uint64_t kbeg,
                                                          uint64_t kend, uint64_t kbase, uint8_t *__restrict__ outcome,
-                                                         EsCounters *__restrict__ ctr, uint32_t *__restrict__ err) {
+                                                         EsCounters *__restrict__ ctr, uint32_t *__restrict__ err,
+                                                         const uint32_t *__restrict__ unsettled) {
+    if (unsettled && *unsettled == 0) return;  // a window that k_es_win_commit wrote back
     __shared__ union {
         EsShared a;
         EsTuples t;
@@ -459,6 +461,321 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
         atomicAdd(&ctr->rounds, (unsigned long long)c_rounds);
         atomicMax(&ctr->rounds_max, (unsigned long long)c_rmax);
         atomicAdd(&ctr->used_slots, (unsigned long long)c_fresh);
+    }
+}
+
+// ---- windows over the whole chip -------------------------------------------
+// One workgroup is bound by the latency of its random reads and by supersteps
+// of about sqrt(m) switches (no shared edge index).  A window takes many more
+// switches of the sequence, shared indices included, and finds the sequential
+// outcome as a fixpoint: given every switch's sources and status, a source is
+// what the previous use of its index left there (its target if that switch was
+// accepted, else its source), and a target is present if the last accepted
+// earlier event on its key in the window inserted it, or, with no such event,
+// if it was an edge when the window began.  Each switch depends on earlier
+// ones only, so the assignment that reproduces itself is unique and is the
+// sequential execution.  Passes over all switches start from "accepted"
+// (99.8 % are) and repeat until one changes nothing; they need about as many
+// as the longest chain of switches that depend on each other's indices.
+// Kernels of a window: draws, links, 10 or 16 passes of two kernels (the ones
+// after the fixpoint return at once), commit.  A window without a fixpoint by
+// then is left to k_es_chain, which starts from the same state.
+// A kernel may read a status or source that another workgroup changes while it
+// runs; the change is counted, so the last pass ran on settled data.
+// m = 6.67e6, r = m / 2: 112 ms on one workgroup, 4.0 in windows of 2^19
+// (random reads and atomics on edges, edge set and event lists).
+constexpr uint32_t kEsUse = 0x7FFFFFFFu;       // pred: no earlier use of the index
+constexpr uint32_t kEsLastUse = 0x80000000u;   // pred flag: no later use in the window
+constexpr uint32_t kEsWalk = 4096;
+constexpr uint32_t kEsPasses = 16;             // of a window at most
+constexpr uint32_t kEsCtrCopies = 32;          // spread counters of the commits
+
+struct EsWindow {
+    uint2 *ij;               // per switch: indices, g in bit 31 of x
+    uint32_t *ulink, *pred;  // per use 2q + h: list link, previous use | kEsLastUse
+    unsigned long long *src, *tgt;  // per use: source and target keys (kEsEmpty: unknown)
+    uint8_t *pres;           // per use: the target is an edge when the window begins
+    uint8_t *st;             // per switch: ST_UNDECIDED = sources unknown
+    uint32_t *cell;          // event lists by key hash (node id + 1, 0: empty)
+    uint32_t *link;          // per node: next node id + 1; nodes 4q + e, then the pool
+    uint32_t *pool;          // event 4q + e of each pool node
+    uint32_t *ctl;           // [0] pool nodes taken, [1 + t] pass t changed something
+    uint32_t *touched;       // per pass a bit per cell: an event of the cell changed since the pass before
+    uint32_t *last;          // per edge index: tag + its newest use linked so far
+    uint32_t cap;            // switches per window at most
+    uint32_t cmask;          // cells - 1
+};
+constexpr uint32_t kEsCtl = kEsPasses + 1;
+
+__device__ __forceinline__ uint32_t es_cell(const EsWindow &w, unsigned long long key) {
+    return (uint32_t)(slot_hash(key) >> 20) & w.cmask;
+}
+
+// Pass t judges again only targets in touched cells (pass 0 judges all): one
+// bit per cell, 128 KB a pass at 2^18 switches, instead of a walk of two cells
+// per switch.
+__device__ __forceinline__ void es_touch(const EsWindow &w, uint32_t t, unsigned long long key) {
+    if (t == 0 || t >= kEsPasses || key == kEsEmpty) return;
+    const uint32_t c = es_cell(w, key);
+    atomicOr(w.touched + (size_t)(t - 1) * ((w.cmask + 1) / 32) + c / 32, 1u << (c & 31u));
+}
+__device__ __forceinline__ bool es_touched(const EsWindow &w, uint32_t t, unsigned long long key) {
+    if (t == 0) return true;
+    const uint32_t c = es_cell(w, key);
+    return (w.touched[(size_t)(t - 1) * ((w.cmask + 1) / 32) + c / 32] >> (c & 31u)) & 1u;
+}
+
+__device__ __forceinline__ void es_link_event(const EsWindow &w, uint32_t node, unsigned long long key) {
+    w.link[node] = atomicExch(w.cell + es_cell(w, key), node + 1);
+}
+
+// Sources e1, e2 of switch q become known in pass t (or change, `again`): targets, their
+// presence before the window, the guess "accepted", and the events.  False if
+// the pool has no node left.
+__device__ __forceinline__ bool es_set_sources(const EsWindow &w, uint32_t q, unsigned long long e1,
+                                               unsigned long long e2, const unsigned long long *H, uint32_t mask,
+                                               bool again, uint32_t t, uint32_t *err) {
+    const Targets T = switch_targets(e1, e2, (w.ij[q].x >> 31) != 0);
+    const unsigned long long key[4] = {e1, e2, T.loop ? kEsEmpty : T.A, T.loop ? kEsEmpty : T.B};
+    unsigned long long was[4] = {kEsEmpty, kEsEmpty, kEsEmpty, kEsEmpty};
+    if (again) {
+        was[0] = w.src[2 * q];
+        was[1] = w.src[2 * q + 1];
+        was[2] = w.tgt[2 * q];
+        was[3] = w.tgt[2 * q + 1];
+    }
+    w.src[2 * q] = key[0];
+    w.src[2 * q + 1] = key[1];
+    w.tgt[2 * q] = key[2];
+    w.tgt[2 * q + 1] = key[3];
+    w.st[q] = T.loop ? ST_LOOP : ST_LEGAL;
+    if (!T.loop) {
+        EsProbe pr[2];
+        es_probe2(H, mask, T.A, T.B, &pr[0], &pr[1], err);
+        w.pres[2 * q] = pr[0].found ? 1 : 0;
+        w.pres[2 * q + 1] = pr[1].found ? 1 : 0;
+    }
+    bool ok = true;
+    for (uint32_t e = 0; e < 4; ++e) {
+        // (an event that stays may count again: the status is back to "accepted")
+        es_touch(w, t, key[e]);
+        if (key[e] == was[e]) continue;
+        es_touch(w, t, was[e]);
+        if (key[e] == kEsEmpty) continue;
+        uint32_t node = 4 * q + e;
+        if (again) {
+            const uint32_t x = atomicAdd(&w.ctl[0], 1u);
+            if (x >= 4 * w.cap) {
+                ok = false;
+                break;
+            }
+            w.pool[x] = node;
+            node = 4 * w.cap + x;
+        }
+        es_link_event(w, node, key[e]);
+    }
+    return ok;
+}
+
+// Draws of switches k0 .. k0 + n - 1 and the per-index lists of their uses;
+// clears the window's event lists and control words.
+__global__ __launch_bounds__(kBlock) void k_es_win_draw(EsWindow w, uint32_t n, uint32_t passes, uint64_t k0,
+                                                        uint32_t m, uint32_t s0, uint32_t s1, uint32_t tag) {
+    const uint32_t tid = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
+    for (uint32_t c = tid; c <= w.cmask; c += stride) w.cell[c] = 0;
+    for (uint32_t c = tid; c < (passes - 1) * ((w.cmask + 1) / 32); c += stride) w.touched[c] = 0;
+    for (uint32_t c = tid; c < kEsCtl; c += stride) w.ctl[c] = 0;
+    for (uint32_t q = tid; q < n; q += stride) {
+        const EsDraw d = es_draw(k0 + q, m, s0, s1);
+        w.ij[q] = make_uint2(d.i | (d.g ? 0x80000000u : 0u), d.j);
+        w.ulink[2 * q] = atomicExch(&w.last[d.i], tag + 2 * q);
+        w.ulink[2 * q + 1] = atomicExch(&w.last[d.j], tag + 2 * q + 1);
+    }
+}
+
+// Previous use of each use's index; switches without one get their sources.
+__global__ __launch_bounds__(kBlock) void k_es_win_link(EsWindow w, uint32_t n, uint32_t tag,
+                                                        const unsigned long long *__restrict__ E,
+                                                        const unsigned long long *__restrict__ H, uint32_t mask,
+                                                        uint32_t *__restrict__ err) {
+    if (*err) return;
+    const uint32_t stride = gridDim.x * kBlock;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
+        const uint2 ij = w.ij[q];
+        const uint32_t idx[2] = {ij.x & 0x7FFFFFFFu, ij.y};
+        unsigned long long e[2];
+        bool first = true;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t best = kEsUse, flag = kEsLastUse;
+            // lists of at most 2n uses, each linked once; older tags end them
+            for (uint32_t u = w.last[idx[h]], c = 0; u - tag < 2 * n && c < 2 * n; u = w.ulink[u - tag], ++c) {
+                const uint32_t x = u - tag;
+                if (x > 2 * q + h) flag = 0;
+                if (x < 2 * q + h && (best == kEsUse || x > best)) best = x;
+            }
+            w.pred[2 * q + h] = best | flag;
+            first &= best == kEsUse;
+            e[h] = best == kEsUse ? E[idx[h]] : kEsEmpty;
+        }
+        if (first) {
+            es_set_sources(w, q, e[0], e[1], H, mask, false, 0, err);
+        } else {
+            w.src[2 * q] = e[0];
+            w.src[2 * q + 1] = e[1];
+            w.tgt[2 * q] = w.tgt[2 * q + 1] = kEsEmpty;
+            w.st[q] = ST_UNDECIDED;
+        }
+    }
+}
+
+// Whether key (an edge before the window: pres) is present when switch q
+// runs; 2 if its cell's list is too long to walk.
+__device__ __forceinline__ uint32_t es_present(const EsWindow &w, uint32_t q, unsigned long long key, uint32_t pres) {
+    uint32_t best = 0, res = pres;  // 1 + the latest accepted earlier event's switch
+    uint32_t x = w.cell[es_cell(w, key)];
+    for (uint32_t c = 0; x != 0; ++c) {
+        if (c == kEsWalk) return 2;
+        const uint32_t node = x - 1;
+        x = w.link[node];
+        const uint32_t ev = node < 4 * w.cap ? node : w.pool[node - 4 * w.cap];
+        const uint32_t p = ev >> 2, e = ev & 3u;
+        if (p >= q || p < best || w.st[p] != ST_LEGAL) continue;  // (p < q: in range)
+        if ((e < 2 ? w.src[2 * p + e] : w.tgt[2 * p + e - 2]) != key) continue;
+        best = p + 1;
+        res = e >= 2 ? 1u : 0u;
+    }
+    return res;
+}
+
+// Pass t, first half: sources of the switches whose indices were used before.
+// (Linking events and walking their lists in one kernel does not settle: a
+// walk that meets a node before its link is written misses the events behind
+// it, and the same two switches can meet so in every pass.)
+__global__ __launch_bounds__(kBlock) void k_es_win_sources(EsWindow w, uint32_t n, uint32_t t,
+                                                           const unsigned long long *__restrict__ H, uint32_t mask,
+                                                           uint32_t *__restrict__ err) {
+    if (*err || (t > 0 && w.ctl[t] == 0)) return;  // ctl[1 + t - 1]: the pass before changed nothing
+    const uint32_t stride = gridDim.x * kBlock;
+    bool changed = false;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
+        const uint32_t p0 = w.pred[2 * q] & kEsUse, p1 = w.pred[2 * q + 1] & kEsUse;
+        if (p0 == kEsUse && p1 == kEsUse) continue;
+        auto left = [&](uint32_t p, uint32_t u) -> unsigned long long {
+            if (p == kEsUse) return w.src[u];
+            const uint8_t sp = w.st[p >> 1];
+            if (sp == ST_UNDECIDED) return kEsEmpty;
+            return sp == ST_LEGAL ? w.tgt[p] : w.src[p];
+        };
+        const unsigned long long e1 = left(p0, 2 * q), e2 = left(p1, 2 * q + 1);
+        const bool again = w.st[q] != ST_UNDECIDED;
+        if (e1 == kEsEmpty || e2 == kEsEmpty) {
+            changed = true;
+        } else if (!again || e1 != w.src[2 * q] || e2 != w.src[2 * q + 1]) {
+            changed = true;
+            es_set_sources(w, q, e1, e2, H, mask, again, t, err);
+        }
+    }
+    if (w.ctl[0] > 4 * w.cap) changed = true;  // the pool ran out: no fixpoint may be declared
+    if (changed) w.ctl[1 + t] = 1;
+}
+
+// Pass t, second half: the status of every switch whose sources are known.
+__global__ __launch_bounds__(kBlock) void k_es_win_decide(EsWindow w, uint32_t n, uint32_t t,
+                                                          const uint32_t *__restrict__ err) {
+    if (*err || (t > 0 && w.ctl[t] == 0)) return;
+    const uint32_t stride = gridDim.x * kBlock;
+    bool changed = false;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
+        const uint8_t sq = w.st[q];
+        if (sq == ST_LOOP || sq == ST_UNDECIDED) continue;
+        const unsigned long long A = w.tgt[2 * q], B = w.tgt[2 * q + 1];
+        if (!es_touched(w, t, A) && !es_touched(w, t, B)) continue;
+        const uint32_t a = es_present(w, q, A, w.pres[2 * q]);
+        const uint32_t b = a == 1 ? 0u : es_present(w, q, B, w.pres[2 * q + 1]);
+        if (a == 2 || b == 2) {  // judged again, so the window does not settle
+            changed = true;
+            es_touch(w, t + 1, A);
+            es_touch(w, t + 1, B);
+        }
+        const uint8_t now = a == 1 || b == 1 ? ST_EXISTS : ST_LEGAL;
+        if (now != sq) {
+            w.st[q] = now;
+            changed = true;
+            es_touch(w, t + 1, w.src[2 * q]);
+            es_touch(w, t + 1, w.src[2 * q + 1]);
+            es_touch(w, t + 1, A);
+            es_touch(w, t + 1, B);
+        }
+    }
+    if (changed) w.ctl[1 + t] = 1;
+}
+
+// The outcomes of a window whose last pass changed nothing: counts, codes, and for each index its last
+// use's value; a changed edge leaves its old slot (a tombstone) and takes the
+// first free one of its chain.
+__global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n, uint32_t passes,
+                                                          unsigned long long *__restrict__ E,
+                                                          uint32_t *__restrict__ slot_of, unsigned long long *H,
+                                                          uint32_t mask, uint8_t *__restrict__ outcome,
+                                                          EsCounters *__restrict__ ctr, uint32_t *__restrict__ err) {
+    if (*err || w.ctl[passes] != 0) return;
+    __shared__ uint32_t c[4];
+    if (threadIdx.x < 4) c[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t stride = gridDim.x * kBlock;
+    uint32_t legal = 0, loop = 0, exists = 0, fresh = 0;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
+        const uint2 ij = w.ij[q];
+        const uint8_t sq = w.st[q];
+        legal += sq == ST_LEGAL;
+        loop += sq == ST_LOOP;
+        exists += sq == ST_EXISTS;
+        if (outcome) outcome[q] = sq;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (!(w.pred[2 * q + h] & kEsLastUse)) continue;
+            const uint32_t i = h ? ij.y : (ij.x & 0x7FFFFFFFu);
+            const unsigned long long key = sq == ST_LEGAL ? w.tgt[2 * q + h] : w.src[2 * q + h];
+            if (E[i] == key) continue;
+            E[i] = key;
+            __hip_atomic_store(H + slot_of[i], kEsTomb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t s = es_home(key, mask);
+            bool done = false;
+            // a slot is freed at most once and taken at most once here, so the lost races are bounded
+            for (uint64_t tries = 0; tries < 2 * (uint64_t)mask + 64 && !done; ++tries) {
+                const unsigned long long cur = __hip_atomic_load(H + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (cur == kEsEmpty || cur == kEsTomb) {
+                    if (atomicCAS(H + s, cur, key) == cur) {
+                        fresh += cur == kEsEmpty;
+                        slot_of[i] = s;
+                        done = true;
+                    }
+                } else {
+                    s = (s + 1) & mask;
+                }
+            }
+            if (!done) atomicOr(err, ERR_INTERNAL);
+        }
+    }
+    if (legal) atomicAdd(&c[0], legal);
+    if (loop) atomicAdd(&c[1], loop);
+    if (exists) atomicAdd(&c[2], exists);
+    if (fresh) atomicAdd(&c[3], fresh);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        EsCounters *o = ctr + (blockIdx.x % kEsCtrCopies);
+        if (c[0]) atomicAdd(&o->legal, (unsigned long long)c[0]);
+        if (c[1]) atomicAdd(&o->rej_loop, (unsigned long long)c[1]);
+        if (c[2]) atomicAdd(&o->rej_exists, (unsigned long long)c[2]);
+        if (c[3]) atomicAdd(&o->used_slots, (unsigned long long)c[3]);
+        if (blockIdx.x == 0) {
+            uint32_t rounds = 1;
+            while (rounds < passes && w.ctl[rounds]) ++rounds;
+            atomicAdd(&o->supersteps, 1ull);
+            atomicAdd(&o->rounds, (unsigned long long)rounds);
+            atomicMax(&o->rounds_max, (unsigned long long)rounds);
+        }
     }
 }
 

@@ -17,11 +17,71 @@ uint64_t es_slots(uint32_t m) {
     return T;
 }
 
+// Switches per window and passes over it; 0 switches (the chain on one
+// workgroup) below kEsWindowEdges edges, where a window's launches cost more
+// than the supersteps they replace.  Small graphs are bound by the launches, so
+// their windows take a larger share of m and the more passes that share needs
+// (m = 1.7e5, switches/s at m / 16, m / 8 and m / 4: 0.86e8, 1.2e8, 1.7e8;
+// m = 1.9e6: 4.7e8, 5.4e8, 5.2e8).
+constexpr uint32_t kEsWindowEdges = 4096;
+constexpr uint32_t kEsSmallEdges = 1u << 20;
+// At most 2^19 switches: the event lists and keys of a window then still sit
+// in L2 and MALL (m = 6.7e6, ms per call at 2^17, 2^18, 2^19: 5.2, 4.3, 4.0).
+constexpr uint32_t kEsWindowMax = 1u << 19;
+uint32_t es_window(uint32_t m) {
+    if (m < kEsWindowEdges) return 0;
+    return std::min<uint32_t>(m < kEsSmallEdges ? m / 4 : m / 8, kEsWindowMax);
+}
+uint32_t es_passes(uint32_t m) { return m < kEsSmallEdges ? kEsPasses : 10u; }
+
+// The window's arrays in one buffer (about 170 bytes a switch, and a word per edge).
+gesmc_status es_ensure_window(gesmc_ctx *c, uint32_t m, uint32_t W, EsWindow *out) {
+    uint32_t cells = 1024;
+    while (cells < 4 * W) cells <<= 1;
+    const uint64_t w = W;
+    const uint64_t sizes[] = {w * 8,  w * 8,  w * 8,           w * 16, w * 16,     w * 2,
+                              w,      cells * 4ull, w * 32, w * 16, kEsCtl * 4ull, cells / 8 * (kEsPasses - 1ull), m * 4ull};
+    uint64_t total = 0;
+    for (uint64_t b : sizes) total += (b + 255) & ~255ull;
+    if (total > c->es_cap_w) {
+        if (c->es_win) dev_free(c, c->es_win);
+        c->es_win = nullptr;
+        c->es_cap_w = 0;
+        GESMC_TRY(dev_alloc(c, (void **)&c->es_win, total));
+        c->es_cap_w = total;
+    }
+    unsigned char *p = c->es_win;
+    int k = 0;
+    auto take = [&]() {
+        unsigned char *q = p;
+        p += (sizes[k++] + 255) & ~255ull;
+        return q;
+    };
+    out->ij = (uint2 *)take();
+    out->ulink = (uint32_t *)take();
+    out->pred = (uint32_t *)take();
+    out->src = (unsigned long long *)take();
+    out->tgt = (unsigned long long *)take();
+    out->pres = (uint8_t *)take();
+    out->st = (uint8_t *)take();
+    out->cell = (uint32_t *)take();
+    out->link = (uint32_t *)take();
+    out->pool = (uint32_t *)take();
+    out->ctl = (uint32_t *)take();
+    out->touched = (uint32_t *)take();
+    out->last = (uint32_t *)take();
+    out->cap = W;
+    out->cmask = cells - 1;
+    return GESMC_OK;
+}
+
+constexpr size_t kEsCtrBytes = kEsCtrCopies * sizeof(EsCounters);
+
 gesmc_status es_ensure(gesmc_ctx *c, uint32_t m) {
     const uint64_t cap = std::max<uint64_t>(m, 1024), T = es_slots(m);
     if (!c->es_ctr) {
-        GESMC_TRY(dev_alloc(c, (void **)&c->es_ctr, sizeof(EsCounters)));
-        if (hipHostMalloc((void **)&c->h_es_ctr, sizeof(EsCounters), hipHostMallocDefault) != hipSuccess) {
+        GESMC_TRY(dev_alloc(c, (void **)&c->es_ctr, kEsCtrBytes));
+        if (hipHostMalloc((void **)&c->h_es_ctr, kEsCtrBytes, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             c->h_es_ctr = nullptr;
             set_error("hipHostMalloc failed");
@@ -70,13 +130,17 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     hipStream_t s = (hipStream_t)stream;
     const uint32_t m = (uint32_t)m64;
     GESMC_TRY(es_ensure(c, m));
+    const uint32_t W = (uint32_t)std::min<uint64_t>(es_window(m), r);
+    const uint32_t passes = es_passes(m);
+    EsWindow win{};
+    if (W > 0) GESMC_TRY(es_ensure_window(c, m, es_window(m), &win));
     const uint64_t T = es_slots(m), epoch = es_epoch(m);
     const uint32_t mask = (uint32_t)(T - 1);
     const uint32_t s0 = (uint32_t)seed, s1 = (uint32_t)(seed >> 32);
     GESMC_TRY(check_hip(hipEventRecord(c->call_a, s), "hipEventRecord"));
     GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(4), dim3(256), 0, c->err, (uint64_t)64));
-    GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(1), dim3(64), 0, (uint32_t *)c->es_ctr,
-                     (uint64_t)(sizeof(EsCounters) / 4)));
+    GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(2), dim3(256), 0, (uint32_t *)c->es_ctr,
+                     (uint64_t)(kEsCtrBytes / 4)));
     if (m > 0)
         GESMC_TRY(launch(c, s, KID_LOAD, m, k_load, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                          (const unsigned long long *)d_in, m, n, c->es_slot, c->es_E, c->err, 0u));
@@ -90,9 +154,34 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
             GESMC_TRY(launch(c, s, KID_ES_BUILD, m, k_es_insert_all, dim3(grid_stride_blocks(c, m)), dim3(kBlock),
                              0, (const unsigned long long *)c->es_E, m, c->es_H, mask, c->es_slot, c->err,
                              c->es_ctr));
-            if (ke > kb)
+            if (ke > kb && W == 0)
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, ke - kb, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
-                                 c->es_slot, c->es_H, mask, m, s0, s1, kb, ke, k0, d_outcome, c->es_ctr, c->err));
+                                 c->es_slot, c->es_H, mask, m, s0, s1, kb, ke, k0, d_outcome, c->es_ctr, c->err,
+                                 (const uint32_t *)nullptr));
+            if (ke > kb && W > 0)  // uses of earlier epochs must read as none
+                GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
+                                 win.last, (uint64_t)m));
+            uint32_t tag = 1;  // of the window's uses: 2 W a window, below 2 (epoch + W) in an epoch
+            for (uint64_t wb = kb; W > 0 && wb < ke; tag += 2 * W, wb += W) {
+                const uint32_t nw = (uint32_t)std::min<uint64_t>(W, ke - wb);
+                const dim3 grid(ceil_div(nw, kBlock)), block(kBlock);
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, nw, k_es_win_draw, grid, block, 0, win, nw, passes, wb, m,
+                                 s0, s1, tag));
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_link, grid, block, 0, win, nw, tag,
+                                 (const unsigned long long *)c->es_E, (const unsigned long long *)c->es_H, mask,
+                                 c->err));
+                for (uint32_t t = 0; t < passes; ++t) {
+                    GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_sources, grid, block, 0, win, nw, t,
+                                     (const unsigned long long *)c->es_H, mask, c->err));
+                    GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_decide, grid, block, 0, win, nw, t,
+                                     (const uint32_t *)c->err));
+                }
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_commit, grid, block, 0, win, nw, passes, c->es_E, c->es_slot,
+                                 c->es_H, mask, d_outcome ? d_outcome + (wb - k0) : nullptr, c->es_ctr, c->err));
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
+                                 c->es_slot, c->es_H, mask, m, s0, s1, wb, wb + nw, k0, d_outcome, c->es_ctr, c->err,
+                                 (const uint32_t *)(win.ctl + passes)));
+            }
             ++launches;
             if (ke - k0 >= r) break;
         }
@@ -103,13 +192,22 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
                          (const uint32_t *)c->err));
     GESMC_TRY(check_hip(hipEventRecord(c->call_b, s), "hipEventRecord"));
     GESMC_TRY(check_hip(hipMemcpyAsync(c->h_err, c->err, 4, hipMemcpyDeviceToHost, s), "hipMemcpyAsync"));
-    GESMC_TRY(check_hip(hipMemcpyAsync(c->h_es_ctr, c->es_ctr, sizeof(EsCounters), hipMemcpyDeviceToHost, s),
+    GESMC_TRY(check_hip(hipMemcpyAsync(c->h_es_ctr, c->es_ctr, kEsCtrBytes, hipMemcpyDeviceToHost, s),
                         "hipMemcpyAsync"));
     GESMC_TRY(check_hip(hipStreamSynchronize(s), "hipStreamSynchronize"));
     if (c->profile) collect_profile(c);
     GESMC_TRY(map_err(*c->h_err));
     if (stats) {
-        const EsCounters &h = *c->h_es_ctr;
+        EsCounters h = c->h_es_ctr[0];
+        for (uint32_t q = 1; q < kEsCtrCopies; ++q) {
+            const EsCounters &o = c->h_es_ctr[q];
+            h.legal += o.legal;
+            h.rej_loop += o.rej_loop;
+            h.rej_exists += o.rej_exists;
+            h.supersteps += o.supersteps;
+            h.rounds += o.rounds;
+            h.rounds_max = std::max(h.rounds_max, o.rounds_max);
+        }
         memset(stats, 0, sizeof(*stats));
         stats->attempts = m >= 2 ? r : 0;
         stats->legal = h.legal;

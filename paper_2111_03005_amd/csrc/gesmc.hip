@@ -246,7 +246,8 @@ struct gesmc_ctx {
     // ParES (gesmc_run_es): edge list, slot of each edge, edge set, counters
     unsigned long long *es_E = nullptr, *es_H = nullptr;
     uint32_t *es_slot = nullptr;
-    uint64_t es_cap_m = 0, es_cap_T = 0;
+    unsigned char *es_win = nullptr;  // window arrays (EsWindow)
+    uint64_t es_cap_m = 0, es_cap_T = 0, es_cap_w = 0;
     EsCounters *es_ctr = nullptr, *h_es_ctr = nullptr;
     // side streams of the batch's LDS small-graph kernels (default priority),
     // forked from and joined back into the call's stream with these events
@@ -2259,7 +2260,7 @@ void gesmc_destroy(gesmc_ctx *c) {
     if (c->call_b) (void)hipEventDestroy(c->call_b);
     if (c->h_up) (void)hipHostFree(c->h_up);
     if (c->h_hr) (void)hipHostFree(c->h_hr);
-    for (void *q : {(void *)c->es_E, (void *)c->es_H, (void *)c->es_slot, (void *)c->es_ctr})
+    for (void *q : {(void *)c->es_E, (void *)c->es_H, (void *)c->es_slot, (void *)c->es_ctr, (void *)c->es_win})
         if (q) dev_free(c, q);
     if (c->h_es_ctr) (void)hipHostFree(c->h_es_ctr);
     if (c->hr_dev) dev_free(c, c->hr_dev);

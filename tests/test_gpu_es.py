@@ -90,6 +90,20 @@ def test_es_gnp_small_and_powerlaw(ctx):
     check_es(ctx, E, 20000, 3, 0, 200000, label="power-law hubs gamma 2.01", outcomes=True)
 
 
+# windows: the smallest graph that has them and its neighbours (m // 4
+# switches up to 2^20 edges, m // 8 from there on), one switch less and more
+# than a window or two, dense and sparse
+@pytest.mark.parametrize("m,r", [(4095, 2000), (4096, 1), (4096, 1023), (4096, 1024), (4096, 1025), (4097, 2049),
+                                 (30011, 7502), (30011, 15005), (1048575, 262144), (1048577, 131073)])
+@pytest.mark.parametrize("n,p", [(300, 0.75), (3000, 0.01), (140000, 1.2e-4)])
+def test_es_windows_exact(ctx, m, r, n, p):
+    E = graphgen.gnp(n, p, 77)
+    if len(E) < m:
+        pytest.skip("the graph has fewer edges")
+    E = np.random.default_rng(m + r).permutation(E)[:m]
+    check_es(ctx, E, n, 5, 3, r, label="windows n=%d" % n, outcomes=True)
+
+
 def test_es_epochs_and_resume(ctx):
     """More switches than one epoch (the edge set is rebuilt between launches),
     and run(r1) followed by run(r2, k0 + r1) equals run(r1 + r2)."""
