@@ -185,6 +185,11 @@ struct gesmc_ctx {
     // radix bookkeeping: per-tile digit counts / run bases of both levels, chunk sums
     uint64_t cap_counts1 = 0, cap_counts2 = 0, cap_partial = 0;
     uint32_t *counts1 = nullptr, *counts2 = nullptr, *partial = nullptr;
+    // the next superstep's first level while this one runs (k_decide_scatter):
+    // counts, chunk sums, bucket offsets and tile map, per-block outcome counts
+    uint32_t *ncounts = nullptr, *npartial = nullptr, *noff = nullptr, *fslot = nullptr;
+    uint64_t cap_ncounts = 0, cap_npartial = 0, cap_noff = 0, cap_fslot = 0;
+    uint2 *pos = nullptr;       // where waiting switches' records stand (inside a tuple buffer)
     uint32_t *small = nullptr;  // counters, histograms, offsets (fixed size)
     uint16_t *small_pi = nullptr;  // permutations of the small-graph path (kSmallPiSteps rows of kCmpMax)
     std::string device_key;        // architecture and PCI address (the tuning cache's device)
@@ -287,11 +292,12 @@ void free_buffers(gesmc_ctx *c) {
     }
     if (c->info) dev_free(c, c->info);
     c->info = nullptr;
-    for (uint32_t **pp : {&c->counts1, &c->counts2, &c->partial}) {
+    for (uint32_t **pp : {&c->counts1, &c->counts2, &c->partial, &c->ncounts, &c->npartial, &c->noff, &c->fslot}) {
         if (*pp) dev_free(c, *pp);
         *pp = nullptr;
     }
     c->cap_counts1 = c->cap_counts2 = c->cap_partial = 0;
+    c->cap_ncounts = c->cap_npartial = c->cap_noff = c->cap_fslot = 0;
     c->cap_tu = 0;
     c->tab = nullptr;
     c->sw_slot = nullptr;
@@ -586,7 +592,9 @@ void set_scatter_lds_limits_one() {
                           (const void *)k_scatter<kSrcEmitPacked, kTile, scatter_threads(kTile), kOne>,
                           (const void *)k_scatter<kSrcEmitPackedLocal, kTile, scatter_threads(kTile), kOne>,
                           (const void *)k_scatter<kSrcPacked, kTile, scatter_threads(kTile), kOne>,
-                          (const void *)k_scatter<kSrcIdx, kTile, scatter_threads(kTile), kOne>})
+                          (const void *)k_scatter<kSrcIdx, kTile, scatter_threads(kTile), kOne>,
+                          (const void *)k_decide_scatter<kSrcPerm, kTile, scatter_threads(kTile), kOne>,
+                          (const void *)k_decide_scatter<kSrcBatch, kTile, scatter_threads(kTile), kOne>})
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)scatter_lds_bytes(kMaxLevelBits, kTile));
 }
@@ -668,15 +676,21 @@ RadixWords radix_words(const Plan &p) {
 // (k_emit_counts) when the tuples are computed from the pair records; its
 // `grid` workgroups store their outcome counts in bslot[0, grid).
 struct EmitOut {
-    uint2 *info;
     uint8_t *st;
     uint32_t *out_idx;
     unsigned long long *out_key;
     uint4 *bslot;
     uint32_t *ucount;
     uint32_t grid;
+    NextCounts nc;  // next superstep's first-level counts, if taken there
 };
 constexpr uint32_t kEmitSlotsMax = 8192;  // workgroups of k_emit_counts (count slots)
+
+// What of a distribution's first level is done already: nothing, its tile
+// counts (in c->counts1), or all of it (records in buffer `mid`, offsets and
+// tile map in c->noff).
+enum Level1 { kLevel1Todo, kLevel1Counted, kLevel1Done };
+constexpr uint32_t kNoffTiles = (1u << kMaxCoarseBits) + 8;  // c->noff: offsets, then first tiles
 
 // Two-level MSD radix distribution of the n records (idx/tag, key) in buffer
 // set `src` into `dst` (one level) or via `mid` into `dst` (two levels), by
@@ -690,7 +704,7 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
                               int dst, int *out, const uint32_t **bucket_off, uint32_t *nbuckets, int kid_counts1,
                               int kid_scatter1, int kid_counts2, int kid_scatter2, SrcArgs ba1, SrcArgs ba2,
                               const uint32_t *in_idx, const unsigned long long *in_key, const EmitOut *eo,
-                              bool counts1_ready) {
+                              Level1 level1) {
     // level-1 input: buffer `src`, or the given arrays (the pair records of kSrcEmit)
     const uint32_t *src_i = in_idx ? in_idx : idx[src];
     const unsigned long long *src_k = in_key ? in_key : key[src];
@@ -707,7 +721,7 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
         if (eo) {  // the emit's outputs in the same pass
             GESMC_TRY(launch(c, s, kid_counts1, n, k_emit_counts<kSrc1, kTile>, dim3(eo->grid), dim3(kBlock),
                              (size_t)nd1 * 4, src_i, src_k, t, k0, k1, shift1, (int)p.b1, n, c->counts1, ba1,
-                             eo->info, eo->st, eo->out_idx, eo->out_key, eo->bslot, eo->ucount));
+                             eo->st, eo->out_idx, eo->out_key, eo->bslot, eo->ucount, eo->nc));
             fused_emit = true;
         }
     }
@@ -715,7 +729,13 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
         set_error("internal: emit outputs need a tuple source computed from the pair records");
         return GESMC_E_INTERNAL;
     }
-    if (!fused_emit && !counts1_ready)  // (ready: counted by the previous superstep's first decision round)
+    const uint32_t *coarse = c->coarse_off, *tile_first = c->tile_first;
+    const int lvl1_out = p.b2 > 0 ? mid : dst;
+    if (level1 == kLevel1Done) {
+        coarse = c->noff;
+        tile_first = c->noff + kNoffTiles;
+    } else {
+    if (!fused_emit && level1 == kLevel1Todo)  // (else counted by the previous superstep)
         GESMC_TRY(launch(c, s, kid_counts1, n, k_tile_counts<kSrc1, kTile, true>,
                          dim3(persistent_blocks(c, k_tile_counts<kSrc1, kTile, true>, (size_t)nd1 * 4, p.ntiles1)),
                          dim3(kBlock), (size_t)nd1 * 4, src_i, src_k, t, k0, k1, shift1, (int)p.b1, 0u, n,
@@ -730,21 +750,28 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
         GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colapply, dim3(nchunks), dim3(scan_threads), 0, c->counts1, p.ntiles1,
                          (int)p.b1, chunk, c->partial, c->coarse_off));
     }
-    const int lvl1_out = p.b2 > 0 ? mid : dst;
     const size_t lds1 =
         scatter_lds_bytes(p.b1, kTile, kSrc1 == kSrcBatch, !src_emits_packed<kSrc1>(), ba1.dig_in_key == 0);
-    const size_t lds2 = scatter_lds_bytes(p.b2, kTile2, kSrc2 == kSrcBatch, kSrc2 != kSrcPacked,
-                                          kSrc2 != kSrcPacked && kSrc2 != kSrcHashed && ba2.dig_in_key == 0);
-    GESMC_TRY(launch(c, s, kid_scatter1, n, k_scatter<kSrc1, kTile, scatter_threads(kTile), true>,
-                     dim3(persistent_blocks(c, k_scatter<kSrc1, kTile, scatter_threads(kTile), true>, lds1, p.ntiles1, scatter_threads(kTile))), dim3(scatter_threads(kTile)), lds1, src_i, src_k, idx[lvl1_out], key[lvl1_out], t, k0,
-                     k1, shift1, (int)p.b1, 0u, n, (const uint32_t *)nullptr, (const uint32_t *)nullptr,
-                     (const uint32_t *)c->counts1, c->err, ba1));
+    auto scatter1 = [&](auto kern) {
+        constexpr int kThreads = scatter_threads(kTile);
+        return launch(c, s, kid_scatter1, n, kern, dim3(persistent_blocks(c, kern, lds1, p.ntiles1, kThreads)),
+                      dim3(kThreads), lds1, src_i, src_k, idx[lvl1_out], key[lvl1_out], t, k0, k1, shift1, (int)p.b1,
+                      0u, n, (const uint32_t *)nullptr, (const uint32_t *)nullptr, (const uint32_t *)c->counts1,
+                      c->err, ba1);
+    };
+    if (ba1.self_off)
+        GESMC_TRY(scatter1(k_scatter<kSrc1, kTile, scatter_threads(kTile), true, true>));
+    else
+        GESMC_TRY(scatter1(k_scatter<kSrc1, kTile, scatter_threads(kTile), true>));
+    }
     if (p.b2 == 0) {
-        *out = dst;
-        *bucket_off = c->coarse_off;
+        *out = lvl1_out;
+        *bucket_off = coarse;
         *nbuckets = p.ncoarse;
         return GESMC_OK;
     }
+    const size_t lds2 = scatter_lds_bytes(p.b2, kTile2, kSrc2 == kSrcBatch, kSrc2 != kSrcPacked,
+                                          kSrc2 != kSrcPacked && kSrc2 != kSrcHashed && ba2.dig_in_key == 0);
     const uint32_t nd2 = 1u << p.b2;
     const uint32_t tiles2 = (uint32_t)level2_tiles(p) + p.ncoarse;  // >= sum over segments of their tiles
     GESMC_TRY(ensure_words(c, &c->counts2, &c->cap_counts2, rw.counts2));
@@ -753,12 +780,12 @@ gesmc_status radix_distribute_t(gesmc_ctx *c, hipStream_t s, const Plan &p, uint
     GESMC_TRY(launch(c, s, kid_counts2, n, k_tile_counts<kSrc2, kTile2, false>,
                      dim3(persistent_blocks(c, k_tile_counts<kSrc2, kTile2, false>, (size_t)nd2 * 4, tiles2)), dim3(kBlock),
                      (size_t)nd2 * 4, idx[mid], key[mid], t, k0, k1, shift2, (int)p.b2, p.ncoarse, 0u,
-                     (const uint32_t *)c->coarse_off, (const uint32_t *)c->tile_first, c->counts2, ba2));
+                     coarse, tile_first, c->counts2, ba2));
     GESMC_TRY(launch(c, s, KID_SCAN, 0, k_segscan, dim3(p.ncoarse), dim3(kBlock), ((size_t)nd2 + kBlock + 1) * 4,
-                     c->counts2, (int)p.b2, p.ncoarse, c->coarse_off, c->tile_first, c->fine_off));
+                     c->counts2, (int)p.b2, p.ncoarse, coarse, tile_first, c->fine_off));
     GESMC_TRY(launch(c, s, kid_scatter2, n, k_scatter<kSrc2, kTile2, scatter_threads(kTile2), false>,
                      dim3(persistent_blocks(c, k_scatter<kSrc2, kTile2, scatter_threads(kTile2), false>, lds2, tiles2, scatter_threads(kTile2))), dim3(scatter_threads(kTile2)), lds2, idx[mid], key[mid], idx[dst], key[dst], t, k0, k1, shift2, (int)p.b2,
-                     p.ncoarse, 0u, (const uint32_t *)c->coarse_off, (const uint32_t *)c->tile_first,
+                     p.ncoarse, 0u, coarse, tile_first,
                      (const uint32_t *)c->counts2, c->err, ba2));
     *out = dst;
     *bucket_off = c->fine_off;
@@ -772,11 +799,11 @@ gesmc_status radix_distribute(gesmc_ctx *c, hipStream_t s, const Plan &p, uint32
                               int dst, int *out, const uint32_t **bucket_off, uint32_t *nbuckets, int kid_counts1,
                               int kid_scatter1, int kid_counts2, int kid_scatter2, SrcArgs ba1, SrcArgs ba2,
                               const uint32_t *in_idx = nullptr, const unsigned long long *in_key = nullptr,
-                              const EmitOut *eo = nullptr, bool counts1_ready = false) {
+                              const EmitOut *eo = nullptr, Level1 level1 = kLevel1Todo) {
 #define GESMC_RADIX_T(T1, T2)                                                                                   \
     radix_distribute_t<kSrc1, kSrc2, T1, T2>(c, s, p, n, t, k0, k1, idx, key, src, mid, dst, out, bucket_off, nbuckets, \
                                              kid_counts1, kid_scatter1, kid_counts2, kid_scatter2, ba1, ba2, in_idx,  \
-                                             in_key, eo, counts1_ready)
+                                             in_key, eo, level1)
     const uint32_t t2 = p.tile2 ? p.tile2 : p.tile;
     if (p.tile == (uint32_t)kTileLarge)
         return t2 == (uint32_t)kTileLarge ? GESMC_RADIX_T(kTileLarge, kTileLarge) : GESMC_RADIX_T(kTileLarge, kTileSmall);
@@ -803,10 +830,11 @@ struct BatchStep {
 // per graph with its own keys if `bs` describes a batch (plan bits then
 // number the global buckets).  Returns the buffer index holding the sorted
 // records.
-// counts1_ready: the first level's tile counts of superstep t are in
-// c->counts1 already (k_decide_chain of superstep t - 1 wrote them).
+// level1: what superstep t - 1 did of the first level (all of it: the records
+// in buffer src are in its order).
 gesmc_status permute(gesmc_ctx *c, hipStream_t s, const Plan &p, uint32_t t, uint32_t k0, uint32_t k1, int src,
-                     int *sorted_out, bool clear_table, const BatchStep *bs = nullptr, bool counts1_ready = false) {
+                     int *sorted_out, bool clear_table, const BatchStep *bs = nullptr,
+                     Level1 level1 = kLevel1Todo) {
     const uint32_t m = p.m;
     const int X = (src + 1) % 3, Y = (src + 2) % 3;
     // the table strategy resets its table, statuses and list counters here;
@@ -832,25 +860,26 @@ gesmc_status permute(gesmc_ctx *c, hipStream_t s, const Plan &p, uint32_t t, uin
     int dist = 0;
     const uint32_t *boff = nullptr;
     uint32_t nb = 0;
-    const int mid = X, dst = p.b2 > 0 ? Y : X;
+    // two levels: X, Y, sorted into X; one level: Y (or src, done already), sorted into X
+    const int mid = level1 == kLevel1Done ? src : p.b2 > 0 ? X : Y, dst = p.b2 > 0 ? Y : mid;
     if (bs) {
         const SrcArgs ba1{bs->gr, bs->pg, bs->bk, bs->step, (int)p.bbits};
         const SrcArgs ba2{bs->gr, bs->bk, nullptr, bs->step, (int)p.bbits};
         GESMC_TRY((radix_distribute<kSrcBatch, kSrcBucket>(c, s, p, m, t, k0, k1, c->idx, c->key, src, mid, dst, &dist,
                                                            &boff, &nb, KID_COUNTS1, KID_SCATTER1, KID_COUNTS2,
                                                            KID_SCATTER2, ba1, ba2, nullptr, nullptr, nullptr,
-                                                           counts1_ready)));
+                                                           level1)));
     } else {
         SrcArgs pa{};
         pa.dig_in_key = p.dig_in_key;
         GESMC_TRY((radix_distribute<kSrcPerm, kSrcPerm>(c, s, p, m, t, k0, k1, c->idx, c->key, src, mid, dst, &dist,
                                                         &boff, &nb, KID_COUNTS1, KID_SCATTER1, KID_COUNTS2,
-                                                        KID_SCATTER2, pa, pa, nullptr, nullptr, nullptr,
-                                                        counts1_ready)));
+                                                        KID_SCATTER2, pa, pa, nullptr, nullptr, nullptr, level1)));
     }
     const int sorted = (dist == X) ? Y : X;  // sort into the buffer not holding the buckets
     GESMC_TRY(launch(c, s, KID_SORT, m, k_sort_buckets, dim3(persistent_blocks(c, k_sort_buckets, sort_lds, nb)),
-                     dim3(kBlock), sort_lds, c->idx[dist], c->key[dist], c->idx[sorted], c->key[sorted], c->key[src],
+                     dim3(kBlock), sort_lds, c->idx[dist], c->key[dist], c->idx[sorted], c->key[sorted],
+                     c->key[3 - dist - sorted],
                      t, k0, k1, (int)p.bbits, boff, nb, m, c->sort_cap, c->ctr_step, bs ? bs->gr : nullptr,
                      bs ? bs->ngraphs : 0u, bs ? bs->step : 0u));
     *sorted_out = sorted;
@@ -912,6 +941,7 @@ TuplePack tuple_pack(const gesmc_ctx *c, const Plan &p, uint32_t nslots, uint64_
 Winners winners(gesmc_ctx *c, int parts, int scratch) {
     uint32_t *w = reinterpret_cast<uint32_t *>(c->tu_key[3 - parts - scratch]);
     c->wn = Winners{w, w + c->cap_tu};
+    c->pos = reinterpret_cast<uint2 *>(c->tu_key[scratch]);  // free once the resolve is done
     return c->wn;
 }
 
@@ -945,7 +975,8 @@ gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots,
         GESMC_TRY(launch(c, s, KID_RESOLVE, nslots, k_resolve<true>,
                          dim3(persistent_blocks(c, k_resolve<true>, rlds, np)), dim3(kBlock), rlds, c->tu_tag[parts],
                          c->tu_key[parts], c->tu_tag[scratch], c->tu_key[scratch], (int)p.b2, poff, np, c->sort_cap,
-                         c->info, c->err, dup_bit, c->ctr_step, ge, pk, winners(c, parts, scratch)));
+                         c->info, c->err, dup_bit, c->ctr_step, ge, pk, winners(c, parts, scratch),
+                         (uint32_t *)c->st));
         return GESMC_OK;
     }
     if (emit)
@@ -964,8 +995,51 @@ gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots,
                      dim3(persistent_blocks(c, k_resolve<false>, rlds, np)), dim3(kBlock), rlds, c->tu_tag[parts],
                      c->tu_key[parts], c->tu_tag[scratch], c->tu_key[scratch], (int)p.bbits, poff, np, c->sort_cap,
                      c->info, c->err, dup_bit, c->ctr_step, ge, TuplePack{0, 0, 0, 0, 0, 0},
-                     winners(c, parts, scratch)));
+                     winners(c, parts, scratch), (uint32_t *)c->st));
     return GESMC_OK;
+}
+
+// Round 1 of a superstep with the next one's first radix level (plan q,
+// superstep t, counts in c->ncounts): the level's scan, then k_decide_scatter
+// from the pair records si / sk into buffer 0.
+template <int kSrc, int kTile>
+gesmc_status decide_and_scatter_t(gesmc_ctx *c, hipStream_t s, const Plan &q, uint32_t t, uint32_t k0, uint32_t k1,
+                                  SrcArgs sa, const uint32_t *si, const unsigned long long *sk, uint4 *slots,
+                                  uint32_t cls) {
+    constexpr int kThreads = scatter_threads(kTile);
+    uint32_t *off = c->noff, *tiles = c->noff + kNoffTiles;
+    if (scan_in_scatter(q)) {
+        sa.self_off = off;
+    } else {
+        const uint32_t chunk = scan_chunk(q.ntiles1), nchunks = ceil_div(q.ntiles1, chunk);
+        const uint32_t threads = std::max<uint32_t>(64, std::min<uint32_t>(kBlock, 1u << q.b1));
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colsum, dim3(nchunks), dim3(threads), 0, c->ncounts, q.ntiles1,
+                         (int)q.b1, chunk, c->npartial));
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colscan_top, dim3(1), dim3(kTopThreads), 0, c->npartial, nchunks,
+                         (int)q.b1, off, tiles, q.tile2 ? q.tile2 : q.tile));
+        GESMC_TRY(launch(c, s, KID_SCAN, 0, k_colapply, dim3(nchunks), dim3(threads), 0, c->ncounts, q.ntiles1,
+                         (int)q.b1, chunk, c->npartial, off));
+    }
+    const size_t lds = scatter_lds_bytes(q.b1, kTile, kSrc == kSrcBatch, true, sa.dig_in_key == 0);
+    auto *kern = sa.self_off ? k_decide_scatter<kSrc, kTile, kThreads, true> : k_decide_scatter<kSrc, kTile, kThreads, false>;
+    return launch(c, s, KID_DECIDE_CHAIN1, q.ell, kern, dim3(q.ntiles1), dim3(kThreads), lds, si, sk, q.m, c->info, c->st, c->wn, c->idx[0], c->key[0], c->pos, c->ulist[0],
+                  &c->ucount[0], slots, c->ctr_step, cls, t, k0, k1, 64 - (int)q.b1, (int)q.b1,
+                  (const uint32_t *)c->ncounts, c->err, sa);
+}
+
+gesmc_status decide_and_scatter(gesmc_ctx *c, hipStream_t s, const Plan &q, uint32_t t, uint32_t k0, uint32_t k1,
+                                const BatchStep *bs, const uint32_t *si, const unsigned long long *sk, uint4 *slots,
+                                uint32_t cls) {
+    const bool large = q.tile == (uint32_t)kTileLarge;
+    if (bs) {
+        const SrcArgs sa{bs->gr, bs->pg, bs->bk, bs->step + 1, (int)q.bbits};
+        return large ? decide_and_scatter_t<kSrcBatch, kTileLarge>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)
+                     : decide_and_scatter_t<kSrcBatch, kTileSmall>(c, s, q, t, k0, k1, sa, si, sk, slots, cls);
+    }
+    SrcArgs sa{};
+    sa.dig_in_key = q.dig_in_key;
+    return large ? decide_and_scatter_t<kSrcPerm, kTileLarge>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)
+                 : decide_and_scatter_t<kSrcPerm, kTileSmall>(c, s, q, t, k0, k1, sa, si, sk, slots, cls);
 }
 
 // Multi-workgroup list rounds before the finisher while
@@ -987,29 +1061,58 @@ int decision_rounds(const gesmc_ctx *c, uint32_t ell) {
     return ell < kRoundsFromSwitches ? 0 : kRoundsPlain;
 }
 
+// After a plain call of r supersteps (their counters in h_ctr).
+void adapt_decision_rounds(gesmc_ctx *c, uint32_t r) {
+    uint64_t left = 0;
+    for (uint32_t q = 0; q < r; ++q) left = std::max<uint64_t>(left, c->h_ctr[q].undecided_round1);
+    c->adapt_rounds = left > kRoundsHubsAbove ? kRoundsHubs : kRoundsPlain;
+}
+
 // One superstep with the partitioned resolution (state in buffer 0).
 // vend bounds the vertex ids of the keys (a batch: bs->vend, bs->dend).
-// counts1_ready: this superstep's first radix level was counted by the
-// previous one; count_next: count superstep t + 1's in the first decision
-// round (a plan with a first radix level; a batch passes its next step's
-// plan, next_p, whose positions are a prefix of this step's).
+// level1: what the previous superstep did of this one's first radix level;
+// count_next: superstep t + 1 follows on a plan with a first level (a batch
+// passes its next step's plan, next_p, whose positions are a prefix of this
+// step's); *next_level1 then receives what was done of it.  Where the next
+// step has the same positions, the first decision round scatters the records
+// itself (k_decide_scatter): afterwards buffer 0 holds all records in that
+// level's order instead of position order.
+#ifndef GESMC_FUSE_SCATTER
+#define GESMC_FUSE_SCATTER 1
+#endif
 gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, uint32_t t, uint32_t k0, uint32_t k1,
-                                   uint32_t pl, uint32_t dup_bit, const BatchStep *bs = nullptr, uint64_t vend = 0,
-                                   uint32_t cls = 0, bool counts1_ready = false, bool count_next = false,
-                                   const Plan *next_p = nullptr) {
+                                   uint32_t pl, uint32_t dup_bit, const BatchStep *bs, uint64_t vend, uint32_t cls,
+                                   bool count_next, Level1 *level1, const Plan *next_p = nullptr) {
     int sorted = 0;
-    GESMC_TRY(permute(c, s, p, t, k0, k1, 0, &sorted, false, bs, counts1_ready));
+    GESMC_TRY(permute(c, s, p, t, k0, k1, 0, &sorted, false, bs, *level1));
+    *level1 = kLevel1Todo;
     const uint32_t *si = c->idx[sorted];
     const unsigned long long *sk = c->key[sorted];
     const uint32_t nslots = 4 * p.ell + (p.m & 1u);
-    // per-block counts of emit and the first round go to slots [0, ge) and [ge, ge + gd);
+    const Plan &q = next_p ? *next_p : p;
     // with the tuples computed from the pair records, the emit runs inside the
     // first tuple count pass (k_emit_counts), one workgroup per tile up to
     // kEmitSlotsMax
     const bool fused = c->fuse_emit && GESMC_FUSE_EMIT_COUNTS;
-    const uint32_t ge = fused ? std::min<uint32_t>(kEmitSlotsMax, make_plan(c, nslots).ntiles1)
+    const bool scatter_next = GESMC_FUSE_SCATTER && count_next && fused && sorted == 1 && q.m == p.m &&
+                              p.ell > 0 && c->persist_mult == 0 && !alloc_forbidden();
+    auto next_counts = [&](uint32_t *counts) {
+        return NextCounts{counts, t + 1, k0, k1, 64 - (int)q.b1, (int)q.b1, q.tile, q.m,
+                          bs ? bs->gr : nullptr, bs ? bs->pg : nullptr, bs ? bs->step + 1 : 0u, (int)q.bbits};
+    };
+    // per-block counts of emit and the first round go to slots [0, ge) and [ge, ge + gd)
+    const uint32_t emit_tiles = make_plan(c, nslots).ntiles1, round_tiles = q.ntiles1;
+    const uint32_t ge = fused ? std::min<uint32_t>(kEmitSlotsMax, scatter_next ? round_tiles : emit_tiles)
                               : grid_stride_blocks(c, (uint64_t)p.ell + 1);
-    const uint32_t gd = grid_stride_blocks(c, p.ell);
+    const uint32_t gd = scatter_next ? round_tiles : grid_stride_blocks(c, p.ell);
+    uint4 *slots = c->bslot;
+    if (scatter_next) {
+        GESMC_TRY(ensure_words(c, &c->ncounts, &c->cap_ncounts, radix_words(q).counts1));
+        GESMC_TRY(ensure_words(c, &c->npartial, &c->cap_npartial, radix_words(q).partial));
+        GESMC_TRY(ensure_words(c, &c->noff, &c->cap_noff, 2 * kNoffTiles));
+        GESMC_TRY(ensure_words(c, &c->fslot, &c->cap_fslot, 4ull * (ge + (uint64_t)gd)));
+        slots = reinterpret_cast<uint4 *>(c->fslot);
+    }
     SrcArgs sa{};
     sa.gr = bs ? bs->gr : nullptr;
     sa.pg = bs ? bs->pg : nullptr;
@@ -1020,10 +1123,11 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
     // directed keys (tail, head) do not fit the packed (u, v - u) coding
     if (cls & CLS_DIRECTED) vend = 0;
     if (!fused)
-        GESMC_TRY(launch(c, s, KID_EMIT, p.ell, k_emit, dim3(ge), dim3(kBlock), 0, si, sk, t, k0, k1, sa, c->info,
-                         c->st, c->idx[0], c->key[0], c->bslot, c->ucount));
+        GESMC_TRY(launch(c, s, KID_EMIT, p.ell, k_emit, dim3(ge), dim3(kBlock), 0, si, sk, t, k0, k1, sa, c->st,
+                         c->idx[0], c->key[0], slots, c->ucount));
     const EmitSource es{si, sk, t, k0, k1, sa};
-    const EmitOut eo{c->info, c->st, c->idx[0], c->key[0], c->bslot, c->ucount, ge};
+    const EmitOut eo{c->st, scatter_next ? nullptr : c->idx[0], c->key[0], slots, c->ucount, ge,
+                     scatter_next ? next_counts(c->ncounts) : NextCounts{}};
     if (!c->fuse_emit)
         GESMC_TRY(launch(c, s, KID_EMIT, nslots, k_emit_tuples, dim3(grid_stride_blocks(c, nslots)), dim3(kBlock), 0,
                          si, sk, t, k0, k1, sa, nslots, c->tu_tag[0], c->tu_key[0]));
@@ -1031,17 +1135,23 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
                                     c->fuse_emit ? &es : nullptr, bs ? bs->vend : vend, bs ? bs->dend : vend,
                                     fused ? &eo : nullptr, bs ? bs->mmax : 0));
     if (p.ell == 0) return GESMC_OK;
-    NextCounts nc{};
-    if (count_next) {
-        const Plan &q = next_p ? *next_p : p;
-        GESMC_TRY(ensure_words(c, &c->counts1, &c->cap_counts1, radix_words(q).counts1));
-        nc = NextCounts{c->counts1, t + 1, k0, k1, 64 - (int)q.b1, (int)q.b1, q.tile, q.m,
-                        bs ? bs->gr : nullptr, bs ? bs->pg : nullptr, bs ? bs->step + 1 : 0u, (int)q.bbits};
+    const uint2 *pos = nullptr;
+    if (scatter_next) {
+        GESMC_TRY(decide_and_scatter(c, s, q, t + 1, k0, k1, bs, si, sk, slots + ge, cls));
+        pos = c->pos;
+        *level1 = kLevel1Done;
+    } else {
+        NextCounts nc{};
+        if (count_next) {  // (c->counts1 may have grown for the tuples' pass above)
+            GESMC_TRY(ensure_words(c, &c->counts1, &c->cap_counts1, radix_words(q).counts1));
+            nc = next_counts(c->counts1);
+        }
+        GESMC_TRY(launch(c, s, KID_DECIDE_CHAIN1, p.ell, k_decide_chain, dim3(gd), dim3(kBlock), 0, si, sk, p.ell,
+                         c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)nullptr,
+                         (const uint32_t *)nullptr, c->ulist[0], &c->ucount[0], (uint32_t *)nullptr, slots + ge,
+                         c->ctr_step, cls, nc, c->wn, (const uint4 *)nullptr, 0u, pos));
+        if (count_next) *level1 = kLevel1Counted;
     }
-    GESMC_TRY(launch(c, s, KID_DECIDE_CHAIN1, p.ell, k_decide_chain, dim3(gd), dim3(kBlock), 0, si, sk, p.ell,
-                     c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)nullptr,
-                     (const uint32_t *)nullptr, c->ulist[0], &c->ucount[0], (uint32_t *)nullptr, c->bslot + ge,
-                     c->ctr_step, cls, nc, c->wn, (const uint4 *)nullptr, 0u));
     const uint32_t rblocks = std::max<uint32_t>(1, std::min<uint32_t>(ceil_div(p.ell, kBlock), c->num_cus * 4));
     int j = 0;
     const int fast = decision_rounds(c, p.ell);
@@ -1050,12 +1160,12 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
                          c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)c->ulist[j % 2],
                          (const uint32_t *)&c->ucount[j % 3], c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3],
                          &c->ucount[(j + 2) % 3], (uint4 *)nullptr, c->ctr_step, cls, NextCounts{},
-                         c->wn, (const uint4 *)c->bslot, j == 0 ? ge + gd : 0u));
+                         c->wn, (const uint4 *)slots, j == 0 ? ge + gd : 0u, pos));
     }
     GESMC_TRY(launch(c, s, KID_FINISH_CHAIN, 0, k_finish_chain, dim3(1), dim3(kChainFinish), 0, si, sk, p.ell,
                      c->info, c->st, c->idx[0], c->key[0], c->ulist[j % 2], &c->ucount[j % 3],
-                     c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3], (const uint4 *)c->bslot, j ? 0u : ge + gd,
-                     c->ctr_step, c->err, c->round_limit, cls, c->wn));
+                     c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3], (const uint4 *)slots, j ? 0u : ge + gd,
+                     c->ctr_step, c->err, c->round_limit, cls, c->wn, pos));
     if (bs && bs->acc)
         GESMC_TRY(launch(c, s, KID_MISC, 0, k_graph_stats, dim3(ceil_div(p.ell, kStatsChunk)), dim3(kBlock), 0,
                          (const uint8_t *)c->st, bs->gr, bs->ngraphs, p.ell, bs->acc));
@@ -1319,6 +1429,7 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
         // supersteps after the first take their first radix level's counts
         // from the previous superstep's first decision round
         const bool chain_counts = GESMC_COUNT_AHEAD && p.bbits > 0 && p.b1 > 0 && p.ell > 0;
+        Level1 level1 = kLevel1Todo;
         for (uint32_t q = 0; q < r; ++q) {
             c->ctr_step = c->ctr + q;
             const uint32_t dup = q == 0 ? ERR_DUP : ERR_INTERNAL;
@@ -1328,7 +1439,7 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
                 GESMC_TRY(superstep(c, s, p, t0 + q, k0, k1, pl, dup));
             else
                 GESMC_TRY(superstep_partitioned(c, s, p, t0 + q, k0, k1, pl, dup, nullptr, n, cls,
-                                                chain_counts && q > 0, chain_counts && q + 1 < r));
+                                                chain_counts && q + 1 < r, &level1));
         }
     }
     if (d_outcome && p.ell > 0)
@@ -1345,11 +1456,7 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
     if (c->profile) collect_profile(c);
     const gesmc_status st = map_err(*c->h_err);
     if (st != GESMC_OK) return st;
-    if (c->fast_rounds_auto && m >= 2 && r > 0) {
-        uint64_t left = 0;
-        for (uint32_t q = 0; q < r; ++q) left = std::max<uint64_t>(left, c->h_ctr[q].undecided_round1);
-        c->adapt_rounds = left > kRoundsHubsAbove ? kRoundsHubs : kRoundsPlain;
-    }
+    if (m >= 2 && r > 0) adapt_decision_rounds(c, r);
     const uint64_t att = (m >= 2) ? p.ell : 0;
     if (steps) {
         for (uint32_t q = 0; q < r; ++q) {
@@ -1983,7 +2090,7 @@ gesmc_status run_batch_impl(gesmc_ctx *c, void *stream, uint32_t G, const uint64
         };
         auto counts_ahead = [&](const Plan &q) { return GESMC_COUNT_AHEAD && q.bbits > 0 && q.b1 > 0 && q.m >= 2; };
         uint32_t qa = nactive;
-        bool ready = false;
+        Level1 level1 = kLevel1Todo;
         for (uint32_t st = 0; st < rmax; ++st) {
             qa = active(st, qa);
             const Plan p = step_plan(qa);
@@ -1993,8 +2100,7 @@ gesmc_status run_batch_impl(gesmc_ctx *c, void *stream, uint32_t G, const uint64
             BatchStep bs{c->gr, qa, st, c->pg, c->bk, stats ? c->gacc : nullptr, ge_all, vbase, nmax, mmax};
             c->ctr_step = c->ctr + st;
             GESMC_TRY(superstep_partitioned(c, s, p, 0u, 0u, 0u, pl, st == 0 ? ERR_DUP : ERR_INTERNAL, &bs, 0, 0,
-                                            ready, next, &pn));
-            ready = next;
+                                            next, &level1, &pn));
         }
         if (s1 != s) GESMC_TRY(check_hip(hipStreamWaitEvent(s, c->join_ev[0], 0), "hipStreamWaitEvent"));
         if (s2 != s) GESMC_TRY(check_hip(hipStreamWaitEvent(s, c->join_ev[1], 0), "hipStreamWaitEvent"));

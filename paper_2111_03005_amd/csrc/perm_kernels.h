@@ -188,9 +188,9 @@ struct SrcArgs {
     // most 8 digit bits; the scatter then stages each record's digit in the
     // edge key's top byte (zero in such keys) instead of a digit array
     uint32_t dig_in_key;
-    // one-level passes over few tiles: the tiles' raw counts are in `offs` and
-    // every workgroup sums its own run bases (scan_in_scatter on the host);
-    // the first tile also writes the bucket offsets here
+    // kSelf, one-level passes over few tiles (scan_in_scatter on the host): the
+    // tiles' raw counts are in `offs`, every workgroup sums its own run bases,
+    // and the first tile writes the bucket offsets here
     uint32_t *self_off;
 };
 
@@ -620,6 +620,53 @@ __global__ __launch_bounds__(kBlock) void k_segscan(uint32_t *__restrict__ count
     if (s == nseg - 1 && tid == 0) fine_off[(size_t)nseg << dbits] = coarse_off[nseg];
 }
 
+// Run bases of tile w of a one-level pass over nt tiles from the tiles' raw
+// counts, into `base` (LDS, nd words); `cnt`, `start` and `tmp` are scratch.
+// Digit d's records before this tile, and all of them, are summed over the
+// tiles, 16 rows at a time (kThreads / nd threads share a digit's rows), then
+// the digits' totals are scanned; the first tile writes the bucket offsets to
+// self_off.  Runs before the tile's records are loaded: with both live the
+// scatter takes 105 registers instead of 75, and only small passes come here.
+template <int kThreads>
+__device__ __forceinline__ void tile_bases(const uint32_t *__restrict__ counts, uint32_t *self_off, uint32_t w,
+                                           uint32_t nt, uint32_t nd, uint32_t *cnt, uint32_t *start, uint32_t *base,
+                                           uint32_t *tmp) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t share = nd < (uint32_t)kThreads ? (uint32_t)kThreads / nd : 1u;
+    const uint32_t rows = (nt + share - 1) / share;
+    for (uint32_t d = tid; d < nd; d += kThreads) {
+        cnt[d] = 0;
+        start[d] = 0;
+    }
+    lds_barrier();
+    const uint32_t part = nd < (uint32_t)kThreads ? tid / nd : 0u;
+    const uint32_t r0 = min(part * rows, nt), r1 = min(r0 + rows, nt);
+    for (uint32_t d = nd < (uint32_t)kThreads ? tid % nd : tid; d < nd; d += kThreads) {
+        uint32_t all = 0, before = 0;
+        for (uint32_t r = r0; r < r1; r += 16) {
+            uint32_t x[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) x[j] = r + j < r1 ? counts[(size_t)(r + j) * nd + d] : 0u;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                all += x[j];
+                before += r + j < w ? x[j] : 0u;
+            }
+        }
+        atomicAdd(&start[d], all);
+        atomicAdd(&cnt[d], before);
+    }
+    lds_barrier();
+    for (uint32_t d = tid; d < nd; d += kThreads) base[d] = cnt[d];
+    lds_barrier();
+    const uint32_t total = block_exclusive_scan<kThreads>(start, nd, tmp);
+    for (uint32_t d = tid; d < nd; d += kThreads) {
+        if (w == 0) self_off[d] = start[d];
+        base[d] += start[d];
+    }
+    if (w == 0 && tid == 0) self_off[nd] = total;
+}
+
 // LDS-staged scatter of one tile of a segment by digit (word >> shift) & mask.
 // Records of one digit leave the workgroup as one contiguous run starting at
 // the run base offs[w][d].  With a tuple source, slots whose key is empty
@@ -630,7 +677,7 @@ __global__ __launch_bounds__(kBlock) void k_segscan(uint32_t *__restrict__ count
 // 3 * 2^dbits + kThreads / 64 + 1 words of counters, then the staged records
 // (scatter_lds_bytes on the host).
 
-template <int kSrc, int kTile, int kThreads, bool kOne>
+template <int kSrc, int kTile, int kThreads, bool kOne, bool kSelf = false>
 __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict__ src_idx,
                                                     const unsigned long long *__restrict__ src_key,
                                                     uint32_t *__restrict__ dst_idx,
@@ -669,6 +716,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
     for (uint32_t v = blockIdx.x; v < nt; v += gridDim.x) {
         const uint32_t w = xcd_tile(v, nt);
         const TileSpan ts = tile_span<kTile, kOne>(seg_off, tile_first, nseg, n1, w);
+        if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
         uint32_t c_idx[kTileItems], c_aux[kTileItems];
         unsigned long long c_key[kTileItems];
         if (src_emits<kSrc>()) {
@@ -686,49 +734,9 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
                 c_aux[q] = (src_reads_aux<kSrc>() && in) ? ba.aux_in[ts.begin + p] : 0u;
             }
         }
-        if (kOne && ba.self_off) {
-            // digit d's records before this tile, and all of them: the tiles'
-            // counts are read 16 rows at a time (kThreads / nd threads share a
-            // digit's rows), then the digits' totals are scanned
-            const uint32_t share = nd < (uint32_t)kThreads ? (uint32_t)kThreads / nd : 1u;
-            const uint32_t rows = (nt + share - 1) / share;
-            for (uint32_t d = tid; d < nd; d += kThreads) {
-                cnt[d] = 0;
-                start[d] = 0;
-            }
-            lds_barrier();
-            const uint32_t part = nd < (uint32_t)kThreads ? tid / nd : 0u;
-            const uint32_t r0 = min(part * rows, nt), r1 = min(r0 + rows, nt);
-            for (uint32_t d = nd < (uint32_t)kThreads ? tid % nd : tid; d < nd; d += kThreads) {
-                uint32_t all = 0, before = 0;
-                for (uint32_t r = r0; r < r1; r += 16) {
-                    uint32_t x[16];
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) x[j] = r + j < r1 ? offs[(size_t)(r + j) * nd + d] : 0u;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        all += x[j];
-                        before += r + j < w ? x[j] : 0u;
-                    }
-                }
-                atomicAdd(&start[d], all);
-                atomicAdd(&cnt[d], before);
-            }
-            lds_barrier();
-            for (uint32_t d = tid; d < nd; d += kThreads) base[d] = cnt[d];
-            lds_barrier();
-            const uint32_t total = block_exclusive_scan<kThreads>(start, nd, tmp);
-            for (uint32_t d = tid; d < nd; d += kThreads) {
-                if (w == 0) ba.self_off[d] = start[d];
-                base[d] += start[d];
-                cnt[d] = 0;
-            }
-            if (w == 0 && tid == 0) ba.self_off[nd] = total;
-        } else {
-            for (uint32_t d = tid; d < nd; d += kThreads) {
-                cnt[d] = 0;
-                base[d] = offs[(size_t)w * nd + d];
-            }
+        for (uint32_t d = tid; d < nd; d += kThreads) {
+            cnt[d] = 0;
+            if (!kSelf) base[d] = offs[(size_t)w * nd + d];
         }
         if (tid == 0) s_total = 0;
         lds_barrier();

@@ -13,9 +13,11 @@
 //   eraser(X)  : the switch whose source X is (or STAYS / none)   -- lookup
 //   pred(k, X) : the next smaller inserter of X                    -- the
 //                chain behind lookup_min over non-illegal inserters.
-// Only tuples with an eraser or a predecessor write their record (rare); all
-// other records keep the "free" value written by the emit (k_emit or
-// k_emit_counts).
+// Only targets with an eraser or a predecessor have a record (rare); a bit in
+// the switch's status byte says so, and the rounds read no other record.  (With
+// a "free" record written by the emit for every target, the emit wrote and the
+// first round read 16 bytes a switch: n = 2^22, d = 32, 45.2 -> 44.0 ms per
+// call of ten supersteps without them.)
 //
 // Decision of switch k (same rule as Alg. 1): illegal if a target is erased
 // by a later switch / stays / is erased by an illegal switch, or if an
@@ -63,7 +65,7 @@ static_assert(kLdsCap < kListEnd, "k_resolve slots fit 16 bits");
 // Emit: one thread per switch (+ one for the idle record of odd m).  The
 // local outcome of every switch (switch_local) goes to its status; a switch
 // decided locally also gets its records (unchanged) and its count, an
-// undecided one its two target records initialised to "free".  Workgroup 0
+// undecided one nothing else.  Workgroup 0
 // clears the undecided-list counters of the rounds that follow.  This kernel
 // serves the unfused schedule; by default the same work runs inside the
 // first tuple count pass (k_emit_counts below), and the switches' tuples are
@@ -72,8 +74,8 @@ static_assert(kLdsCap < kListEnd, "k_resolve slots fit 16 bits");
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_emit(const uint32_t *__restrict__ s_idx,
                                                  const unsigned long long *__restrict__ s_key, uint32_t t, uint32_t k0,
-                                                 uint32_t k1, SrcArgs sa, uint2 *__restrict__ info,
-                                                 uint8_t *__restrict__ st, uint32_t *__restrict__ out_idx,
+                                                 uint32_t k1, SrcArgs sa, uint8_t *__restrict__ st,
+                                                 uint32_t *__restrict__ out_idx,
                                                  unsigned long long *__restrict__ out_key, uint4 *__restrict__ bslot,
                                                  uint32_t *__restrict__ ucount) {
     __shared__ BlockCounts bc;
@@ -96,9 +98,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint32_t *__restrict__ s_
         Targets T{0, 0, false};
         const uint8_t status = switch_local(k, ij, ee, t, k0, k1, sa, &T);
         st[k] = status;
-        if (status == ST_UNDECIDED) {
-            reinterpret_cast<uint4 *>(info)[k] = make_uint4(kNoEraser, kNoPred, kNoEraser, kNoPred);
-        } else {
+        if (status != ST_UNDECIDED) {
             reinterpret_cast<uint2 *>(out_idx)[k] = ij;
             reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
             if (status == ST_PL) atomicAdd(&bc.pl, 1u);
@@ -158,25 +158,55 @@ __global__ __launch_bounds__(kBlock) void k_decide_local(const uint32_t *__restr
     flush_counts(&bc, ctr);
 }
 
+// The next superstep's first radix level: the records' positions do not change
+// in a superstep (the sorted records of position p keep their index), so the
+// level-1 digit counts of superstep t + 1 over tiles of `tile` positions need
+// only the indices.  They are taken where the indices are read anyway: in the
+// emit (k_emit_counts) when the first round scatters the records itself
+// (k_decide_scatter), else in the first round.  A batch (gr != nullptr) counts
+// the global buckets of its next step's prefix of m positions (each
+// position's graph from pg).
+struct NextCounts {
+    uint32_t *counts;  // [tile][digit], nullptr: none
+    uint32_t t, k0, k1;
+    int shift, dbits;
+    uint32_t tile, m;
+    const BatchGraph *gr;  // batch: graph records, the graph of each position,
+    const uint32_t *pg;    // the next step and its bucket bits
+    uint32_t step;
+    int bbits;
+};
+
+__device__ __forceinline__ uint32_t next_digit(const NextCounts &nc, uint32_t i, uint32_t pos) {
+    const uint32_t dmask = (1u << nc.dbits) - 1;
+    if (!nc.gr) return (uint32_t)(perm_key(i, nc.t, nc.k0, nc.k1) >> nc.shift) & dmask;
+    const BatchGraph &g = nc.gr[nc.pg[pos]];
+    const uint64_t word = (uint64_t)batch_bucket(g, batch_perm_key(g, i, nc.step)) << (64 - nc.bbits);
+    return (uint32_t)(word >> nc.shift) & dmask;
+}
+
 // k_emit fused into the first tuple partition pass's counts (kSrcEmit or
 // kSrcEmitPacked, one segment [0, nslots) of kTile-slot tiles): the pair
 // records of a switch are read once, for its status, its records and
 // counts (as k_emit) and for its four tuples' digit counts (as
 // k_tile_counts).  Tiles are taken grid-stride; each workgroup stores its
 // outcome counts in bslot[blockIdx.x].  The per-tile digit counts equal
-// k_tile_counts' (the same tiles, tuples and radix words).
+// k_tile_counts' (the same tiles, tuples and radix words).  With nc.counts
+// also the next superstep's first-level counts; without out_idx no record is
+// written (k_decide_scatter moves them all).
 template <int kSrc, int kTile>
 __global__ __launch_bounds__(kBlock) void k_emit_counts(const uint32_t *__restrict__ s_idx,
                                                         const unsigned long long *__restrict__ s_key, uint32_t t,
                                                         uint32_t k0, uint32_t k1, int shift, int dbits, uint32_t nslots,
                                                         uint32_t *__restrict__ counts, SrcArgs sa,
-                                                        uint2 *__restrict__ info, uint8_t *__restrict__ st,
-                                                        uint32_t *__restrict__ out_idx,
+                                                        uint8_t *__restrict__ st, uint32_t *__restrict__ out_idx,
                                                         unsigned long long *__restrict__ out_key,
-                                                        uint4 *__restrict__ bslot, uint32_t *__restrict__ ucount) {
+                                                        uint4 *__restrict__ bslot, uint32_t *__restrict__ ucount,
+                                                        NextCounts nc) {
     static_assert(src_emits<kSrc>(), "tuples emitted from the pair records");
     extern __shared__ uint32_t hs[];
     __shared__ BlockCounts bc;
+    __shared__ uint32_t hn[1u << kMaxCoarseBits];
     constexpr int kSwitches = kTile / kBlock / 4;  // switches per thread and tile
     constexpr bool kPacked = src_emits_packed<kSrc>();
     const uint32_t nt = max(1u, (nslots + kTile - 1) / kTile);
@@ -184,7 +214,11 @@ __global__ __launch_bounds__(kBlock) void k_emit_counts(const uint32_t *__restri
     const uint32_t m = sa.m, ell = m >> 1;
     if (tid == 0) bc = BlockCounts{0, 0, 0, 0};
     if (blockIdx.x == 0 && tid < 3) ucount[tid] = 0;  // the undecided-list counters of the rounds
-    for (uint32_t w = blockIdx.x; w < nt; w += gridDim.x) {
+    // nc.counts: nc.tile positions (2 nc.tile slots) a trip, which are whole tiles here
+    const uint32_t per = nc.counts ? 2 * nc.tile / kTile : 1u, nnext = nc.counts ? 1u << nc.dbits : 0u;
+    for (uint32_t w0 = blockIdx.x * per; w0 < nt; w0 += gridDim.x * per) {
+        for (uint32_t d = tid; d < nnext; d += kBlock) hn[d] = 0;  // (before the tile's first barrier)
+    for (uint32_t w = w0; w < min(w0 + per, nt); ++w) {
         const uint32_t begin = w * kTile;
         const uint32_t cnt = begin < nslots ? min((uint32_t)kTile, nslots - begin) : 0u;
         for (uint32_t d = tid; d < nd; d += kBlock) hs[d] = 0;
@@ -201,19 +235,26 @@ __global__ __launch_bounds__(kBlock) void k_emit_counts(const uint32_t *__restri
                     Targets T{0, 0, false};
                     const uint8_t status = switch_local(k, ij, ee, t, k0, k1, sa, &T);
                     st[k] = status;
-                    if (status == ST_UNDECIDED) {
-                        reinterpret_cast<uint4 *>(info)[k] = make_uint4(kNoEraser, kNoPred, kNoEraser, kNoPred);
-                    } else {
-                        reinterpret_cast<uint2 *>(out_idx)[k] = ij;
-                        reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
+                    if (nnext) {
+                        atomicAdd(&hn[next_digit(nc, ij.x, 2 * k)], 1u);
+                        atomicAdd(&hn[next_digit(nc, ij.y, 2 * k)], 1u);
+                    }
+                    if (status != ST_UNDECIDED) {
+                        if (out_idx) {
+                            reinterpret_cast<uint2 *>(out_idx)[k] = ij;
+                            reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
+                        }
                         if (status == ST_PL) atomicAdd(&bc.pl, 1u);
                         if (status == ST_LOOP) atomicAdd(&bc.loop, 1u);
                         if (status == ST_EXISTS) atomicAdd(&bc.exists, 1u);
                     }
                     switch_tuples(k, ij, ee, status, T, tp);
                 } else if (k == ell && (m & 1u)) {  // the idle record of odd m stays
-                    out_idx[m - 1] = s_idx[m - 1];
-                    out_key[m - 1] = s_key[m - 1];
+                    if (out_idx) {
+                        out_idx[m - 1] = s_idx[m - 1];
+                        out_key[m - 1] = s_key[m - 1];
+                    }
+                    if (nnext) atomicAdd(&hn[next_digit(nc, s_idx[m - 1], m - 1)], 1u);
                     tp[0] = Tuple{kTagStays, s_key[m - 1]};
                 }
             }
@@ -227,6 +268,9 @@ __global__ __launch_bounds__(kBlock) void k_emit_counts(const uint32_t *__restri
         lds_barrier();
         for (uint32_t d = tid; d < nd; d += kBlock) counts[(size_t)w * nd + d] = hs[d];
         lds_barrier();
+    }
+        for (uint32_t d = tid; d < nnext; d += kBlock) nc.counts[(size_t)(w0 / per) * nnext + d] = hn[d];
+        if (nnext) lds_barrier();
     }
     store_counts(&bc, bslot + blockIdx.x);
 }
@@ -305,8 +349,8 @@ __device__ __forceinline__ void flag_duplicate(unsigned long long key, uint32_t 
 // second ERASE tuple means the edge occurs twice: dup_bit is raised (and the graph flagged in a batch).
 __device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, uint32_t first_ins, uint32_t p,
                                             uint32_t first, uint32_t prev_tag, unsigned long long key, uint32_t f,
-                                            const TuplePack &pk, uint2 *info, const Winners &wn, uint32_t *err,
-                                            uint32_t dup_bit, const GraphErr &ge) {
+                                            const TuplePack &pk, uint2 *info, uint32_t *st4, const Winners &wn,
+                                            uint32_t *err, uint32_t dup_bit, const GraphErr &ge) {
     const bool ins = (tag & kTagInsert) != 0;
     if (!ins) {
         if (p != first) flag_duplicate(key, f, pk, err, dup_bit, ge);
@@ -326,6 +370,8 @@ __device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, ui
         if (pred != kNoPred) pred += 2 * kbase;
     }
     info[slot] = make_uint2(eraser, pred);
+    // bytes of other switches share the word
+    atomicOr(st4 + (slot >> 3), (uint32_t)(kStRecord << (slot & 1u)) << (8 * ((slot >> 1) & 3u)));
     if (pred != kNoPred) {
         wn.head[slot] = head;
         wn.win[head] = kNoWinner;  // every inserter after the first writes the same value
@@ -348,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                                                     const uint32_t *__restrict__ part_off, uint32_t np, uint32_t cap,
                                                     uint2 *__restrict__ info, uint32_t *__restrict__ err,
                                                     uint32_t dup_bit, StepCounters *ctr, GraphErr ge, TuplePack pk,
-                                                    Winners wn) {
+                                                    Winners wn, uint32_t *__restrict__ st4) {
     extern __shared__ uint32_t lds[];
     constexpr uint32_t kCells = 1u << kCellBits;
     uint32_t *cell = lds;
@@ -435,7 +481,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 // a group holds one ERASE tuple at most (two are an input error)
                 const uint32_t fi = (ta & kTagInsert) ? ta : a < p ? tag_at(a + 1) : tp;
                 resolve_one(tp, ta, (fi & kTagInsert) ? fi : tp, p, a, p > 0 ? tag_at(p - 1) : 0u, kp, f, pk, info,
-                            wn, err, dup_bit, ge);
+                            st4, wn, err, dup_bit, ge);
             }
             if (tid == 0) atomicAdd(&ctr->fallback_buckets, 1ull);
             __syncthreads();
@@ -496,7 +542,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 }
                 const uint32_t fi = (at[a] & kTagInsert) ? at[a] : a < p ? at[a + 1] : at[p];
                 resolve_one(at[p], at[a], (fi & kTagInsert) ? fi : at[p], p, a, p > 0 ? at[p - 1] : 0u, kp, f, pk,
-                            info, wn, err, dup_bit, ge);
+                            info, st4, wn, err, dup_bit, ge);
             }
             if (tid == 0) atomicAdd(&ctr->fallback_buckets, 1ull);
             __syncthreads();
@@ -543,21 +589,31 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 if (p >= c) continue;
                 const unsigned long long kx = c_key[q];
                 const uint32_t tx = c_tag[q];
-                uint32_t first_tag = tx, first_ins = tx, prev_tag = 0;
+                uint32_t first_tag = tx, prev_tag = 0;
                 bool before = false;
                 for (uint32_t y = cell[r_cell[q]] & 0xFFFFu; y != kListEnd; y = nxt[y]) {
                     const unsigned long long wy = sK[y];
                     if (y == p || (kPacked ? (wy & ~code_mask) : wy) != kx) continue;
                     const uint32_t ty = kPacked ? tag_of_code((uint32_t)(wy & code_mask), pk.kb) : sT[y];
                     first_tag = min(first_tag, ty);
-                    if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     if (ty < tx || (ty == tx && y < p)) {
                         prev_tag = before ? max(prev_tag, ty) : ty;
                         before = true;
                     }
                 }
-                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, wn, err, dup_bit,
-                            ge);
+                // a target with a predecessor (rare) walks again for the key's first
+                // inserter: kept in the walk above, it cost the kernel a wave per SIMD
+                uint32_t first_ins = tx;
+                if (before && (prev_tag & kTagInsert)) {
+                    for (uint32_t y = cell[r_cell[q]] & 0xFFFFu; y != kListEnd; y = nxt[y]) {
+                        const unsigned long long wy = sK[y];
+                        if ((kPacked ? (wy & ~code_mask) : wy) != kx) continue;
+                        const uint32_t ty = kPacked ? tag_of_code((uint32_t)(wy & code_mask), pk.kb) : sT[y];
+                        if (ty & kTagInsert) first_ins = min(first_ins, ty);
+                    }
+                }
+                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, st4, wn, err,
+                            dup_bit, ge);
             }
         } else if (c > 0) {  // counting sort into cell order
             for (uint32_t q = tid; q < kCells; q += kBlock) cell[q] = 0;
@@ -614,8 +670,8 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                         before = true;
                     }
                 }
-                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, wn, err, dup_bit,
-                            ge);
+                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, st4, wn, err,
+                            dup_bit, ge);
             }
         }
         // the next partition's loads are issued before the barrier that ends
@@ -661,6 +717,7 @@ __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn
         if (!chain_end(p)) below = (p >> 1) + 1;
     }
     const uint32_t p0 = p;
+    const uint32_t first = chain_end(p) ? kNoPred : wn.head[self];  // ends the chain (it may have no record)
     int out = v;
     while (!chain_end(p)) {
         const uint32_t pk = p >> 1;
@@ -676,15 +733,14 @@ __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn
         }
         if (sp == ST_UNDECIDED) {
             // an inserter before it may have won already
-            const uint32_t h = wn.head[self];
-            out = load_status(st, h >> 1) == ST_LEGAL ||
-                          __hip_atomic_load(wn.win + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kNoWinner
+            out = load_status(st, first >> 1) == ST_LEGAL ||
+                          __hip_atomic_load(wn.win + first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kNoWinner
                       ? V_ILLEGAL
                       : V_WAIT;
             break;
         }
         below = pk;
-        const uint32_t q = info[p].y;
+        const uint32_t q = p == first ? kWalked : info[p].y;
         p = chain_end(q) ? kWalked : q;
     }
     if (p != p0) info[self].y = p;
@@ -700,6 +756,22 @@ __device__ __forceinline__ void post_winner(const Winners &wn, uint4 recs, uint3
         __hip_atomic_store(wn.win + wn.head[2 * k + 1], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The target records of a switch with undecided status byte s.
+__device__ __forceinline__ uint4 target_records(const uint2 *info, uint32_t k, uint8_t s) {
+    uint4 r = make_uint4(kNoEraser, kNoPred, kNoEraser, kNoPred);
+    if (s & kStRecord) {
+        const uint2 a = info[2 * k];
+        r.x = a.x;
+        r.y = a.y;
+    }
+    if (s & (kStRecord << 1)) {
+        const uint2 b = info[2 * k + 1];
+        r.z = b.x;
+        r.w = b.y;
+    }
+    return r;
+}
+
 // Verdict on switch k from its two target records.
 __device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 *info, const Winners &wn,
                                                   const uint8_t *st, uint2 *from = nullptr) {
@@ -709,43 +781,33 @@ __device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 
 
 // Carries out verdict v on switch k; true if it has to wait.  The pair's
 // records (ij, ee) are passed in so that callers can issue every load of the
-// switch at once.
+// switch at once.  pos (nullable): the pair's records stand at pos[k] with the
+// sources' keys (k_decide_scatter), else they go to slots 2k, 2k + 1.
 __device__ __forceinline__ bool commit_switch_chain(int v, uint32_t k, uint4 recs, uint2 ij, ulonglong2 ee,
                                                     const Winners &wn, uint8_t *st, uint32_t *out_idx,
-                                                    unsigned long long *out_key, BlockCounts *bc, uint32_t cls) {
+                                                    unsigned long long *out_key, const uint2 *pos, BlockCounts *bc,
+                                                    uint32_t cls) {
     if (v == V_WAIT) return true;
-    reinterpret_cast<uint2 *>(out_idx)[k] = ij;
+    if (!pos) reinterpret_cast<uint2 *>(out_idx)[k] = ij;
     if (v == V_OK) {
         const Targets T = switch_targets_cls(ee.x, ee.y, ij.x < ij.y, cls);
-        reinterpret_cast<ulonglong2 *>(out_key)[k] = make_ulonglong2(T.A, T.B);
+        if (pos) {
+            const uint2 g = pos[k];
+            out_key[g.x] = T.A;
+            out_key[g.y] = T.B;
+        } else {
+            reinterpret_cast<ulonglong2 *>(out_key)[k] = make_ulonglong2(T.A, T.B);
+        }
         post_winner(wn, recs, k);
         st[k] = ST_LEGAL;
         atomicAdd(&bc->legal, 1u);
     } else {
-        reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
+        if (!pos) reinterpret_cast<ulonglong2 *>(out_key)[k] = ee;
         st[k] = ST_EXISTS;
         atomicAdd(&bc->exists, 1u);
     }
     return false;
 }
-
-// The next superstep's first radix level, counted while round 1 runs: the
-// records' positions do not change in a superstep (the sorted records of
-// position p keep their index), so the level-1 digit counts of superstep
-// t + 1 over tiles of `tile` positions need only the indices, which round 1
-// reads anyway, and the Philox work hides under its memory traffic.
-// A batch (gr != nullptr) counts the global buckets of its next step's
-// prefix of m positions (each position's graph from pg).
-struct NextCounts {
-    uint32_t *counts;  // [tile][digit], nullptr: none
-    uint32_t t, k0, k1;
-    int shift, dbits;
-    uint32_t tile, m;
-    const BatchGraph *gr;  // batch: graph records, the graph of each position,
-    const uint32_t *pg;    // the next step and its bucket bits
-    uint32_t step;
-    int bbits;
-};
 
 // Undecided switches staged per workgroup of k_decide_chain: the switches of
 // one 4096-record tile.
@@ -769,13 +831,14 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
                                                          uint32_t *__restrict__ zero_count,
                                                          uint4 *__restrict__ bslot, StepCounters *ctr,
                                                          uint32_t cls, NextCounts nc, Winners wn,
-                                                         const uint4 *__restrict__ fold, uint32_t nfold) {
+                                                         const uint4 *__restrict__ fold, uint32_t nfold,
+                                                         const uint2 *__restrict__ pos) {
     __shared__ BlockCounts bc;
     __shared__ uint32_t hs[1u << kMaxCoarseBits];
-    __shared__ uint32_t s_wait[kWaitStage], s_nwait, s_wbase, s_total;
+    __shared__ uint32_t s_wait[kWaitStage], s_nwait, s_wbase;
     if (threadIdx.x == 0) {
         bc = BlockCounts{0, 0, 0, 0};
-        s_nwait = s_total = 0;
+        s_nwait = 0;
     }
     __syncthreads();
     // Undecided switches are staged in LDS and leave with one device atomic
@@ -797,10 +860,7 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
         const uint32_t c = s_nwait;
         __syncthreads();  // read by every wave before the next trip may stage again
         if (c == 0) return;
-        if (threadIdx.x == 0) {
-            s_wbase = atomicAdd(next_count, c);
-            s_total += c;
-        }
+        if (threadIdx.x == 0) s_wbase = atomicAdd(next_count, c);
         __syncthreads();
         for (uint32_t q = threadIdx.x; q < c; q += kBlock) next_list[s_wbase + q] = s_wait[q];
         if (threadIdx.x == 0) s_nwait = 0;
@@ -810,13 +870,13 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
     if (zero_count && blockIdx.x == 0 && threadIdx.x == 0) *zero_count = 0;
     auto decide_one = [&](uint32_t k, bool *wait, uint2 *ij_out) {
         const uint8_t sk = st[k];
-        const uint4 recs = reinterpret_cast<const uint4 *>(info)[k];
         const uint2 ij = reinterpret_cast<const uint2 *>(s_idx)[k];
         const ulonglong2 ee = reinterpret_cast<const ulonglong2 *>(s_key)[k];
         *ij_out = ij;
-        if (sk == ST_UNDECIDED)
-            *wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, st), k, recs, ij, ee, wn, st, out_idx,
-                                        out_key, &bc, cls);
+        if ((sk & kStOutcome) != ST_UNDECIDED) return;
+        const uint4 recs = target_records(info, k, sk);
+        *wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, st), k, recs, ij, ee, wn, st, out_idx, out_key,
+                                    pos, &bc, cls);
     };
     const uint32_t n = list ? min(*count, ell) : ell;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nfold; q += gridDim.x * kBlock) {
@@ -827,17 +887,12 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
         if (v.w) atomicAdd(&bc.pl, v.w);
     }
     if (nc.counts) {
-        const uint32_t nd = 1u << nc.dbits, dmask = nd - 1, half = nc.tile / 2;
+        const uint32_t nd = 1u << nc.dbits, half = nc.tile / 2;
         // tiles of the next step's positions (a batch's prefix may shrink: the
         // tiles then also cover this step's remaining switches, uncounted)
         const uint32_t ncount = (nc.m + nc.tile - 1) / nc.tile;
         const uint32_t ntiles = max(ncount, (ell + half - 1) / half);
-        auto digit = [&](uint32_t i, uint32_t pos) -> uint32_t {
-            if (!nc.gr) return (uint32_t)(perm_key(i, nc.t, nc.k0, nc.k1) >> nc.shift) & dmask;
-            const BatchGraph &g = nc.gr[nc.pg[pos]];
-            const uint64_t word = (uint64_t)batch_bucket(g, batch_perm_key(g, i, nc.step)) << (64 - nc.bbits);
-            return (uint32_t)(word >> nc.shift) & dmask;
-        };
+        auto digit = [&](uint32_t i, uint32_t pos) { return next_digit(nc, i, pos); };
         for (uint32_t w = blockIdx.x; w < ntiles; w += gridDim.x) {
             for (uint32_t d = threadIdx.x; d < nd; d += kBlock) hs[d] = 0;
             __syncthreads();
@@ -877,12 +932,168 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
             if ((r + 1) % (kWaitStage / kBlock) == 0 || r + 1 == trips) flush_undecided();
         }
     }
-    if (!list && threadIdx.x == 0 && s_total) atomicAdd(&ctr->undecided_round1, (unsigned long long)s_total);
+    // the list of round 1 is counted by whoever reads it first (and sums its counts)
+    if (nfold && blockIdx.x == 0 && threadIdx.x == 0) ctr->undecided_round1 = n;
     if (bslot)
         store_counts(&bc, bslot + blockIdx.x);
     else
         flush_counts(&bc, ctr);
     if (blockIdx.x == 0 && threadIdx.x == 0 && n > 0) atomicAdd(&ctr->rounds, 1ull);
+}
+
+// Round 1 and the next superstep's first radix scatter in one pass over the
+// pair records: a tile's switches are judged as by k_decide_chain, and its
+// records -- accepted switches with their targets, all others as they are --
+// leave through the LDS stage of k_scatter in the order of the next
+// permutation's first level (run bases in offs, counted by k_emit_counts).
+// A switch that waits leaves its sources there and its two places in pos; the
+// later rounds write its targets over them.  The two passes apart wrote the
+// records and read them back, 48 of 114 bytes a switch; both are bound by
+// memory: n = 2^22, d = 32, 467 + 382 us a superstep apart, 370 together (5.3
+// TB/s in loads and stores; the emit takes 90 us more for the counts).
+// One workgroup per tile; its counts go to bslot[blockIdx.x].
+template <int kSrc, int kTile, int kThreads, bool kSelf>
+__global__ __launch_bounds__(kThreads) void k_decide_scatter(
+    const uint32_t *__restrict__ s_idx, const unsigned long long *__restrict__ s_key, uint32_t m, uint2 *info,
+    uint8_t *st, Winners wn, uint32_t *__restrict__ dst_idx, unsigned long long *__restrict__ dst_key,
+    uint2 *__restrict__ pos, uint32_t *__restrict__ next_list, uint32_t *__restrict__ next_count,
+    uint4 *__restrict__ bslot, StepCounters *ctr, uint32_t cls, uint32_t t, uint32_t k0, uint32_t k1, int shift,
+    int dbits, const uint32_t *__restrict__ offs, uint32_t *__restrict__ err, SrcArgs ba) {
+    static_assert(kSrc == kSrcPerm || kSrc == kSrcBatch, "edge records");
+    extern __shared__ uint32_t lds[];
+    __shared__ uint32_t s_nwait, s_wbase, s_legal, s_exists;
+    constexpr int kPairs = kTile / kThreads / 2;
+    constexpr uint32_t kScanWords = kThreads / 64 + 1;
+    const bool dik = kSrc == kSrcPerm && ba.dig_in_key != 0;
+    constexpr unsigned long long kKeyLow56 = 0x00FFFFFFFFFFFFFFull;
+    const uint32_t nd = 1u << dbits, dmask = nd - 1;
+    uint32_t *cnt = lds, *start = cnt + nd, *base = start + nd, *tmp = base + nd;
+    uint32_t *l_idx = tmp + kScanWords;
+    unsigned long long *l_key =
+        reinterpret_cast<unsigned long long *>(l_idx + kTile + ((kScanWords + 3 * nd + kTile) & 1));
+    uint16_t *l_dig = reinterpret_cast<uint16_t *>(l_key + kTile);
+    uint32_t *l_bkt = reinterpret_cast<uint32_t *>(l_dig + kTile);  // kSrcBatch only
+    const uint32_t nt = (m + kTile - 1) / kTile, w = xcd_tile(blockIdx.x, nt), tid = threadIdx.x, ell = m >> 1;
+    const uint32_t begin = w * kTile, staged = min((uint32_t)kTile, m - begin);
+    if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
+    // a thread's pairs: k = begin / 2 + tid + j kThreads (the idle record of odd m is half a pair)
+    uint2 ij[kPairs];
+    ulonglong2 ee[kPairs];
+    uint8_t sk[kPairs];
+    uint32_t aux[kPairs];
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        const uint32_t k = (begin >> 1) + tid + j * kThreads;
+        ij[j] = make_uint2(0, 0);
+        ee[j] = make_ulonglong2(0, 0);
+        sk[j] = ST_IDLE;
+        aux[j] = 0;
+        if (k < ell) {
+            ij[j] = reinterpret_cast<const uint2 *>(s_idx)[k];
+            ee[j] = reinterpret_cast<const ulonglong2 *>(s_key)[k];
+            sk[j] = st[k];
+            if (kSrc == kSrcBatch) aux[j] = ba.aux_in[2 * k];  // both records of a pair belong to one graph
+        } else if (k == ell && (m & 1u)) {
+            ij[j].x = s_idx[m - 1];
+            ee[j].x = s_key[m - 1];
+            if (kSrc == kSrcBatch) aux[j] = ba.aux_in[m - 1];
+        }
+    }
+    if (tid == 0) s_nwait = s_legal = s_exists = 0;
+    for (uint32_t d = tid; d < nd; d += kThreads) {
+        cnt[d] = 0;
+        if (!kSelf) base[d] = offs[(size_t)w * nd + d];
+    }
+    lds_barrier();
+    uint32_t legal = 0, exists = 0, slot[kPairs];
+    uint32_t waits = 0;
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        const uint32_t k = (begin >> 1) + tid + j * kThreads;
+        slot[j] = 0;
+        if (k >= ell || (sk[j] & kStOutcome) != ST_UNDECIDED) continue;
+        const uint4 recs = target_records(info, k, sk[j]);
+        const int v = judge_switch_chain(k, recs, info, wn, st);
+        if (v == V_WAIT) {
+            waits |= 1u << j;
+            slot[j] = atomicAdd(&s_nwait, 1u);
+        } else if (v == V_OK) {
+            const Targets T = switch_targets_cls(ee[j].x, ee[j].y, ij[j].x < ij[j].y, cls);
+            ee[j] = make_ulonglong2(T.A, T.B);
+            post_winner(wn, recs, k);
+            st[k] = ST_LEGAL;
+            ++legal;
+        } else {
+            st[k] = ST_EXISTS;
+            ++exists;
+        }
+    }
+    if (legal) atomicAdd(&s_legal, legal);
+    if (exists) atomicAdd(&s_exists, exists);
+    // (from here on as k_scatter)
+    uint32_t r_dig[2 * kPairs], r_rank[2 * kPairs], r_bkt[2 * kPairs];
+#pragma unroll
+    for (int q = 0; q < 2 * kPairs; ++q) {
+        const uint32_t p = begin + 2 * (tid + (q >> 1) * kThreads) + (q & 1);
+        r_dig[q] = 0xFFFFFFFFu;
+        r_bkt[q] = 0;
+        if (p < m) {
+            const uint32_t i = (q & 1) ? ij[q >> 1].y : ij[q >> 1].x;
+            const uint64_t word = radix_word<kSrc>(i, 0ull, aux[q >> 1], t, k0, k1, ba, &r_bkt[q]);
+            r_dig[q] = (uint32_t)(word >> shift) & dmask;
+            r_rank[q] = atomicAdd(&cnt[r_dig[q]], 1u);
+        }
+    }
+    lds_barrier();
+    for (uint32_t d = tid; d < nd; d += kThreads) start[d] = cnt[d];
+    if (tid == 0) {
+        if (s_nwait) s_wbase = atomicAdd(next_count, s_nwait);
+        bslot[blockIdx.x] = make_uint4(s_legal, 0u, s_exists, 0u);
+        if (blockIdx.x == 0) atomicAdd(&ctr->rounds, 1ull);
+    }
+    lds_barrier();
+    block_exclusive_scan<kThreads>(start, nd, tmp);
+#pragma unroll
+    for (int q = 0; q < 2 * kPairs; ++q) {
+        if (r_dig[q] == 0xFFFFFFFFu) continue;
+        const uint32_t lp = start[r_dig[q]] + r_rank[q];
+        const unsigned long long key = (q & 1) ? ee[q >> 1].y : ee[q >> 1].x;
+        l_idx[lp] = (q & 1) ? ij[q >> 1].y : ij[q >> 1].x;
+        if (dik) {
+            l_key[lp] = (key & kKeyLow56) | ((unsigned long long)r_dig[q] << 56);
+        } else {
+            l_key[lp] = key;
+            l_dig[lp] = (uint16_t)r_dig[q];
+        }
+        if (kSrc == kSrcBatch) l_bkt[lp] = r_bkt[q];
+    }
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        if (!(waits & (1u << j))) continue;
+        const uint32_t k = (begin >> 1) + tid + j * kThreads;
+        const uint2 g = make_uint2(base[r_dig[2 * j]] + r_rank[2 * j], base[r_dig[2 * j + 1]] + r_rank[2 * j + 1]);
+        if (g.x < m && g.y < m) {
+            pos[k] = g;
+            next_list[s_wbase + slot[j]] = k;
+        } else {  // never for consistent counts
+            pos[k] = make_uint2(0, 0);
+            next_list[s_wbase + slot[j]] = k;
+            atomicOr(err, ERR_INTERNAL);
+        }
+    }
+    lds_barrier();
+    for (uint32_t lp = tid; lp < staged; lp += kThreads) {
+        const unsigned long long word = l_key[lp];
+        const uint32_t d = dik ? (uint32_t)(word >> 56) : (uint32_t)l_dig[lp];
+        const uint32_t g = base[d] + (lp - start[d]);
+        if (g < m) {
+            dst_idx[g] = l_idx[lp];
+            dst_key[g] = dik ? word & kKeyLow56 : word;
+            if (kSrc == kSrcBatch) ba.aux_out[g] = l_bkt[lp];
+        } else {
+            atomicOr(err, ERR_INTERNAL);
+        }
+    }
 }
 
 // Remaining rounds in one workgroup; the next round's list counter is cleared
@@ -909,13 +1120,15 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                                                                uint32_t *count_b, const uint4 *__restrict__ bslot,
                                                                uint32_t nbslot, StepCounters *ctr,
                                                                uint32_t *__restrict__ err, uint32_t round_limit,
-                                                               uint32_t cls, Winners wn) {
+                                                               uint32_t cls, Winners wn,
+                                                               const uint2 *__restrict__ pos) {
     __shared__ BlockCounts bc;
     __shared__ uint32_t s_n;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) {
         bc = BlockCounts{0, 0, 0, 0};
         s_n = min(*count_a, ell);
+        if (nbslot) ctr->undecided_round1 = s_n;
         // a caller's round budget (0: none), counted over the superstep's rounds so
         // far (the multi-workgroup rounds before this kernel included)
         const unsigned long long so_far = round_limit ? atomicAdd(&ctr->rounds, 0ull) : 0ull;
@@ -963,9 +1176,10 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
             int v = V_WAIT;
             if (q < n) {
                 k = cur[q];
-                todo = k < ell && st[k] == ST_UNDECIDED;
+                const uint8_t sk = k < ell ? st[k] : (uint8_t)ST_LEGAL;
+                todo = (sk & kStOutcome) == ST_UNDECIDED;
                 if (todo) {
-                    recs = reinterpret_cast<const uint4 *>(info)[k];
+                    recs = target_records(info, k, sk);
                     v = judge_switch_chain(k, recs, info, wn, st);
                 }
             }
@@ -975,7 +1189,7 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
             if (todo)
                 wait = commit_switch_chain(v, k, recs, reinterpret_cast<const uint2 *>(s_idx)[k],
                                            reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx, out_key,
-                                           &bc, cls);
+                                           pos, &bc, cls);
             __syncthreads();
             append_undecided(wait, k, nxt, cnxt);
         }
@@ -1038,11 +1252,11 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                     for (uint32_t j = 0; j < kPer; ++j) {
                         const uint32_t k = kb + tid + j * kChainFinish;
                         if (k >= ke || load_status(st, k) != ST_UNDECIDED) continue;
-                        const uint4 recs = reinterpret_cast<const uint4 *>(info)[k];
+                        const uint4 recs = target_records(info, k, st[k]);
                         if (commit_switch_chain(judge_switch_chain(k, recs, info, wn, st, &from[j]), k, recs,
                                                 reinterpret_cast<const uint2 *>(s_idx)[k],
                                                 reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx,
-                                                out_key, &bc, cls))
+                                                out_key, pos, &bc, cls))
                             ++waits;
                         else
                             ++dones;

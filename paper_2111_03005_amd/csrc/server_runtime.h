@@ -389,10 +389,12 @@ gesmc_status serve_enqueue(gesmc_server *S, ServeFlight &F, const std::vector<Se
     }
     GESMC_TRY(up_end(c, s));
     const Plan p = batch_plan(c, npos, bbase);
+    const bool ahead = GESMC_COUNT_AHEAD && p.bbits > 0 && p.b1 > 0 && p.m >= 2;
+    Level1 level1 = kLevel1Todo;
     for (uint32_t st = 0; st < k; ++st) {
         BatchStep bs{c->gr, G, st, c->pg, c->bk, c->gacc, GraphErr{c->gr, G, c->gerr}, vbase, nmax, mmax};
         c->ctr_step = c->ctr + st;
-        GESMC_TRY(superstep_partitioned(c, s, p, 0u, 0u, 0u, pl_any, 0u, &bs));
+        GESMC_TRY(superstep_partitioned(c, s, p, 0u, 0u, 0u, pl_any, 0u, &bs, 0, 0, ahead && st + 1 < k, &level1));
     }
     F.tuple_bytes = c->tuple_bytes;
     // results of the graphs finishing now (discarded on the host if flagged),

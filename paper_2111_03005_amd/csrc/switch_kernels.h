@@ -161,8 +161,11 @@ __global__ __launch_bounds__(kBlock) void k_build(const uint32_t *__restrict__ s
 // ---------------------------------------------------------------------------
 enum Verdict : int { V_OK = 0, V_WAIT = 1, V_ILLEGAL = 2 };
 
+// An undecided status byte of the sorted-tuples strategy also says which of the
+// switch's two targets has a record (kStRecord << h, set by k_resolve).
+constexpr uint8_t kStRecord = 0x40, kStOutcome = 0x3F;
 __device__ __forceinline__ uint8_t load_status(const uint8_t *st, uint32_t k) {
-    return __hip_atomic_load(st + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(st + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStOutcome;
 }
 
 __device__ __forceinline__ int judge_target(const Slot *tab, uint32_t s, uint32_t k, const uint8_t *st,
