@@ -30,38 +30,72 @@ __device__ __forceinline__ bool mix_bit(const uint32_t *bits, uint32_t pid) {
     return (bits[pid >> 5] >> (pid & 31u)) & 1u;
 }
 
-// Sets (set = true) or clears the bits of the m edges of E.
+// Sets the bits of the m edges of E.
 __global__ __launch_bounds__(kBlock) void k_mix_bits(const unsigned long long *__restrict__ E, uint32_t m,
-                                                     uint32_t n, uint32_t *__restrict__ bits, bool set) {
+                                                     uint32_t n, uint32_t *__restrict__ bits) {
     const uint32_t stride = gridDim.x * kBlock;
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < m; i += stride) {
         const uint32_t pid = mix_pid(E[i], n);
-        if (set)
-            atomicOr(&bits[pid >> 5], 1u << (pid & 31u));
-        else
-            atomicAnd(&bits[pid >> 5], ~(1u << (pid & 31u)));
+        atomicOr(&bits[pid >> 5], 1u << (pid & 31u));
     }
 }
 
-// One sample of a thinned series (not the first): each edge present now
-// counts a 1 -> 1 or 0 -> 1 transition and joins the tracked set; each edge
-// of the previous sample that is gone counts 1 -> 0.  The graph is simple,
-// so every pair has one writer per counter.
-__global__ __launch_bounds__(kBlock) void k_mix_count(const unsigned long long *__restrict__ E,
-                                                      const unsigned long long *__restrict__ prev, uint32_t m,
-                                                      uint32_t n, const uint32_t *__restrict__ cur_bits,
-                                                      const uint32_t *__restrict__ prev_bits,
-                                                      MixCount *__restrict__ cnt, uint32_t *__restrict__ ever) {
+// The thinned series a sample belongs to (blockIdx.y: one each).
+constexpr uint32_t kMixMaxThin = 16;
+struct MixSeries {
+    unsigned long long *prev[kMixMaxThin];  // the series' last sample, in any order
+    uint32_t *prev_bits[kMixMaxThin];       // its bitmap
+    uint32_t *ever[kMixMaxThin];            // pairs of any sample
+    MixCount *cnt[kMixMaxThin];
+};
+
+// Bitmap of the current sample: sets the bits of E, and clears the other
+// bitmap of the sample before (its edges `last`; nullptr: none).
+__global__ __launch_bounds__(kBlock) void k_mix_mark(const unsigned long long *__restrict__ E,
+                                                     const unsigned long long *__restrict__ last, uint32_t m,
+                                                     uint32_t n, uint32_t *__restrict__ bits,
+                                                     uint32_t *__restrict__ old_bits) {
     const uint32_t stride = gridDim.x * kBlock;
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < m; i += stride) {
         const uint32_t pid = mix_pid(E[i], n);
-        if (mix_bit(prev_bits, pid))
+        atomicOr(&bits[pid >> 5], 1u << (pid & 31u));
+        if (last) {
+            const uint32_t pq = mix_pid(last[i], n);
+            old_bits[pq >> 5] = 0;  // every bit of the word goes
+        }
+    }
+}
+
+// One sample of each due series (not its first): an edge present now counts
+// a 1 -> 1 or 0 -> 1 transition and joins the tracked set; an edge of the
+// previous sample that is gone counts 1 -> 0.  The graph is simple, so every
+// pair has one writer per counter.  The sample then becomes the series' last
+// one in the same pass: only bits of pairs absent now are cleared and only
+// bits of pairs present now are set, and each thread moves its own list entry
+// (three launches and a copy per due series before, two launches in all now).
+__global__ __launch_bounds__(kBlock) void k_mix_sample(const unsigned long long *__restrict__ E, uint32_t m,
+                                                       uint32_t n, const uint32_t *__restrict__ cur_bits,
+                                                       MixSeries due) {
+    const uint32_t q = blockIdx.y, stride = gridDim.x * kBlock;
+    unsigned long long *prev = due.prev[q];
+    uint32_t *prev_bits = due.prev_bits[q], *ever = due.ever[q];
+    MixCount *cnt = due.cnt[q];
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < m; i += stride) {
+        const unsigned long long e = E[i], o = prev[i];
+        const uint32_t pid = mix_pid(e, n), bit = 1u << (pid & 31u);
+        if (mix_bit(prev_bits, pid)) {
             cnt[pid].n11 += 1;
-        else
+        } else {
             cnt[pid].n01 += 1;
-        atomicOr(&ever[pid >> 5], 1u << (pid & 31u));
-        const uint32_t pq = mix_pid(prev[i], n);
-        if (!mix_bit(cur_bits, pq)) cnt[pq].n10 += 1;
+            atomicOr(&prev_bits[pid >> 5], bit);
+            atomicOr(&ever[pid >> 5], bit);
+        }
+        const uint32_t pq = mix_pid(o, n);
+        if (!mix_bit(cur_bits, pq)) {
+            cnt[pq].n10 += 1;
+            atomicAnd(&prev_bits[pq >> 5], ~(1u << (pq & 31u)));
+        }
+        prev[i] = e;
     }
 }
 

@@ -5,7 +5,53 @@
 namespace {
 
 constexpr uint32_t kMixMaxN = 1u << 14;  // pair ids below 2^27
-constexpr uint32_t kMixMaxThin = 16;
+
+// The G-ES-MC chain of a diagnostic on the multi-kernel supersteps: the state
+// stays in its records (buffer 0) between supersteps, whose order no sample
+// depends on, and the host waits once per kMixPiece supersteps instead of
+// loading, writing back and waiting for each (n = 2^13, m = 1.1e4, per
+// superstep with its samples: 232 -> 200 us).
+constexpr uint32_t kMixPiece = 64;
+
+struct MixChain {
+    Plan p;
+    uint32_t m, n, k0, k1, pl, K, piece0;
+    bool ahead;
+    Level1 level1;
+};
+
+gesmc_status mix_chain_open(gesmc_ctx *c, hipStream_t s, MixChain *q, const unsigned long long *E) {
+    GESMC_TRY(ensure_capacity(c, q->m, true));
+    GESMC_TRY(ensure_counters(c, kMixPiece));
+    q->p = make_plan(c, q->m);
+    q->p.dig_in_key = digit_in_key(q->p, q->n);
+    q->ahead = GESMC_COUNT_AHEAD && q->p.bbits > 0 && q->p.b1 > 0 && q->p.ell > 0;
+    q->piece0 = 0;
+    GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(4), dim3(256), 0, c->err, (uint64_t)64));
+    return launch(c, s, KID_LOAD, q->m, k_load, dim3(grid_stride_blocks(c, q->m)), dim3(kBlock), 0, E, q->m, q->n,
+                  c->idx[0], c->key[0], c->err, 0u);
+}
+
+// Superstep t (in order from 0); after a piece's last one, waits and checks.
+gesmc_status mix_chain_step(gesmc_ctx *c, hipStream_t s, MixChain *q, uint32_t t) {
+    const uint32_t k = t - q->piece0;
+    if (k == 0)
+        GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(4), dim3(256), 0, (uint32_t *)c->ctr,
+                         (uint64_t)kMixPiece * (sizeof(StepCounters) / 4)));
+    c->ctr_step = c->ctr + k;
+    GESMC_TRY(superstep_partitioned(c, s, q->p, t, q->k0, q->k1, q->pl, t == 0 ? ERR_DUP : ERR_INTERNAL, nullptr,
+                                    q->n, 0, q->ahead && t + 1 < q->K, &q->level1));
+    if (k + 1 < kMixPiece && t + 1 < q->K) return GESMC_OK;
+    GESMC_TRY(check_hip(hipMemcpyAsync(c->h_err, c->err, 4, hipMemcpyDeviceToHost, s), "hipMemcpyAsync"));
+    GESMC_TRY(check_hip(hipMemcpyAsync(c->h_ctr, c->ctr, sizeof(StepCounters) * (k + 1), hipMemcpyDeviceToHost, s),
+                        "hipMemcpyAsync"));
+    GESMC_TRY(check_hip(hipStreamSynchronize(s), "hipStreamSynchronize"));
+    if (c->profile) collect_profile(c);
+    GESMC_TRY(map_err(*c->h_err));
+    adapt_decision_rounds(c, k + 1);
+    q->piece0 = t + 1;
+    return GESMC_OK;
+}
 
 gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t m64, uint32_t n, uint64_t seed,
                          uint32_t chain, uint32_t pl, uint32_t K, const uint32_t *thin, uint32_t nthin,
@@ -39,7 +85,7 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     // the previous sample's list and bitmap, the tracked bitmap and the counters
     const uint64_t mm = std::max<uint32_t>(m, 1);
     const uint64_t per_q = mm * 8 + words * 8 + npairs * sizeof(MixCount) + 256 * 3;
-    const uint64_t bytes = mm * 8 + words * 4 + 64 + nthin * per_q + 256;
+    const uint64_t bytes = mm * 8 + 2 * (words * 4 + 256) + 64 + nthin * per_q + 256;
     unsigned char *blk = nullptr;
     GESMC_TRY(dev_alloc(c, (void **)&blk, bytes));
     struct Free {
@@ -57,7 +103,7 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
         return p;
     };
     auto *E = (unsigned long long *)take(mm * 8);
-    auto *cur_bits = (uint32_t *)take(words * 4);
+    uint32_t *cur_bits[2] = {(uint32_t *)take(words * 4), (uint32_t *)take(words * 4)};
     auto *res = (unsigned long long *)take(64);
     std::vector<unsigned long long *> prev(nthin);
     std::vector<uint32_t *> prev_bits(nthin), ever(nthin);
@@ -74,14 +120,23 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     const uint32_t gb = grid_stride_blocks(c, m);
     for (uint32_t q = 0; q < nthin && m > 0; ++q) {
         GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E, m, n,
-                         prev_bits[q], true));
+                         prev_bits[q]));
         GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E, m, n,
-                         ever[q], true));
+                         ever[q]));
         GESMC_TRY(check_hip(hipMemcpyAsync(prev[q], E, m * 8ull, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync"));
     }
     auto t_start = std::chrono::steady_clock::now();
+    // small graphs run a superstep in one workgroup's LDS (run_impl)
+    const bool resident = chain == 0 && c->strategy == 0 && m >= 2 &&
+                          !(c->small_graphs && (m <= kMidMax || (m <= kCmpMax && n <= kCmpMaxN)));
+    MixChain mc{Plan{}, m, n, (uint32_t)seed, (uint32_t)(seed >> 32), pl, K, 0, false, kLevel1Todo};
+    if (resident && K > 0) GESMC_TRY(mix_chain_open(c, s, &mc, (const unsigned long long *)E));
+    const unsigned long long *last = nullptr;  // a series' list of the sample before
+    uint32_t nsample = 0;
     for (uint32_t t = 0; t < K; ++t) {
-        if (m >= 2) {
+        if (resident) {
+            GESMC_TRY(mix_chain_step(c, s, &mc, t));
+        } else if (m >= 2) {
             if (chain == 0)
                 GESMC_TRY(run_impl(c, stream, (const uint64_t *)E, (uint64_t *)E, m, n, seed, t, 1, pl, nullptr,
                                    nullptr, nullptr));
@@ -90,24 +145,25 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
                                       ell, nullptr, nullptr));
         }
         const uint32_t tt = t + 1;
-        bool any = false;
-        for (uint32_t q = 0; q < nthin; ++q) any |= tt % thin[q] == 0;
-        if (!any || m == 0) continue;
-        GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E, m, n,
-                         cur_bits, true));
+        MixSeries due;
+        uint32_t ndue = 0;
         for (uint32_t q = 0; q < nthin; ++q) {
             if (tt % thin[q]) continue;
-            GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_count, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E,
-                             (const unsigned long long *)prev[q], m, n, (const uint32_t *)cur_bits,
-                             (const uint32_t *)prev_bits[q], cnt[q], ever[q]));
-            GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0,
-                             (const unsigned long long *)prev[q], m, n, prev_bits[q], false));
-            GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E,
-                             m, n, prev_bits[q], true));
-            GESMC_TRY(check_hip(hipMemcpyAsync(prev[q], E, m * 8ull, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync"));
+            due.prev[ndue] = prev[q];
+            due.prev_bits[ndue] = prev_bits[q];
+            due.ever[ndue] = ever[q];
+            due.cnt[ndue] = cnt[q];
+            ++ndue;
         }
-        GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_bits, dim3(gb), dim3(kBlock), 0, (const unsigned long long *)E, m, n,
-                         cur_bits, false));
+        if (ndue == 0 || m == 0) continue;
+        const unsigned long long *now = resident ? (const unsigned long long *)c->key[0] : E;
+        uint32_t *bits = cur_bits[nsample & 1u];
+        GESMC_TRY(launch(c, s, KID_MIX, m, k_mix_mark, dim3(gb), dim3(kBlock), 0, now, last, m, n, bits,
+                         cur_bits[1u - (nsample & 1u)]));
+        GESMC_TRY(launch(c, s, KID_MIX, (uint64_t)m * ndue, k_mix_sample, dim3(gb, ndue), dim3(kBlock), 0, now, m, n,
+                         (const uint32_t *)bits, due));
+        last = due.prev[0];  // holds this sample until its series is due again
+        ++nsample;
     }
     for (uint32_t q = 0; q < nthin; ++q) {
         const uint32_t N = K / thin[q];
