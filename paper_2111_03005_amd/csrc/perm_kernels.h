@@ -625,8 +625,8 @@ __global__ __launch_bounds__(kBlock) void k_segscan(uint32_t *__restrict__ count
 // Digit d's records before this tile, and all of them, are summed over the
 // tiles, 16 rows at a time (kThreads / nd threads share a digit's rows), then
 // the digits' totals are scanned; the first tile writes the bucket offsets to
-// self_off.  Runs before the tile's records are loaded: with both live the
-// scatter takes 105 registers instead of 75, and only small passes come here.
+// self_off.  An instance of its own: with the tile's records in flight it takes
+// 105 registers instead of 75, which only its small passes can afford.
 template <int kThreads>
 __device__ __forceinline__ void tile_bases(const uint32_t *__restrict__ counts, uint32_t *self_off, uint32_t w,
                                            uint32_t nt, uint32_t nd, uint32_t *cnt, uint32_t *start, uint32_t *base,
@@ -687,7 +687,10 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
                                                     const uint32_t *__restrict__ tile_first,
                                                     const uint32_t *__restrict__ offs, uint32_t *__restrict__ err,
                                                     SrcArgs ba) {
-    extern __shared__ uint32_t lds[];
+    // (aligned: the dynamic area starts behind the static words, and the 8-byte
+    // key stage at an odd multiple of 4 bytes made the tuple scatters a quarter
+    // slower: n = 2^22, 660 -> 513 and 623 -> 538 us)
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ uint32_t s_total;
     constexpr int kTileItems = kTile / kThreads;
     constexpr uint32_t kScanWords = kThreads / 64 + 1;
@@ -716,7 +719,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
     for (uint32_t v = blockIdx.x; v < nt; v += gridDim.x) {
         const uint32_t w = xcd_tile(v, nt);
         const TileSpan ts = tile_span<kTile, kOne>(seg_off, tile_first, nseg, n1, w);
-        if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
         uint32_t c_idx[kTileItems], c_aux[kTileItems];
         unsigned long long c_key[kTileItems];
         if (src_emits<kSrc>()) {
@@ -734,6 +736,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t *__restrict
                 c_aux[q] = (src_reads_aux<kSrc>() && in) ? ba.aux_in[ts.begin + p] : 0u;
             }
         }
+        if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
         for (uint32_t d = tid; d < nd; d += kThreads) {
             cnt[d] = 0;
             if (!kSelf) base[d] = offs[(size_t)w * nd + d];
@@ -810,7 +813,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_buckets(const uint32_t *__restr
                                                          uint32_t m, uint32_t cap, StepCounters *__restrict__ ctr,
                                                          const BatchGraph *__restrict__ gr, uint32_t ngraphs,
                                                          uint32_t step) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     constexpr uint32_t kCells = 1u << kCellBits;
     uint32_t *cell = lds;                    // kCells
     uint32_t *tmp = cell + kCells;           // kBlock + 1 (+1 pad for 8-byte alignment)

@@ -387,15 +387,18 @@ __device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, ui
 // words with the cell lists (the tags stay in the words).  kPacked: the tuples are
 // packed words (no tag array); pbits is then the second level's bits only,
 // the first level's having been dropped from the words.
+// Seven waves per SIMD (72 registers): the walks wait on LDS, and at the 74 the
+// compiler takes by itself a wave per SIMD is lost (n = 2^22: 38.2 -> 37.9 ms
+// per call of ten supersteps; at eight waves 38.6).
 template <bool kPacked>
-__global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_tag, unsigned long long *__restrict__ tu_key,
+__global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu_tag, unsigned long long *__restrict__ tu_key,
                                                     uint32_t *__restrict__ sc_tag,
                                                     unsigned long long *__restrict__ sc_key, int pbits,
                                                     const uint32_t *__restrict__ part_off, uint32_t np, uint32_t cap,
                                                     uint2 *__restrict__ info, uint32_t *__restrict__ err,
                                                     uint32_t dup_bit, StepCounters *ctr, GraphErr ge, TuplePack pk,
                                                     Winners wn, uint32_t *__restrict__ st4) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     constexpr uint32_t kCells = 1u << kCellBits;
     uint32_t *cell = lds;
     uint32_t *tmp = cell + kCells;
@@ -589,27 +592,17 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
                 if (p >= c) continue;
                 const unsigned long long kx = c_key[q];
                 const uint32_t tx = c_tag[q];
-                uint32_t first_tag = tx, prev_tag = 0;
+                uint32_t first_tag = tx, first_ins = tx, prev_tag = 0;
                 bool before = false;
                 for (uint32_t y = cell[r_cell[q]] & 0xFFFFu; y != kListEnd; y = nxt[y]) {
                     const unsigned long long wy = sK[y];
                     if (y == p || (kPacked ? (wy & ~code_mask) : wy) != kx) continue;
                     const uint32_t ty = kPacked ? tag_of_code((uint32_t)(wy & code_mask), pk.kb) : sT[y];
                     first_tag = min(first_tag, ty);
+                    if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     if (ty < tx || (ty == tx && y < p)) {
                         prev_tag = before ? max(prev_tag, ty) : ty;
                         before = true;
-                    }
-                }
-                // a target with a predecessor (rare) walks again for the key's first
-                // inserter: kept in the walk above, it cost the kernel a wave per SIMD
-                uint32_t first_ins = tx;
-                if (before && (prev_tag & kTagInsert)) {
-                    for (uint32_t y = cell[r_cell[q]] & 0xFFFFu; y != kListEnd; y = nxt[y]) {
-                        const unsigned long long wy = sK[y];
-                        if ((kPacked ? (wy & ~code_mask) : wy) != kx) continue;
-                        const uint32_t ty = kPacked ? tag_of_code((uint32_t)(wy & code_mask), pk.kb) : sT[y];
-                        if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     }
                 }
                 resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, st4, wn, err,
@@ -697,13 +690,14 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t *__restrict__ tu_ta
 // rec.y) and leaves there the predecessor it waits for: decided predecessors
 // never change, so a repeated judgement of the same switch walks each link
 // once.
+template <bool kOne>
 __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn, uint2 rec, uint32_t self, uint32_t k,
                                                   const uint8_t *st, uint32_t *from = nullptr) {
     int v = V_OK;
     const uint32_t e = rec.x;
     if (e != kNoEraser) {
         if (e == kStays || e >= k) return V_ILLEGAL;
-        const uint8_t se = load_status(st, e);
+        const uint8_t se = load_status<kOne>(st, e);
         if (se == ST_UNDECIDED)
             v = V_WAIT;
         else if (se != ST_LEGAL)
@@ -726,15 +720,17 @@ __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn
             p = kWalked;
             break;
         }
-        const uint8_t sp = load_status(st, pk);
+        const uint8_t sp = load_status<kOne>(st, pk);
         if (sp == ST_LEGAL) {
             out = V_ILLEGAL;
             break;
         }
         if (sp == ST_UNDECIDED) {
             // an inserter before it may have won already
-            out = load_status(st, first >> 1) == ST_LEGAL ||
-                          __hip_atomic_load(wn.win + first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kNoWinner
+            out = load_status<kOne>(st, first >> 1) == ST_LEGAL ||
+                          __hip_atomic_load(wn.win + first, __ATOMIC_RELAXED,
+                                            kOne ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT) !=
+                              kNoWinner
                       ? V_ILLEGAL
                       : V_WAIT;
             break;
@@ -773,10 +769,12 @@ __device__ __forceinline__ uint4 target_records(const uint2 *info, uint32_t k, u
 }
 
 // Verdict on switch k from its two target records.
+template <bool kOne = false>
 __device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 *info, const Winners &wn,
                                                   const uint8_t *st, uint2 *from = nullptr) {
-    return max(judge_target_chain(info, wn, make_uint2(recs.x, recs.y), 2 * k, k, st, from ? &from->x : nullptr),
-               judge_target_chain(info, wn, make_uint2(recs.z, recs.w), 2 * k + 1, k, st, from ? &from->y : nullptr));
+    return max(judge_target_chain<kOne>(info, wn, make_uint2(recs.x, recs.y), 2 * k, k, st, from ? &from->x : nullptr),
+               judge_target_chain<kOne>(info, wn, make_uint2(recs.z, recs.w), 2 * k + 1, k, st,
+                                        from ? &from->y : nullptr));
 }
 
 // Carries out verdict v on switch k; true if it has to wait.  The pair's
@@ -960,7 +958,7 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
     uint4 *__restrict__ bslot, StepCounters *ctr, uint32_t cls, uint32_t t, uint32_t k0, uint32_t k1, int shift,
     int dbits, const uint32_t *__restrict__ offs, uint32_t *__restrict__ err, SrcArgs ba) {
     static_assert(kSrc == kSrcPerm || kSrc == kSrcBatch, "edge records");
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ uint32_t s_nwait, s_wbase, s_legal, s_exists;
     constexpr int kPairs = kTile / kThreads / 2;
     constexpr uint32_t kScanWords = kThreads / 64 + 1;
@@ -975,7 +973,6 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
     uint32_t *l_bkt = reinterpret_cast<uint32_t *>(l_dig + kTile);  // kSrcBatch only
     const uint32_t nt = (m + kTile - 1) / kTile, w = xcd_tile(blockIdx.x, nt), tid = threadIdx.x, ell = m >> 1;
     const uint32_t begin = w * kTile, staged = min((uint32_t)kTile, m - begin);
-    if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
     // a thread's pairs: k = begin / 2 + tid + j kThreads (the idle record of odd m is half a pair)
     uint2 ij[kPairs];
     ulonglong2 ee[kPairs];
@@ -1000,6 +997,7 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
         }
     }
     if (tid == 0) s_nwait = s_legal = s_exists = 0;
+    if (kSelf) tile_bases<kThreads>(offs, ba.self_off, w, nt, nd, cnt, start, base, tmp);
     for (uint32_t d = tid; d < nd; d += kThreads) {
         cnt[d] = 0;
         if (!kSelf) base[d] = offs[(size_t)w * nd + d];
@@ -1180,7 +1178,7 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                 todo = (sk & kStOutcome) == ST_UNDECIDED;
                 if (todo) {
                     recs = target_records(info, k, sk);
-                    v = judge_switch_chain(k, recs, info, wn, st);
+                    v = judge_switch_chain<true>(k, recs, info, wn, st);
                 }
             }
             // a pass judges by what earlier passes decided, so its round count
@@ -1251,9 +1249,9 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
 #pragma unroll
                     for (uint32_t j = 0; j < kPer; ++j) {
                         const uint32_t k = kb + tid + j * kChainFinish;
-                        if (k >= ke || load_status(st, k) != ST_UNDECIDED) continue;
+                        if (k >= ke || load_status<true>(st, k) != ST_UNDECIDED) continue;
                         const uint4 recs = target_records(info, k, st[k]);
-                        if (commit_switch_chain(judge_switch_chain(k, recs, info, wn, st, &from[j]), k, recs,
+                        if (commit_switch_chain(judge_switch_chain<true>(k, recs, info, wn, st, &from[j]), k, recs,
                                                 reinterpret_cast<const uint2 *>(s_idx)[k],
                                                 reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx,
                                                 out_key, pos, &bc, cls))

@@ -164,8 +164,12 @@ enum Verdict : int { V_OK = 0, V_WAIT = 1, V_ILLEGAL = 2 };
 // An undecided status byte of the sorted-tuples strategy also says which of the
 // switch's two targets has a record (kStRecord << h, set by k_resolve).
 constexpr uint8_t kStRecord = 0x40, kStOutcome = 0x3F;
+// kOne: only the calling workgroup writes meanwhile (its CU's cache serves the load)
+template <bool kOne = false>
 __device__ __forceinline__ uint8_t load_status(const uint8_t *st, uint32_t k) {
-    return __hip_atomic_load(st + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStOutcome;
+    return __hip_atomic_load(st + k, __ATOMIC_RELAXED,
+                             kOne ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT) &
+           kStOutcome;
 }
 
 __device__ __forceinline__ int judge_target(const Slot *tab, uint32_t s, uint32_t k, const uint8_t *st,
