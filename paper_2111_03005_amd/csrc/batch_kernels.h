@@ -211,17 +211,20 @@ __global__ __launch_bounds__(kBlock) void k_extract(const uint4 *__restrict__ ch
 // ---------------------------------------------------------------------------
 // Small graphs: one workgroup runs all r global switches of one graph inside
 // LDS -- the permutation (LDS counting sort of (K_i, i) on the top bits of K,
-// then ranks within cells), the switches' ERASE / INSERT tuples grouped by
-// tuple hash, the rounds of decisions of Alg. 1 and the writes -- with the
-// same definitions as the multi-kernel path, so the result is the same chain.
-// The records stay in LDS across supersteps.  Size classes:
+// then ranks within cells), the switches' ERASE / INSERT tuples in lists per
+// cell of tuple hash bits, the rounds of decisions of Alg. 1 and the writes --
+// with the same definitions as the multi-kernel path, so the result is the same
+// chain.  The records stay in LDS across supersteps.  Size classes of batches:
 //   m <= 1024 on 256 threads (39 KB of LDS, several workgroups per CU),
 //   m <= 4096 on 1024 threads (158 KB, one per CU),
 //   m <= 6144 on 1024 threads with every vertex id below 2^16 ("compact":
-//   edge keys (min << 16) | max and 32-bit sort words, 151 KB).
-// Each thread holds kMax / kThreads permutation items and half as many
-// switches; there are eight sort cells per thread.
-// ---------------------------------------------------------------------------
+//   edge keys (min << 16) | max and 32-bit sort words, 151 KB);
+// a single graph has the chip to itself and takes more threads and compact
+// keys wherever the ids allow (run_small_impl).  Each thread holds kMax /
+// kThreads permutation items and half as many switches.  What bounds a chain is
+// the instructions of a superstep on its one CU: with the tuples grouped by a
+// counting sort (count, scan, place: each word computed twice, five barriers) a
+// superstep of 512 edges took 6.1 us and one of 5,100 14, with lists 4.6 and 12.
 constexpr uint32_t kSmallMax = 1024, kSmallThreads = 256;  // edges, threads
 constexpr uint32_t kMidMax = 4096, kMidThreads = 1024;
 constexpr uint32_t kCmpMax = 6144, kCmpThreads = 1024;     // compact keys: vertex ids < 2^16
@@ -268,12 +271,13 @@ struct SmallLds {
     using Key = typename SmallKeys<kCompact>::Key;
     using Word = typename SmallKeys<kCompact>::Word;
     Key E[kMax];                      // edge keys by local index
-    Word sK[2 * kMax];                // sorted permutation words, then sorted tuple words
+    Word sK[2 * kMax];                // sorted permutation words, then tuple words by slot
     uint32_t info[kMax];              // per target 2k+h: eraser << 16 | predecessor
     uint16_t pi[kMax];                // the permutation of this superstep
-    uint16_t sT[2 * kMax];            // sorted local index, then sorted tuple tag
+    uint16_t sT[2 * kMax];            // sorted local index, then tuple list links
     // sort cells: 16-bit counts, then offsets, eight per thread (two per
-    // word), and the total after them at entry 8 kThreads
+    // word), and the total after them at entry 8 kThreads; then tuple list
+    // heads, one per word
     alignas(16) uint32_t cellw[4 * kThreads + 4];
     uint32_t tmp[kThreads / 64 + 2];
     uint8_t st[kMax / 2];
@@ -291,6 +295,11 @@ template <uint32_t kThreads>
 constexpr int small_cell_bits() {  // 8 kThreads cells
     return kThreads == 256 ? 11 : kThreads == 512 ? 12 : 13;
 }
+template <uint32_t kThreads>
+constexpr int small_list_bits() {  // 4 kThreads tuple lists
+    return small_cell_bits<kThreads>() - 1;
+}
+constexpr uint32_t kSmEpochs = 0xFFF0;  // supersteps between clearings of the list heads
 
 // The sort cells' 16-bit counters share 32-bit words (no count reaches 2^16,
 // so a half never carries into the other).  Zeroing: four words per thread.
@@ -362,53 +371,6 @@ __device__ __forceinline__ void small_group(SmallLds<kMax, kThreads, kCompact> &
         L.sT[slot] = g[q];
     }
     __syncthreads();
-}
-
-// small_group with items produced on demand: item(q, &w, &g) returns whether
-// item q is present and sets its word and tag.  It is called twice per item
-// (count, then place) and nothing per item is kept in between; placed(q,
-// slot) is told where each present item went.  Cells as in small_group.
-template <int kPer, uint32_t kMax, uint32_t kThreads, bool kCompact, typename Item, typename Placed>
-__device__ __forceinline__ void small_group_fn(SmallLds<kMax, kThreads, kCompact> &L, Item item, Placed placed) {
-    using Word = typename SmallKeys<kCompact>::Word;
-    constexpr int kShift = 8 * (int)sizeof(Word) - small_cell_bits<kThreads>();
-    small_cells_zero<kThreads>(L.cellw);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        Word w;
-        uint16_t g;
-        if (!item(q, &w, &g)) continue;
-        small_cell_add(L.cellw, (uint32_t)(w >> kShift));
-    }
-    __syncthreads();
-    small_cells_scan<kThreads>(L.cellw, L.tmp);
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        Word w;
-        uint16_t g;
-        if (!item(q, &w, &g)) continue;
-        const uint32_t slot = small_cell_add(L.cellw, (uint32_t)(w >> kShift));
-        L.sK[slot] = w;
-        L.sT[slot] = g;
-        placed(q, slot);
-    }
-    __syncthreads();
-}
-
-// Calls fn(z) for every slot z != self of the cell [a, e) whose word equals
-// wy.  The words are loaded four at a time, so a walk has several LDS loads
-// in flight instead of one after another.
-template <typename W, typename Fn>
-__device__ __forceinline__ void cell_matches(const W *sK, uint32_t a, uint32_t e, uint32_t self, W wy, Fn fn) {
-    for (uint32_t z0 = a; z0 < e; z0 += 4) {
-        W wz[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) wz[u] = z0 + u < e ? sK[z0 + u] : wy;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (z0 + u < e && z0 + u != self && wz[u] == wy) fn(z0 + u);
-    }
 }
 
 // Alg. 1's rule for target 2k+h from its packed record (see judge_target_chain).
@@ -517,6 +479,8 @@ __global__ __launch_bounds__(kThreads) void k_small_perm(uint32_t m, uint32_t t0
 // exists, P_L, per thread).  A duplicate edge (two ERASE tuples of one key
 // in the first superstep) sets L.flags.  kPre: the permutations of the r
 // supersteps are read from pre (k_small_perm rows), else computed here.
+// Barriers order LDS only: a row is loaded one superstep ahead, and a full
+// barrier would wait for it at once.
 template <bool kPre, uint32_t kMax, uint32_t kThreads, bool kCompact>
 __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompact> &L, uint32_t m, uint32_t r,
                                                  uint32_t t0, uint32_t pl, uint32_t k0, uint32_t k1, uint32_t *c,
@@ -526,10 +490,9 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
     constexpr int kPer = (int)(kMax / kThreads);  // permutation items per thread
     constexpr int kSw = kPer / 2;                 // switches per thread
     static_assert(kSw <= 4, "a thread's switch statuses are the bytes of one 32-bit word");
-    constexpr int kTu = 4 * kSw + 1;              // tuples per thread (+ the idle record of odd m)
     constexpr int kPiW = kPer / 2;                // 32-bit words of a permutation row per thread
     constexpr uint8_t kAbsent = 0xFF;             // a switch index at or beyond ell
-    constexpr int kCellShift = 8 * (int)sizeof(Word) - small_cell_bits<kThreads>();
+    constexpr int kListShift = 8 * (int)sizeof(Word) - small_list_bits<kThreads>();
     const uint32_t tid = threadIdx.x;
     const uint32_t ell = m >> 1, mw = (m + 1) >> 1;
     uint32_t pw[kPiW];  // the next superstep's permutation row (kPre), loaded one superstep ahead
@@ -541,8 +504,17 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
             pw[q] = x < mw ? row[x] : 0u;
         }
     }
+    // Tuples stay in their own slots 4k + h (ERASE of source h, INSERT of target
+    // h - 2; 4 ell: the idle record of odd m), linked into a list per cell of
+    // word bits by one exchange each.  A head is (epoch << 16) | slot, the epoch
+    // a superstep, so lists need no clearing while the epochs last -- except
+    // where small_permute uses the cells in between (!kPre).
+    auto clear_heads = [&]() { reinterpret_cast<uint4 *>(L.cellw)[tid] = make_uint4(~0u, ~0u, ~0u, ~0u); };
+    uint16_t *nxt = L.sT;
     for (uint32_t s = 0; s < r; ++s) {
         const uint32_t t = t0 + s;
+        const uint32_t ep = kPre ? (s % kSmEpochs) << 16 : 0u;
+        if (kPre && s % kSmEpochs == 0) clear_heads();
         if (kPre) {
             uint32_t *lp = reinterpret_cast<uint32_t *>(L.pi);
 #pragma unroll
@@ -558,11 +530,22 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
                     pw[q] = x < mw ? row[x] : 0u;
                 }
             }
-            __syncthreads();
+            lds_barrier();
         } else {
             small_permute(L, m, t, k0, k1);
+            clear_heads();
+            lds_barrier();
         }
-        // switches: local checks; this thread's switches (k = tid + y kThreads)
+        auto link = [&](uint32_t slot, Word w) {
+            L.sK[slot] = w;
+            const uint32_t old = atomicExch(&L.cellw[(uint32_t)(w >> kListShift)], ep | slot);
+            nxt[slot] = (old & 0xFFFF0000u) == ep ? (uint16_t)old : (uint16_t)kSmNone;
+        };
+        auto head = [&](Word w) -> uint32_t {
+            const uint32_t c = L.cellw[(uint32_t)(w >> kListShift)];
+            return (c & 0xFFFF0000u) == ep ? c & 0xFFFFu : kSmNone;
+        };
+        // switches: local checks and tuples; this thread's switches (k = tid + y kThreads)
         // keep their indices and status (byte y of sst) in registers, and with
         // kPre (no permutation code beside them) their edge keys too
         uint32_t sij[kSw];
@@ -596,10 +579,11 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
             }
             const unsigned long long e1 = K::unpack(ki), e2 = K::unpack(kj);
             uint8_t status = ST_UNDECIDED;
+            Targets T{0, 0, false};
             if (pl_skip(k, t, pl, k0, k1)) {
                 status = ST_PL;
             } else {
-                const Targets T = switch_targets(e1, e2, i < j);
+                T = switch_targets(e1, e2, i < j);
                 if (kTg) {
                     tg[y < kTe ? y : 0][0] = K::pack(T.A);
                     tg[y < kTe ? y : 0][1] = K::pack(T.B);
@@ -611,108 +595,60 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
             }
             set_st(y, status);
             L.st[k] = status;
-            L.info[2 * k] = L.info[2 * k + 1] = 0xFFFFFFFFu;
-        }
-        // tuples (4 per switch, + the idle record of odd m) grouped by word,
-        // computed from the registers whenever the grouping needs them; the
-        // slots of this thread's INSERT tuples are kept
-        uint32_t islot[kSw];  // slots of the two INSERT tuples, 16 bits each
-#pragma unroll
-        for (int y = 0; y < kSw; ++y) islot[y] = 0;
-        {
-            auto tuple = [&](int q, Word *w, uint16_t *g) -> bool {
-                if (q == kTu - 1) {  // the idle record of odd m survives the superstep
-                    if (!((m & 1u) && tid == 0)) return false;
-                    *w = K::word(L.E[L.pi[m - 1]]);
-                    *g = kSmTagStays;
-                    return true;
-                }
-                const int y = q >> 2;
-                const uint32_t h = (uint32_t)q & 3u, k = tid + (uint32_t)y * kThreads;
-                if (st_of(y) == kAbsent) return false;
-                const uint32_t i = sij[y] & 0xFFFFu, j = sij[y] >> 16;
-                if (h < 2) {
-                    *w = K::word(key_of(y, h));
-                    *g = st_of(y) == ST_UNDECIDED ? (uint16_t)k : kSmTagStays;
-                    return true;
-                }
-                if (st_of(y) != ST_UNDECIDED) return false;
-                if (kTg) {
-                    *w = K::word(tg[y < kTe ? y : 0][h - 2]);
-                } else {
-                    const Targets T = switch_targets(K::unpack(key_of(y, 0)), K::unpack(key_of(y, 1)), i < j);
-                    *w = K::word(K::pack(h == 2 ? T.A : T.B));
-                }
-                *g = (uint16_t)(kSmTagInsert | (k << 1) | (h - 2));
-                return true;
-            };
-            auto placed = [&](int q, uint32_t slot) {
-                if (q < kTu - 1 && (q & 3) == 2) islot[q >> 2] = slot;
-                if (q < kTu - 1 && (q & 3) == 3) islot[q >> 2] |= slot << 16;
-            };
-            small_group_fn<kTu>(L, tuple, placed);
-        }
-        // all tuples of one key share a cell.  Input duplicates (first
-        // superstep only: every later state is simple): an ERASE tuple with
-        // another ERASE tuple of its key before it in (key, tag, slot) order.
-        if (s == 0) {
-            const uint32_t ntu = L.cell(8 * kThreads);
-            for (uint32_t y = tid; y < ntu; y += kThreads) {
-                const uint16_t ty = L.sT[y];
-                if (ty & kSmTagInsert) continue;
-                const Word wy = L.sK[y];
-                const uint32_t cc = (uint32_t)(wy >> kCellShift);
-                const uint32_t a = small_cell_begin(L, cc), e = L.cell(cc);
-                bool before = false;
-                cell_matches(L.sK, a, e, y, wy, [&](uint32_t z) {
-                    const uint16_t tz = L.sT[z];
-                    before |= tz < ty || (tz == ty && z < y);
-                });
-                if (before) atomicOr(&L.flags, 1u);
+            link(4 * k, K::word(ki));
+            link(4 * k + 1, K::word(kj));
+            if (status == ST_UNDECIDED) {
+                link(4 * k + 2, K::word(K::pack(T.A)));
+                link(4 * k + 3, K::word(K::pack(T.B)));
+            } else {
+                L.info[2 * k] = L.info[2 * k + 1] = 0xFFFFFFFFu;
             }
         }
-        // each INSERT tuple of an undecided switch finds in its cell its
-        // key group's smallest tag (-> eraser) and the largest tag before its
-        // own (-> predecessor inserter)
+        if ((m & 1u) && tid == 0) link(4 * ell, K::word(L.E[L.pi[m - 1]]));
+        lds_barrier();
+        // Input duplicates (first superstep only: every later state is
+        // simple): two ERASE tuples of one key
+        if (s == 0) {
+            for (uint32_t x = tid; x < m; x += kThreads) {
+                const uint32_t self = 4 * (x >> 1) + (x & 1u);
+                const Word w = L.sK[self];
+                for (uint32_t y = head(w); y != kSmNone; y = nxt[y])
+                    if (y != self && (y & 2u) == 0 && L.sK[y] == w) atomicOr(&L.flags, 1u);
+            }
+        }
+        // each INSERT tuple of an undecided switch finds in its cell's list the
+        // ERASE tuple of its key (-> eraser: a switch still undecided, else the
+        // edge stays) and the last INSERT tuple before its own (-> predecessor)
 #pragma unroll
         for (int y = 0; y < kSw; ++y) {
             if (st_of(y) != ST_UNDECIDED) continue;
             const uint32_t k = tid + (uint32_t)y * kThreads;
-            Word tw[2] = {0, 0};  // the two INSERT words, from the keys in registers (kPre)
-            if (kTg) {
-                tw[0] = K::word(tg[y < kTe ? y : 0][0]);
-                tw[1] = K::word(tg[y < kTe ? y : 0][1]);
-            } else if (kPre) {
-                const Targets T = switch_targets(K::unpack(key_of(y, 0)), K::unpack(key_of(y, 1)),
-                                                 (sij[y] & 0xFFFFu) < (sij[y] >> 16));
-                tw[0] = K::word(K::pack(T.A));
-                tw[1] = K::word(K::pack(T.B));
+            const Word wa = L.sK[4 * k + 2], wb = L.sK[4 * k + 3];
+            uint32_t za = head(wa), zb = head(wb);
+            uint32_t ea = kSmNone, eb = kSmNone, pa = 0, pb = 0;  // pa, pb: 1 + the predecessor
+            auto visit = [&](uint32_t z, uint32_t h, uint32_t *er, uint32_t *pr) {
+                const uint32_t kz = z >> 2;
+                if (z & 2u) {  // (the idle slot 4 ell is an ERASE slot)
+                    const uint32_t tz = 2 * kz + (z & 1u);
+                    if (tz < 2 * k + h) *pr = max(*pr, tz + 1);
+                } else {
+                    *er = kz < ell && L.st[kz] == ST_UNDECIDED ? kz : kSmStays;
+                }
+            };
+            while (za != kSmNone || zb != kSmNone) {  // both lists at once: the loads of one hide the other's
+                const uint32_t ya = za != kSmNone ? za : 4 * k + 2, yb = zb != kSmNone ? zb : 4 * k + 3;
+                const Word va = L.sK[ya], vb = L.sK[yb];
+                const uint32_t na = nxt[ya], nb = nxt[yb];
+                if (va == wa && ya != 4 * k + 2) visit(ya, 0, &ea, &pa);
+                if (vb == wb && yb != 4 * k + 3) visit(yb, 1, &eb, &pb);
+                if (za != kSmNone) za = na;
+                if (zb != kSmNone) zb = nb;
             }
-#pragma unroll 1
-            for (uint32_t h = 0; h < 2; ++h) {
-                const uint32_t sl = (islot[y] >> (16 * h)) & 0xFFFFu;
-                const Word wy = kPre ? (h ? tw[1] : tw[0]) : L.sK[sl];
-                const uint32_t ty = kSmTagInsert | (k << 1) | h;
-                const uint32_t cc = (uint32_t)(wy >> kCellShift);
-                const uint32_t a = small_cell_begin(L, cc), e = L.cell(cc);
-                uint32_t first = ty, prev = 0;
-                bool before = false;
-                cell_matches(L.sK, a, e, sl, wy, [&](uint32_t z) {
-                    const uint32_t tz = L.sT[z];
-                    first = min(first, tz);
-                    if (tz < ty) {  // INSERT tags are distinct
-                        prev = before ? max(prev, tz) : tz;
-                        before = true;
-                    }
-                });
-                uint32_t eraser = kSmNone;
-                if (!(first & kSmTagInsert)) eraser = first == kSmTagStays ? kSmStays : first;
-                const uint32_t pred = (before && (prev & kSmTagInsert)) ? (prev & ~(uint32_t)kSmTagInsert) : kSmNone;
-                L.info[2 * k + h] = (eraser << 16) | pred;
-            }
+            L.info[2 * k] = (ea << 16) | (pa ? pa - 1 : kSmNone);
+            L.info[2 * k + 1] = (eb << 16) | (pb ? pb - 1 : kSmNone);
         }
         if (tid == 0) L.und[0] = 0;
-        __syncthreads();
+        lds_barrier();
         // rounds of decisions until every switch is decided, one barrier each:
         // round x counts its waits in und[x mod 3] and clears und[x + 1 mod 3],
         // which was last read in round x - 2
@@ -731,7 +667,7 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
                     L.st[k] = (uint8_t)d;
                 }
             }
-            __syncthreads();
+            lds_barrier();
             if (L.und[x] == 0) break;  // uniform: no count of round x changes after the barrier
         }
         // writes and counts
@@ -754,7 +690,7 @@ __device__ __forceinline__ void small_chain_body(SmallLds<kMax, kThreads, kCompa
             c[2] += sv == ST_EXISTS;
             c[3] += sv == ST_PL;
         }
-        __syncthreads();
+        lds_barrier();
     }
 }
 
@@ -763,7 +699,7 @@ __device__ __forceinline__ void small_flush_counts(SmallLds<kMax, kThreads, kCom
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (c[q]) atomicAdd(&L.cnt[q], c[q]);
-    __syncthreads();
+    lds_barrier();
 }
 
 // One workgroup per listed graph of a batch (ranks `small[0 .. count)`, r of
@@ -806,18 +742,27 @@ __global__ __launch_bounds__(kThreads) void k_small_chain(const uint32_t *__rest
 // added to acc[0 .. 3].  A call's supersteps may come in several launches,
 // each resuming from the last one's output (in may equal out); a launch
 // does nothing once an earlier one has set err[0].  pre: the r supersteps'
-// permutations (k_small_perm).
+// permutations (k_small_perm).  host (nullable, pinned memory, a call's last
+// launch): receives the error word and, at words 8 .. 15, the counts, so no copy
+// has to follow (6 of the smallest call's 127 us).
 template <uint32_t kMax, uint32_t kThreads, bool kCompact>
 __global__ __launch_bounds__(kThreads) void k_small_plain(const unsigned long long *in, unsigned long long *out,
                                                           uint32_t m, uint32_t n, uint32_t t0, uint32_t r,
                                                           uint32_t pl, uint32_t k0, uint32_t k1,
                                                           unsigned long long *__restrict__ acc,
                                                           uint32_t *__restrict__ err,
-                                                          const uint16_t *__restrict__ pre) {
+                                                          const uint16_t *__restrict__ pre,
+                                                          uint32_t *__restrict__ host) {
     using K = SmallKeys<kCompact>;
     __shared__ SmallLds<kMax, kThreads, kCompact> L;
     const uint32_t tid = threadIdx.x;
-    if (err[0] != 0) return;  // uniform: written by an earlier launch
+    auto report = [&](uint32_t e) {
+        if (host && tid == 0) __hip_atomic_store(host, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    if (err[0] != 0) {  // uniform: written by an earlier launch
+        report(err[0]);
+        return;
+    }
     if (tid < 4) L.cnt[tid] = 0;
     if (tid == 0) L.flags = 0;
     __syncthreads();
@@ -838,11 +783,20 @@ __global__ __launch_bounds__(kThreads) void k_small_plain(const unsigned long lo
     small_flush_counts(L, c);
     const uint32_t fl = L.flags;
     if (fl) {
-        if (tid == 0) atomicOr(err, (fl & 1u ? ERR_DUP : 0u) | (fl >> 1));
+        const uint32_t e = (fl & 1u ? ERR_DUP : 0u) | (fl >> 1);
+        if (tid == 0) atomicOr(err, e);
+        report(e);
         return;
     }
     for (uint32_t li = tid; li < m; li += kThreads) out[li] = K::unpack(L.E[li]);
-    if (tid < 4) acc[tid] += L.cnt[tid];
+    if (tid < 4) {
+        const unsigned long long total = acc[tid] + L.cnt[tid];
+        acc[tid] = total;
+        if (host)
+            __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + 4 + tid, total, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    report(0u);
 }
 
 }  // namespace gesmc

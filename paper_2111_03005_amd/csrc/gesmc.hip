@@ -187,8 +187,8 @@ struct gesmc_ctx {
     uint32_t *counts1 = nullptr, *counts2 = nullptr, *partial = nullptr;
     // the next superstep's first level while this one runs (k_decide_scatter):
     // counts, chunk sums, bucket offsets and tile map, per-block outcome counts
-    uint32_t *ncounts = nullptr, *npartial = nullptr, *noff = nullptr, *fslot = nullptr;
-    uint64_t cap_ncounts = 0, cap_npartial = 0, cap_noff = 0, cap_fslot = 0;
+    uint32_t *nbuf = nullptr, *ncounts = nullptr, *npartial = nullptr, *noff = nullptr, *fslot = nullptr;
+    uint64_t cap_nbuf = 0;
     uint2 *pos = nullptr;       // where waiting switches' records stand (inside a tuple buffer)
     uint32_t *small = nullptr;  // counters, histograms, offsets (fixed size)
     uint16_t *small_pi = nullptr;  // permutations of the small-graph path (kSmallPiSteps rows of kCmpMax)
@@ -292,12 +292,12 @@ void free_buffers(gesmc_ctx *c) {
     }
     if (c->info) dev_free(c, c->info);
     c->info = nullptr;
-    for (uint32_t **pp : {&c->counts1, &c->counts2, &c->partial, &c->ncounts, &c->npartial, &c->noff, &c->fslot}) {
+    for (uint32_t **pp : {&c->counts1, &c->counts2, &c->partial, &c->nbuf}) {
         if (*pp) dev_free(c, *pp);
         *pp = nullptr;
     }
     c->cap_counts1 = c->cap_counts2 = c->cap_partial = 0;
-    c->cap_ncounts = c->cap_npartial = c->cap_noff = c->cap_fslot = 0;
+    c->cap_nbuf = 0;
     c->cap_tu = 0;
     c->tab = nullptr;
     c->sw_slot = nullptr;
@@ -1107,10 +1107,14 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
     const uint32_t gd = scatter_next ? round_tiles : grid_stride_blocks(c, p.ell);
     uint4 *slots = c->bslot;
     if (scatter_next) {
-        GESMC_TRY(ensure_words(c, &c->ncounts, &c->cap_ncounts, radix_words(q).counts1));
-        GESMC_TRY(ensure_words(c, &c->npartial, &c->cap_npartial, radix_words(q).partial));
-        GESMC_TRY(ensure_words(c, &c->noff, &c->cap_noff, 2 * kNoffTiles));
-        GESMC_TRY(ensure_words(c, &c->fslot, &c->cap_fslot, 4ull * (ge + (uint64_t)gd)));
+        // one buffer: outcome counts (16-byte slots), tile counts, chunk sums, offsets
+        const RadixWords rw = radix_words(q);
+        const uint64_t slot_words = 4 * (ge + (uint64_t)gd);
+        GESMC_TRY(ensure_words(c, &c->nbuf, &c->cap_nbuf, slot_words + rw.counts1 + rw.partial + 2 * kNoffTiles));
+        c->fslot = c->nbuf;
+        c->ncounts = c->fslot + slot_words;
+        c->npartial = c->ncounts + rw.counts1;
+        c->noff = c->npartial + rw.partial;
         slots = reinterpret_cast<uint4 *>(c->fslot);
     }
     SrcArgs sa{};
@@ -1314,11 +1318,17 @@ gesmc_status run_small_pieces(gesmc_ctx *c, hipStream_t s, int kid, const unsign
                          dim3(kThreads), 0, m, t0 + done, k0, k1, c->small_pi, done ? nullptr : c->err));
         GESMC_TRY(launch(c, s, kid, m, k_small_plain<kMax, kThreads, kCompact>, dim3(1), dim3(kThreads), 0,
                          done ? (const unsigned long long *)out : in, out, m, n, t0 + done, rr, pl, k0, k1, acc,
-                         c->err, (const uint16_t *)c->small_pi));
+                         c->err, (const uint16_t *)c->small_pi, done + rr < r ? nullptr : c->h_err));
         done += rr;
     }
     return GESMC_OK;
 }
+
+template <uint32_t M, uint32_t T, bool C>
+struct SmallSize {
+    static constexpr uint32_t kMax = M, kThreads = T;
+    static constexpr bool kCompact = C;
+};
 
 gesmc_status run_small_impl(gesmc_ctx *c, hipStream_t s, const uint64_t *d_in, uint64_t *d_out, uint32_t m,
                             uint32_t n, uint64_t seed, uint32_t t0, uint32_t r, uint32_t pl, gesmc_stats *stats) {
@@ -1328,17 +1338,25 @@ gesmc_status run_small_impl(gesmc_ctx *c, hipStream_t s, const uint64_t *d_in, u
     auto *out = (unsigned long long *)d_out;
     if (!c->small_pi) GESMC_TRY(dev_alloc(c, (void **)&c->small_pi, kSmallPiBytes));
     GESMC_TRY(check_hip(hipEventRecord(c->call_a, s), "hipEventRecord"));
-    if (m <= kSmallMax)
-        GESMC_TRY((run_small_pieces<kSmallMax, kSmallThreads, false>(c, s, KID_SMALL, in, out, m, n, t0, r, pl, k0,
-                                                                     k1, acc)));
+    // One workgroup runs the whole chain, so it takes as many threads as give
+    // each at least one switch (a batch member of at most 1024 edges shares its
+    // CU and runs on 256), and 32-bit keys and words wherever the ids fit
+    auto pieces = [&](auto size, int kid) {
+        using S = decltype(size);
+        return run_small_pieces<S::kMax, S::kThreads, S::kCompact>(c, s, kid, in, out, m, n, t0, r, pl, k0, k1, acc);
+    };
+    const bool ids16 = n <= kCmpMaxN;
+    if (m <= 1024)
+        GESMC_TRY(ids16 ? pieces(SmallSize<1024, 512, true>{}, KID_SMALL)
+                        : pieces(SmallSize<1024, 512, false>{}, KID_SMALL));
+    else if (ids16 && m <= 2048)
+        GESMC_TRY(pieces(SmallSize<2048, 1024, true>{}, KID_SMALL_MID));
     else if (m <= kMidMax)
-        GESMC_TRY((run_small_pieces<kMidMax, kMidThreads, false>(c, s, KID_SMALL_MID, in, out, m, n, t0, r, pl, k0,
-                                                                 k1, acc)));
+        GESMC_TRY(ids16 ? pieces(SmallSize<kMidMax, kMidThreads, true>{}, KID_SMALL_MID)
+                        : pieces(SmallSize<kMidMax, kMidThreads, false>{}, KID_SMALL_MID));
     else
-        GESMC_TRY((run_small_pieces<kCmpMax, kCmpThreads, true>(c, s, KID_SMALL_CMP, in, out, m, n, t0, r, pl, k0,
-                                                                k1, acc)));
+        GESMC_TRY(pieces(SmallSize<kCmpMax, kCmpThreads, true>{}, KID_SMALL_CMP));
     GESMC_TRY(check_hip(hipEventRecord(c->call_b, s), "hipEventRecord"));
-    GESMC_TRY(check_hip(hipMemcpyAsync(c->h_err, c->err, 64, hipMemcpyDeviceToHost, s), "hipMemcpyAsync"));
     GESMC_TRY(check_hip(hipStreamSynchronize(s), "hipStreamSynchronize"));
     if (c->profile) collect_profile(c);
     GESMC_TRY(map_err(*c->h_err));
