@@ -678,6 +678,25 @@ __global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu
 // ---------------------------------------------------------------------------
 // Decisions
 // ---------------------------------------------------------------------------
+// Where a judgement reads statuses: from memory while other workgroups write
+// them too, from memory while only this one does (its CU's cache serves the
+// loads), or from a copy in LDS.
+struct GridStatus {
+    static constexpr int kScope = __HIP_MEMORY_SCOPE_AGENT;
+    const uint8_t *st;
+    __device__ __forceinline__ uint8_t operator()(uint32_t k) const { return load_status(st, k); }
+};
+struct GroupStatus {
+    static constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const uint8_t *st;
+    __device__ __forceinline__ uint8_t operator()(uint32_t k) const { return load_status<true>(st, k); }
+};
+struct LdsStatus {
+    static constexpr int kScope = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const volatile uint8_t *st;  // (in LDS; every id is below the switches copied)
+    __device__ __forceinline__ uint8_t operator()(uint32_t k) const { return st[k] & kStOutcome; }
+};
+
 // Two shortcuts keep long chains (many switches inserting one hub edge)
 // linear: inserters older than the target's eraser saw the target present,
 // so they were rejected and the walk stops there; and a walk that passed
@@ -690,14 +709,14 @@ __global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu
 // rec.y) and leaves there the predecessor it waits for: decided predecessors
 // never change, so a repeated judgement of the same switch walks each link
 // once.
-template <bool kOne>
+template <typename St>
 __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn, uint2 rec, uint32_t self, uint32_t k,
-                                                  const uint8_t *st, uint32_t *from = nullptr) {
+                                                  St st, uint32_t *from = nullptr) {
     int v = V_OK;
     const uint32_t e = rec.x;
     if (e != kNoEraser) {
         if (e == kStays || e >= k) return V_ILLEGAL;
-        const uint8_t se = load_status<kOne>(st, e);
+        const uint8_t se = st(e);
         if (se == ST_UNDECIDED)
             v = V_WAIT;
         else if (se != ST_LEGAL)
@@ -720,17 +739,16 @@ __device__ __forceinline__ int judge_target_chain(uint2 *info, const Winners &wn
             p = kWalked;
             break;
         }
-        const uint8_t sp = load_status<kOne>(st, pk);
+        const uint8_t sp = st(pk);
         if (sp == ST_LEGAL) {
             out = V_ILLEGAL;
             break;
         }
         if (sp == ST_UNDECIDED) {
             // an inserter before it may have won already
-            out = load_status<kOne>(st, first >> 1) == ST_LEGAL ||
+            out = st(first >> 1) == ST_LEGAL ||
                           __hip_atomic_load(wn.win + first, __ATOMIC_RELAXED,
-                                            kOne ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT) !=
-                              kNoWinner
+                                            St::kScope) != kNoWinner
                       ? V_ILLEGAL
                       : V_WAIT;
             break;
@@ -769,11 +787,11 @@ __device__ __forceinline__ uint4 target_records(const uint2 *info, uint32_t k, u
 }
 
 // Verdict on switch k from its two target records.
-template <bool kOne = false>
-__device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 *info, const Winners &wn,
-                                                  const uint8_t *st, uint2 *from = nullptr) {
-    return max(judge_target_chain<kOne>(info, wn, make_uint2(recs.x, recs.y), 2 * k, k, st, from ? &from->x : nullptr),
-               judge_target_chain<kOne>(info, wn, make_uint2(recs.z, recs.w), 2 * k + 1, k, st,
+template <typename St>
+__device__ __forceinline__ int judge_switch_chain(uint32_t k, uint4 recs, uint2 *info, const Winners &wn, St st,
+                                                  uint2 *from = nullptr) {
+    return max(judge_target_chain(info, wn, make_uint2(recs.x, recs.y), 2 * k, k, st, from ? &from->x : nullptr),
+               judge_target_chain(info, wn, make_uint2(recs.z, recs.w), 2 * k + 1, k, st,
                                         from ? &from->y : nullptr));
 }
 
@@ -873,7 +891,8 @@ __global__ __launch_bounds__(kBlock) void k_decide_chain(const uint32_t *__restr
         *ij_out = ij;
         if ((sk & kStOutcome) != ST_UNDECIDED) return;
         const uint4 recs = target_records(info, k, sk);
-        *wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, st), k, recs, ij, ee, wn, st, out_idx, out_key,
+        *wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, GridStatus{st}), k, recs, ij, ee, wn, st,
+                                    out_idx, out_key,
                                     pos, &bc, cls);
     };
     const uint32_t n = list ? min(*count, ell) : ell;
@@ -1011,7 +1030,7 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
         slot[j] = 0;
         if (k >= ell || (sk[j] & kStOutcome) != ST_UNDECIDED) continue;
         const uint4 recs = target_records(info, k, sk[j]);
-        const int v = judge_switch_chain(k, recs, info, wn, st);
+        const int v = judge_switch_chain(k, recs, info, wn, GridStatus{st});
         if (v == V_WAIT) {
             waits |= 1u << j;
             slot[j] = atomicAdd(&s_nwait, 1u);
@@ -1105,6 +1124,10 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
 // are then final and only chains inside a chunk cost repeats.  Each repeat
 // counts as a round.
 constexpr int kChainFinish = 512;
+// Undecided switches, of so many in all, whose list and statuses go to LDS
+// (mixing on m = 1.4e4, 970 undecided: 47 -> 31 us; on 55,000 switches the copy
+// costs more than the two passes of 41 undecided ones save).
+constexpr uint32_t kFinishList = 2048, kFinishSwitches = 16384;
 constexpr uint32_t kSweepAfter = 8;
 constexpr uint32_t kSweepChunk = 1024;
 constexpr uint32_t kSweepWords = 16384;  // chunk marks: ids below 2^29 (m < 2^30)
@@ -1160,8 +1183,60 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
         if (acc.w) atomicAdd(&bc.pl, acc.w);
     }
     uint32_t *cur = list_a, *nxt = list_b, *ccur = count_a, *cnxt = count_b;
-    uint32_t n = s_n;
-    for (uint32_t here = 0; n > 0 && here < kSweepAfter; ++here) {
+    uint32_t n = s_n, here = 0;
+    __shared__ __align__(16) uint32_t s_chunks[kSweepWords];  // the sweep's chunk marks; statuses before it
+    if (n > 0 && n <= kFinishList && ell <= kFinishSwitches) {
+        // few enough switches: statuses and list in LDS.  A pass from memory is
+        // a chain of eight dependent loads and two atomics on the list counter.
+        __shared__ uint32_t l_list[2][kFinishList], l_n;
+        uint8_t *ls = reinterpret_cast<uint8_t *>(s_chunks);
+        for (uint32_t w = tid; 16 * w < ell; w += kChainFinish)  // (st has 64 bytes to spare)
+            reinterpret_cast<uint4 *>(s_chunks)[w] = reinterpret_cast<const uint4 *>(st)[w];
+        for (uint32_t q = tid; q < n; q += kChainFinish) l_list[0][q] = cur[q];
+        for (; n > 0 && here < kSweepAfter; ++here) {
+            const uint32_t *in = l_list[here & 1u];
+            uint32_t *out = l_list[(here + 1) & 1u];
+            if (tid == 0) l_n = 0;
+            __syncthreads();
+            const uint32_t trips = (n + kChainFinish - 1) / kChainFinish;
+            for (uint32_t r = 0; r < trips; ++r) {
+                const uint32_t q = r * kChainFinish + tid;
+                const uint32_t k = q < n ? in[q] : 0u;
+                const bool todo = q < n && k < ell && (ls[k] & kStOutcome) == ST_UNDECIDED;
+                uint4 recs = make_uint4(0, 0, 0, 0);
+                int v = V_WAIT;
+                if (todo) {
+                    recs = target_records(info, k, ls[k]);
+                    v = judge_switch_chain(k, recs, info, wn, LdsStatus{ls});
+                }
+                __syncthreads();  // (as below)
+                if (todo) {
+                    if (commit_switch_chain(v, k, recs, reinterpret_cast<const uint2 *>(s_idx)[k],
+                                            reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx, out_key,
+                                            pos, &bc, cls))
+                        out[atomicAdd(&l_n, 1u)] = k;
+                    else
+                        ls[k] = v == V_OK ? ST_LEGAL : ST_EXISTS;
+                }
+                __syncthreads();
+            }
+            if (tid == 0) {
+                const uint32_t nn = l_n;
+                if (nn >= n) atomicOr(err, ERR_INTERNAL);  // the smallest undecided switch always decides
+                s_n = nn >= n ? 0 : nn;
+                const unsigned long long done = atomicAdd(&ctr->rounds, (unsigned long long)trips) + trips;
+                if (round_limit && s_n > 0 && done >= round_limit) {
+                    atomicOr(err, ERR_ROUNDS);
+                    s_n = 0;
+                }
+            }
+            __syncthreads();
+            n = s_n;
+        }
+        for (uint32_t q = tid; q < n; q += kChainFinish) cur[q] = l_list[here & 1u][q];  // (the sweep's)
+        __syncthreads();
+    }
+    for (; n > 0 && here < kSweepAfter; ++here) {
         if (tid == 0) *cnxt = 0;
         __threadfence();
         __syncthreads();
@@ -1178,7 +1253,7 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                 todo = (sk & kStOutcome) == ST_UNDECIDED;
                 if (todo) {
                     recs = target_records(info, k, sk);
-                    v = judge_switch_chain<true>(k, recs, info, wn, st);
+                    v = judge_switch_chain(k, recs, info, wn, GroupStatus{st});
                 }
             }
             // a pass judges by what earlier passes decided, so its round count
@@ -1213,7 +1288,6 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
         cnxt = tc;
     }
     if (n > 0) {
-        __shared__ uint32_t s_chunks[kSweepWords];
         __shared__ uint32_t s_wait, s_done, s_stop;
         __shared__ unsigned long long s_rounds;
         const uint32_t nwords = ((ell + kSweepChunk - 1) / kSweepChunk + 31) / 32;
@@ -1251,7 +1325,7 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                         const uint32_t k = kb + tid + j * kChainFinish;
                         if (k >= ke || load_status<true>(st, k) != ST_UNDECIDED) continue;
                         const uint4 recs = target_records(info, k, st[k]);
-                        if (commit_switch_chain(judge_switch_chain<true>(k, recs, info, wn, st, &from[j]), k, recs,
+                        if (commit_switch_chain(judge_switch_chain(k, recs, info, wn, GroupStatus{st}, &from[j]), k, recs,
                                                 reinterpret_cast<const uint2 *>(s_idx)[k],
                                                 reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx,
                                                 out_key, pos, &bc, cls))
