@@ -541,13 +541,19 @@ Plan batch_plan(const gesmc_ctx *c, uint32_t m, uint64_t nb) {
 }
 
 // Radix plan for n records: B bucket bits (mean bucket <= bucket_avg), split
-// into a coarse level (level1_bits) and a second level of the rest.
-Plan make_plan(const gesmc_ctx *c, uint32_t m) {
+// into a coarse level (level1_bits) and a second level of the rest.  A bucket
+// is one workgroup's, so small passes take smaller means (`spread`): about
+// kSpreadBuckets buckets, of kSpreadMean records at least (us per superstep at a
+// mean of 1152, 288 and 144: m = 7,213 62.7, 56.5, 56.1; 30,204 62.2, 57.5,
+// 59.3; 109,596 73, 83, 104; hub keys, m = 13,691: 156, 124, 119).
+constexpr uint32_t kSpreadBuckets = 128, kSpreadMean = 144;
+Plan make_plan(const gesmc_ctx *c, uint32_t m, bool spread = true) {
     Plan p;
     p.m = m;
     p.ell = m / 2;
+    const uint32_t mean = spread ? std::min(c->bucket_avg, std::max(kSpreadMean, m / kSpreadBuckets)) : c->bucket_avg;
     uint32_t B = 0;
-    while (B < kMaxFineBits && ((uint64_t)c->bucket_avg << B) < m) ++B;
+    while (B < kMaxFineBits && ((uint64_t)mean << B) < m) ++B;
     p.bbits = B;
     p.b1 = level1_bits(B, c->level1_cap);
     p.b2 = B - p.b1;
@@ -916,9 +922,10 @@ TuplePack tuple_pack(const gesmc_ctx *c, const Plan &p, uint32_t nslots, uint64_
     const int vb = width_below(vend), db = width_below(std::min(dend, vend)), w = vb + db;
     int kb = std::max(1, width_below(2ull * (nslots / 4) + 1));  // 2 ell < 2^kb, so ell < 2^kb - 1
     int local = 0;
-    // the hash bits a first level of two would drop decide also where one level
-    // drops more: which calls pack does not depend on the number of passes
-    const int drop = (int)std::min(p.b1, level1_bits(p.bbits, c->level1_cap, false, false));
+    // the hash bits a first level of two over full buckets would drop decide also
+    // where a pass drops more: which calls pack does not depend on its plan
+    const Plan full = make_plan(c, p.m, false);
+    const int drop = (int)std::min(p.b1, level1_bits(full.bbits, c->level1_cap, false, false));
     if ((w - drop + kb + 1 > 64 || c->pack_tuples == 2) && mmax > 0) {
         // a batch (mmax: its largest even record count): tags local to each
         // graph, codes below mmax, so its switches k < mmax / 2 < 2^kb - 1
@@ -949,13 +956,21 @@ gesmc_status partition_and_resolve(gesmc_ctx *c, hipStream_t s, uint32_t nslots,
                                    GraphErr ge = GraphErr{nullptr, 0, nullptr}, const EmitSource *emit = nullptr,
                                    uint64_t vend = 0, uint64_t dend = 0, const EmitOut *eo = nullptr,
                                    uint64_t mmax = 0) {
-    const Plan p = make_plan(c, nslots);
+    Plan p = make_plan(c, nslots);
     int parts = 0;
     const uint32_t *poff = nullptr;
     uint32_t np = 0;
     // graph-local tags need the graphs (emit: their first switches; resolve: the key's graph)
-    const TuplePack pk = emit ? tuple_pack(c, p, nslots, vend, dend, (ge.gr && emit->sa.pg) ? mmax : 0)
-                              : TuplePack{0, 0, 0, 0, 0, 0};
+    const uint64_t mm = (ge.gr && emit && emit->sa.pg) ? mmax : 0;
+    TuplePack pk{0, 0, 0, 0, 0, 0};
+    if (emit) {
+        pk = tuple_pack(c, p, nslots, vend, dend, mm);
+        if (!pk.w) {  // too few hash bits below so many buckets (dense graphs)?
+            const Plan full = make_plan(c, nslots, false);
+            pk = tuple_pack(c, full, nslots, vend, dend, mm);
+            if (pk.w) p = full;
+        }
+    }
     c->tuple_bytes = pk.w ? 8u : 12u;
     if (pk.w) {
         SrcArgs sa = emit->sa;
