@@ -482,7 +482,10 @@ uint32_t digit_in_key(const Plan &p, uint32_t n) {
     return GESMC_DIGIT_IN_KEY && n <= (1u << 24) && p.b1 <= 8 && p.b2 <= 8 ? 1u : 0u;
 }
 
-uint32_t tile_for(uint32_t n) { return n >= kLargeTileRecords ? (uint32_t)kTileLarge : (uint32_t)kTileSmall; }
+uint32_t tile_for(uint32_t n) {
+    return n >= kLargeTileRecords ? (uint32_t)kTileLarge
+                                  : n >= kTinyTileRecords ? (uint32_t)kTileSmall : (uint32_t)kTileTiny;
+}
 
 // Tiles per chunk of the level-1 column scan: a power of two in [8, 256]
 // giving about 192 chunks.
@@ -517,7 +520,7 @@ uint32_t level1_bits(uint32_t B, uint32_t cap, bool ceil_half = false, bool one_
 }
 
 // Plan of a batch permutation: global buckets [0, nb) over m records.  The
-// second level runs on 2048-record tiles at every size (its scatter stages
+// second level runs on tiles of at most 2048 records (its scatter stages
 // 14 bytes per record: smaller workgroups, more of them per CU), the first
 // on the size's usual tile; 0: both levels on the usual tile.
 #ifndef GESMC_BATCH_LEVEL2_SMALL_TILES
@@ -535,7 +538,7 @@ Plan batch_plan(const gesmc_ctx *c, uint32_t m, uint64_t nb) {
     p.ncoarse = 1u << p.b1;
     p.nfine = 1u << B;
     p.tile = tile_for(m);
-    p.tile2 = GESMC_BATCH_LEVEL2_SMALL_TILES ? (uint32_t)kTileSmall : 0u;
+    p.tile2 = GESMC_BATCH_LEVEL2_SMALL_TILES ? std::min<uint32_t>(p.tile, kTileSmall) : 0u;
     p.ntiles1 = std::max<uint32_t>(1, ceil_div(m, p.tile));
     return p;
 }
@@ -813,7 +816,7 @@ gesmc_status radix_distribute(gesmc_ctx *c, hipStream_t s, const Plan &p, uint32
     const uint32_t t2 = p.tile2 ? p.tile2 : p.tile;
     if (p.tile == (uint32_t)kTileLarge)
         return t2 == (uint32_t)kTileLarge ? GESMC_RADIX_T(kTileLarge, kTileLarge) : GESMC_RADIX_T(kTileLarge, kTileSmall);
-    return GESMC_RADIX_T(kTileSmall, kTileSmall);
+    return p.tile == (uint32_t)kTileSmall ? GESMC_RADIX_T(kTileSmall, kTileSmall) : GESMC_RADIX_T(kTileTiny, kTileTiny);
 #undef GESMC_RADIX_T
 }
 
@@ -1045,16 +1048,20 @@ gesmc_status decide_and_scatter_t(gesmc_ctx *c, hipStream_t s, const Plan &q, ui
 gesmc_status decide_and_scatter(gesmc_ctx *c, hipStream_t s, const Plan &q, uint32_t t, uint32_t k0, uint32_t k1,
                                 const BatchStep *bs, const uint32_t *si, const unsigned long long *sk, uint4 *slots,
                                 uint32_t cls) {
-    const bool large = q.tile == (uint32_t)kTileLarge;
+#define GESMC_DECIDE_T(SRC)                                                                                  \
+    (q.tile == (uint32_t)kTileLarge                                                                          \
+         ? decide_and_scatter_t<SRC, kTileLarge>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)                 \
+     : q.tile == (uint32_t)kTileSmall                                                                        \
+         ? decide_and_scatter_t<SRC, kTileSmall>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)                 \
+         : decide_and_scatter_t<SRC, kTileTiny>(c, s, q, t, k0, k1, sa, si, sk, slots, cls))
     if (bs) {
         const SrcArgs sa{bs->gr, bs->pg, bs->bk, bs->step + 1, (int)q.bbits};
-        return large ? decide_and_scatter_t<kSrcBatch, kTileLarge>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)
-                     : decide_and_scatter_t<kSrcBatch, kTileSmall>(c, s, q, t, k0, k1, sa, si, sk, slots, cls);
+        return GESMC_DECIDE_T(kSrcBatch);
     }
     SrcArgs sa{};
     sa.dig_in_key = q.dig_in_key;
-    return large ? decide_and_scatter_t<kSrcPerm, kTileLarge>(c, s, q, t, k0, k1, sa, si, sk, slots, cls)
-                 : decide_and_scatter_t<kSrcPerm, kTileSmall>(c, s, q, t, k0, k1, sa, si, sk, slots, cls);
+    return GESMC_DECIDE_T(kSrcPerm);
+#undef GESMC_DECIDE_T
 }
 
 // Multi-workgroup list rounds before the finisher while
@@ -2344,6 +2351,7 @@ gesmc_status gesmc_create(int hip_device, gesmc_ctx **out) {
     // kernels whose dynamic LDS can exceed 64 KiB (gfx950 has 160 KiB per CU)
     (void)hipFuncSetAttribute((const void *)k_sort_buckets, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sort_lds_bytes(kLdsCap));
+    set_scatter_lds_limits<kTileTiny>();
     set_scatter_lds_limits<kTileSmall>();
     set_scatter_lds_limits<kTileLarge>();
     for (const void *f : {(const void *)k_resolve<false>, (const void *)k_resolve<true>})

@@ -21,8 +21,18 @@ namespace gesmc {
 
 // Records per scatter workgroup ("tile"): 2048, or 4096 for passes over at
 // least 2^25 records, where the longer runs per digit of the second level
-// pay off; on smaller passes the larger tile leaves CUs idle.
-constexpr int kTileSmall = 2048, kTileLarge = 4096;
+// pay off; on smaller passes the larger tile leaves CUs idle.  Passes below
+// 2^17 records take 1024: there a pass is one wave of at most 128 workgroups
+// whatever the tile, so its time is that of one tile (loads, LDS ranks and
+// stores in series).  Microseconds per superstep at tiles of 2048 and 1024:
+// m = 7,213 55.8 and 48.5, 30,204 56.9 and 51.7, 60,370 64.2 and 60.5; at
+// 109,596 and above the two agree within the spread (69.9 and 70.5, 164,722
+// 78.0 and 78.0, 219,744 82.9 and 84.2).
+constexpr int kTileTiny = 1024, kTileSmall = 2048, kTileLarge = 4096;
+#ifndef GESMC_TINY_TILE_RECORDS
+#define GESMC_TINY_TILE_RECORDS (1u << 17)
+#endif
+constexpr uint32_t kTinyTileRecords = GESMC_TINY_TILE_RECORDS;
 #ifndef GESMC_LARGE_TILE_RECORDS
 #define GESMC_LARGE_TILE_RECORDS (1u << 25)
 #endif

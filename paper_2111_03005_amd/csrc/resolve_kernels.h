@@ -828,7 +828,7 @@ __device__ __forceinline__ bool commit_switch_chain(int v, uint32_t k, uint4 rec
 // Undecided switches staged per workgroup of k_decide_chain: the switches of
 // one 4096-record tile.
 constexpr uint32_t kWaitStage = kTileLarge / 2;
-static_assert(kWaitStage >= kTileSmall / 2 && kWaitStage % kBlock == 0, "stage flushes cover whole trips");
+static_assert(kTileTiny % (2 * kBlock) == 0 && kWaitStage % kBlock == 0, "stage flushes cover whole trips");
 
 // Round 1 (list == nullptr: every switch) or a later round over a list.
 // With fold, also sums the nfold per-block counts of the emit and of round 1
