@@ -216,6 +216,8 @@ struct gesmc_ctx {
     uint4 *chunks = nullptr;
     uint64_t chunk_cap = 0;
     uint32_t *small_list = nullptr, *rrank = nullptr;  // small graphs' ranks; r per rank
+    unsigned char *mix_blk = nullptr;                 // kept between mixing diagnostics (MixBlock)
+    uint64_t mix_bytes = 0;
     bool small_graphs = true;                         // graphs with m <= kSmallMax run in LDS
     bool unpermute_buckets = true;                    // large write-backs by index buckets
     gesmc_alloc_fn alloc_fn = nullptr;                // the caller's allocator (gesmc_set_allocator)
@@ -269,6 +271,7 @@ constexpr uint32_t kMaxLevelBits = 12;  // digit bits of one radix level (first 
 constexpr uint64_t kMaxEdges = 1ull << 30;
 
 void dev_free(gesmc_ctx *c, void *p);
+void release_mix_block(gesmc_ctx *c);
 
 void free_buffers(gesmc_ctx *c) {
     for (int q = 0; q < 3; ++q) {
@@ -320,6 +323,10 @@ gesmc_status dev_alloc(gesmc_ctx *c, void **p, size_t bytes) {
     const size_t b = bytes ? bytes : 16;
     if (c && c->alloc_fn) {
         void *q = c->alloc_fn(b, c->alloc_user);
+        if (!q && c->mix_blk) {
+            release_mix_block(c);
+            q = c->alloc_fn(b, c->alloc_user);
+        }
         *p = q;
         if (!q || ((uintptr_t)q & 255u)) {
             if (q) c->free_fn(q, c->alloc_user);
@@ -332,7 +339,13 @@ gesmc_status dev_alloc(gesmc_ctx *c, void **p, size_t bytes) {
         c->hooked[q] = HookedBuffer{c->free_fn, c->alloc_user};
         return GESMC_OK;
     }
-    if (hipMalloc(p, b) != hipSuccess) {
+    hipError_t e = hipMalloc(p, b);
+    if (e != hipSuccess && c && c->mix_blk) {
+        (void)hipGetLastError();
+        release_mix_block(c);
+        e = hipMalloc(p, b);
+    }
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         *p = nullptr;
         set_error("hipMalloc of %zu bytes failed", bytes);
@@ -357,6 +370,12 @@ void dev_free(gesmc_ctx *c, void *p) {
         }
     }
     (void)hipFree(p);
+}
+
+void release_mix_block(gesmc_ctx *c) {
+    if (c->mix_blk) dev_free(c, c->mix_blk);
+    c->mix_blk = nullptr;
+    c->mix_bytes = 0;
 }
 
 uint64_t table_slots_for(uint64_t m) {
@@ -2390,6 +2409,7 @@ void gesmc_destroy(gesmc_ctx *c) {
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
     free_buffers(c);
+    release_mix_block(c);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->small) dev_free(c, c->small);
     if (c->small_pi) dev_free(c, c->small_pi);

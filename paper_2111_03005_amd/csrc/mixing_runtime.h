@@ -6,6 +6,43 @@ namespace {
 
 constexpr uint32_t kMixMaxN = 1u << 14;  // pair ids below 2^27
 
+// The diagnostic's device block.  After a call that finished (its stream is
+// idle then) the context keeps a block of up to kMixKeepBytes for its next
+// diagnostic, instead of gigabytes mapped and unmapped on each call: the
+// driver clears freed memory before it maps it again, and calls that follow
+// each other sooner than that wait.  n = 2^13, seven thinnings (2.9 GB), 400
+// calls in a row, ms at the median and the 90th percentile: K = 200 21.9 and
+// 163 without, 21.2 and 21.2 with it; K = 20 3.95 and 225, 3.27 and 3.30.
+// It is returned with the context, for a larger block, or as soon as another
+// allocation of the context finds no memory.
+constexpr uint64_t kMixKeepBytes = 4ull << 30;
+
+struct MixBlock {
+    gesmc_ctx *c;
+    unsigned char *p = nullptr;
+    uint64_t bytes = 0;
+
+    gesmc_status take(uint64_t want) {
+        if (c->mix_bytes < want) release_mix_block(c);
+        bytes = want;
+        if (!c->mix_blk) return dev_alloc(c, (void **)&p, want);
+        p = c->mix_blk;
+        bytes = c->mix_bytes;
+        c->mix_blk = nullptr;
+        c->mix_bytes = 0;
+        return GESMC_OK;
+    }
+    void keep() {
+        if (bytes > kMixKeepBytes) return;
+        c->mix_blk = p;
+        c->mix_bytes = bytes;
+        p = nullptr;
+    }
+    ~MixBlock() {
+        if (p) dev_free(c, p);
+    }
+};
+
 // The G-ES-MC chain of a diagnostic on the multi-kernel supersteps: the state
 // stays in its records (buffer 0) between supersteps, whose order no sample
 // depends on, and the host waits once per kMixPiece supersteps instead of
@@ -86,15 +123,9 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     const uint64_t mm = std::max<uint32_t>(m, 1);
     const uint64_t per_q = mm * 8 + words * 8 + npairs * sizeof(MixCount) + 256 * 3;
     const uint64_t bytes = mm * 8 + 2 * (words * 4 + 256) + 64 + nthin * per_q + 256;
-    unsigned char *blk = nullptr;
-    GESMC_TRY(dev_alloc(c, (void **)&blk, bytes));
-    struct Free {
-        gesmc_ctx *c;
-        unsigned char *p;
-        ~Free() {
-            if (p) dev_free(c, p);
-        }
-    } guard{c, blk};
+    MixBlock block{c};
+    GESMC_TRY(block.take(bytes));
+    unsigned char *const blk = block.p;
     uint64_t off = 0;
     auto take = [&](uint64_t b) {
         off = (off + 255) & ~255ull;
@@ -188,6 +219,7 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     if (ms_total)
         *ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
     if (c->profile) collect_profile(c);
+    block.keep();
     return GESMC_OK;
 }
 

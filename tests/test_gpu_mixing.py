@@ -83,3 +83,19 @@ def test_mixing_argument_checks(ctx):
     with pytest.raises(gesmc.GesmcError) as ei:
         ctx.mixing(to_dev(bad), 10, 1, 10, [1])
     assert ei.value.status == gesmc.E_NOT_SIMPLE
+
+
+# m above the LDS chain's sizes: the state stays on the device, with a wait
+# every 64 supersteps (K at that edge, and thinnings that leave it out)
+@pytest.mark.parametrize("K,thin", [(1, [1]), (64, [1, 3, 64]), (65, [2, 64, 65]), (130, [1, 5, 66])])
+@pytest.mark.parametrize("pl", [0, 1 << 30])
+def test_mixing_resident_pieces(ctx, K, thin, pl):
+    E = graphgen.gnp(1500, 0.006, 8)
+    check(ctx, E, 1500, 11, K, thin, 0, pl=pl, label="resident")
+
+
+def test_mixing_calls_share_block(ctx):
+    """One context's calls of changing sizes, larger and smaller, each on its own."""
+    for n, p, thin in ((300, 0.1, [1, 2]), (1500, 0.006, [1, 2, 3, 4]), (200, 0.05, [3]), (1500, 0.006, [2])):
+        for chain in (0, 1):
+            check(ctx, graphgen.gnp(n, p, n), n, 7, 12, thin, chain, label="sequence")
