@@ -49,13 +49,13 @@ def kernel_bytes(name: str, m: int, ell: int, tb: int = 12) -> float | None:
         "k_unpermute": 12.0 * m + 8.0 * m,
         "k_load": 8.0 * m + 12.0 * m,
         # sorted-tuples dependency resolution: 4 tuples of tb bytes per switch
-        "k_emit": 24.0 * ell + 16.0 * ell + 1.0 * ell,   # pair records in, free target records + statuses out
-        "k_tcounts1": 24.0 * ell + 16.0 * ell + 1.0 * ell,  # the emit fused in: as k_emit
+        "k_emit": 24.0 * ell + 1.0 * ell + 48.0 * ell,   # pair records in, statuses and (tag, key) tuples out
+        "k_tcounts1": 24.0 * ell + 1.0 * ell,            # the emit fused in: pair records in, statuses out
         "k_tscatter1": 24.0 * ell + 4.0 * tb * ell,      # pair records in, partitioned tuples out
         "k_tcounts2": 32.0 * ell,                        # the 8-byte key (or packed) word of each tuple
         "k_tscatter2": 8.0 * tb * ell,
         "k_resolve": 4.0 * tb * ell,                     # tuples in (records out are rare)
-        "k_decide_chain1": 16.0 * ell + 24.0 * ell + 24.0 * ell + 2.0 * ell,
+        "k_decide_chain1": 24.0 * ell + 24.0 * ell + 2.0 * ell,  # pair records and statuses, in and out
     }.get(name)
 
 

@@ -7,7 +7,8 @@
 //   level 1   : coarse digit = top b1 bits of K (b1 <= 10), LDS-staged scatter;
 //               run bases from per-tile digit counts and a column scan
 //   level 2   : sub digit    = next b2 bits, scattered inside each coarse
-//               bucket (its region is small enough to stay L2/MALL resident)
+//               bucket (its region is small enough to stay L2/MALL resident);
+//               left out where level 1 takes all bucket bits (at most 10)
 //   bucket    : each fine bucket (~400-1500 records) is counting-sorted in
 //               LDS on the next kCellBits bits of K (about one record per
 //               cell), then each record's place in its cell is the number of
