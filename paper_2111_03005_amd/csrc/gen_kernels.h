@@ -624,26 +624,49 @@ __global__ __launch_bounds__(64) void k_hh_steps(const uint32_t *__restrict__ E0
     }
 }
 
-// The edges of the logged steps: block w takes steps [w 256, w 256 + 256),
-// whose edges are contiguous; each thread finds its step in the staged
-// offsets.  Edge keys (min id << 32) | max id.
-constexpr uint32_t kHhEmitSteps = 256;
+// The edges of the logged steps.  A workgroup takes kHhEmitEdges consecutive
+// edges, not a number of steps: degrees fall along the steps, so 256 steps of
+// the front hold up to 256 * D edges.  It finds the step of its first edge in
+// the log (kBlock probes at a time), stages the steps that start before its
+// last (every step has an edge, so at most kHhEmitEdges of them), and each
+// thread finds its edges' steps there.  Edge keys (min id << 32) | max id.
+// n = 2^20, Pld([5..1024], 2.5), m = 6.67e6: 497 us by 256 steps a workgroup
+// (its first workgroups alone), 42 by edges (1.3 TB/s of keys; 512 or 2048
+// edges a workgroup: the same).
+constexpr uint32_t kHhEmitEdges = 1024;
+static_assert(kHhEmitEdges % kBlock == 0, "whole trips");
 
 __global__ __launch_bounds__(kBlock) void k_hh_emit(const HhStep *__restrict__ log, uint32_t S, uint32_t m,
                                                     const uint32_t *__restrict__ O, uint32_t n,
                                                     unsigned long long *__restrict__ out) {
-    __shared__ uint32_t offs[kHhEmitSteps + 1];
-    __shared__ HhStep st[kHhEmitSteps];
-    const uint32_t s0 = blockIdx.x * kHhEmitSteps;
-    const uint32_t ns = min(kHhEmitSteps, S - s0);
-    for (uint32_t i = threadIdx.x; i < ns; i += kBlock) {
-        st[i] = log[s0 + i];
-        offs[i] = st[i].off;
+    __shared__ HhStep st[kHhEmitEdges];
+    __shared__ uint32_t offs[kHhEmitEdges];
+    const uint32_t e0 = blockIdx.x * kHhEmitEdges, e1 = e0 + min(kHhEmitEdges, m - e0);
+    uint32_t s0 = 0;
+    for (uint32_t len = S; len > 1;) {  // the last step with offset <= e0 is in [s0, s0 + len)
+        const uint32_t w = (len + kBlock - 1) / kBlock, i = threadIdx.x * w;
+        const uint32_t c = max(__syncthreads_count(i < len && log[s0 + i].off <= e0), 1);
+        s0 += (c - 1) * w;
+        len = min(w, len - (c - 1) * w);
     }
-    if (threadIdx.x == 0) offs[ns] = s0 + ns < S ? log[s0 + ns].off : m;
-    __syncthreads();
-    const uint32_t e0 = offs[0], e1 = offs[ns];
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
+    uint32_t ns = 0;
+    for (uint32_t base = 0; base < kHhEmitEdges; base += kBlock) {
+        const uint32_t i = base + threadIdx.x;
+        bool in = i < S - s0;
+        if (in) {
+            const HhStep v = log[s0 + i];
+            in = v.off < e1;
+            if (in) {
+                st[i] = v;
+                offs[i] = v.off;
+            }
+        }
+        const uint32_t c = __syncthreads_count(in);
+        ns += c;
+        if (c < kBlock) break;
+    }
+    for (uint32_t j = threadIdx.x; j < e1 - e0 && ns; j += kBlock) {
+        const uint32_t e = e0 + j;
         uint32_t lo = 0, hi = ns - 1;  // the last step whose offset is <= e
         while (lo < hi) {
             const uint32_t mid = (lo + hi + 1) >> 1;
@@ -655,7 +678,7 @@ __global__ __launch_bounds__(kBlock) void k_hh_emit(const HhStep *__restrict__ l
         const HhStep t = st[lo];
         const uint32_t s = s0 + lo, i = e - t.off, pre = t.a - s - 1;
         const uint32_t p = i < pre ? s + 1 + i : t.b - t.k + (i - pre);
-        if (p >= n || e >= m) continue;  // never for a consistent log
+        if (p >= n) continue;  // never for a consistent log
         const uint32_t u = O[s], v = O[p];
         out[e] = u < v ? ((unsigned long long)u << 32) | v : ((unsigned long long)v << 32) | u;
     }

@@ -246,7 +246,7 @@ gesmc_status gen_hh_impl(gesmc_ctx *c, void *stream, uint32_t n, const uint32_t 
         set_error("Havel-Hakimi took %u steps on %u vertices", S, n);
         return GESMC_E_INTERNAL;
     }
-    GESMC_TRY(launch(c, s, KID_GEN, m, k_hh_emit, dim3(ceil_div(S, kHhEmitSteps)), dim3(kBlock), 0,
+    GESMC_TRY(launch(c, s, KID_GEN, m, k_hh_emit, dim3(ceil_div(m, kHhEmitEdges)), dim3(kBlock), 0,
                      (const HhStep *)log, S, (uint32_t)m, (const uint32_t *)O, n, (unsigned long long *)d_out));
     return gen_sync(c, s);
 }

@@ -169,3 +169,16 @@ def test_havel_hakimi_runs_and_boundaries(ctx, label, deg):
     if deg.sum() % 2:
         deg[-1] += 1
     check_hh(ctx, deg, label)
+
+
+# edge counts at a workgroup's 1024 edges, one edge per step (as many steps as
+# edges, and more than 256^2 of them), and one step longer than several workgroups
+@pytest.mark.parametrize("deg", [np.full(2 * k, 1) for k in (1, 1023, 1024, 1025, 2048, 70000)]
+                         + [np.concatenate([[5000], np.full(5000 + x, 1)]) for x in (0, 2, 120)]
+                         + [np.concatenate([np.full(4, 3000), np.full(6000, 2), np.full(3001, 1)])],
+                         ids=lambda d: "n%d" % len(d))
+def test_havel_hakimi_emit_edges(ctx, deg):
+    deg = np.asarray(deg, dtype=np.uint32)
+    if deg.sum() % 2:
+        deg[-1] += 1
+    check_hh(ctx, deg, "emit n=%d" % len(deg))
