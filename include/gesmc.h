@@ -425,7 +425,10 @@ gesmc_status gesmc_es_draws(gesmc_ctx *ctx, void *stream, uint64_t m, uint64_t s
  * summed over tracked edges (exact integers).  ms_chain (host, nullable):
  * wall time of the chain and its sampling.  Limits: 2 <= n <= 2^14 (dense
  * pair counters: 12 bytes per vertex pair and thinning value), 1 <= nthin
- * <= 16, every k >= 1.  Device memory is allocated for the call and freed.
+ * <= 16, every k >= 1.  The context keeps a call's device block of up to 4 GiB
+ * for its next diagnostic; it is returned for a larger one, with the context, or
+ * when another allocation of the context finds no memory.  Larger blocks are
+ * freed before the call returns.
  */
 typedef struct gesmc_mixing_result {
     uint32_t k;            /* thinning value                                */
