@@ -162,7 +162,9 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
                 GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                                  win.last, (uint64_t)m));
             uint32_t tag = 1;  // of the window's uses: 2 W a window, below 2 (epoch + W) in an epoch
-            for (uint64_t wb = kb; W > 0 && wb < ke; tag += 2 * W, wb += W) {
+            // (by offset: a counter near 2^64 must not wrap past the epoch's end)
+            for (uint64_t o = 0; W > 0 && o < ke - kb; tag += 2 * W, o += W) {
+                const uint64_t wb = kb + o;
                 const uint32_t nw = (uint32_t)std::min<uint64_t>(W, ke - wb);
                 const dim3 grid(ceil_div(nw, kBlock)), block(kBlock);
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, nw, k_es_win_draw, grid, block, 0, win, nw, passes, wb, m,

@@ -143,3 +143,10 @@ def test_es_full_size_powerlaw_n2p20(ctx):
     E, n = graphgen.workload_powerlaw_1m()
     st = check_es(ctx, E, n, 42, 0, len(E), label="pld_n2^20_g2.5, r = m")
     print("ParES stats:", st, flush=True)
+
+
+# the last counter is 2^64 - 2, the last window or epoch not a whole one
+@pytest.mark.parametrize("m,r", [(300, 5000), (4096, 1025), (4096, 2560), (6000, 70001)])
+def test_es_counters_up_to_the_last(ctx, m, r):
+    E = np.random.default_rng(m).permutation(graphgen.gnp(900, 0.02, 12))[:m]
+    check_es(ctx, E, 900, 21, 2**64 - 1 - r, r, label="last counters", outcomes=True)
