@@ -385,8 +385,10 @@ gesmc_status gesmc_server_info_get(gesmc_server *srv, gesmc_server_info *out);
  * present).  stats (host, nullable).  m < 2 copies the canonicalised input
  * (no two distinct indices exist).  Errors as for gesmc_run, d_out untouched.
  * Graphs of 4096 edges and more run in windows of up to 2^19 switches over the
- * whole device, smaller ones on one workgroup in supersteps of about sqrt(m)
- * switches (Sec. 3).
+ * whole device; smaller ones, and fewer than min(10 sqrt(m), 2048) switches (3072
+ * from 2^18 edges on) at a time, on one workgroup in supersteps of about sqrt(m)
+ * switches (Sec. 3).  The context keeps 130 to 160 bytes per switch of a window
+ * and 4 per edge for calls with windows, beside the edge set.
  */
 typedef struct gesmc_es_stats {
     uint64_t attempts, legal, rej_loop, rej_exists;

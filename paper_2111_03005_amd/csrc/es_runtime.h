@@ -33,8 +33,19 @@ uint32_t es_window(uint32_t m) {
     return std::min<uint32_t>(m < kEsSmallEdges ? m / 4 : m / 8, kEsWindowMax);
 }
 uint32_t es_passes(uint32_t m) { return m < kEsSmallEdges ? kEsPasses : 10u; }
+// Fewer switches than this (a short call, the rest of an epoch) go to the chain
+// on one workgroup: it takes about 16 / sqrt(m) us a switch, and 0.055 to 0.033
+// from m = 1.7e5 on, where its supersteps reach their 1024 switches and wait for
+// HBM; a window's launches take 90 to 135 us whatever it holds.  Calls cross, in
+// switches: m = 4,096 700 (r = 600: 181 us on the chain, 194 as a window; 1000:
+// 262, 206), 16,384 1,250 (1000: 167, 208; 2000: 299, 202), 110,000 2,100 (2000:
+// 198, 207; 3000: 261, 200), 1.0e6 3,500 (3000: 223, 249; 5000: 300, 241), 6.7e6
+// 3,100 (3000: 547, 556; 5000: 616, 554).
+uint32_t es_chain_below(uint32_t m) {
+    return std::min<uint32_t>((uint32_t)(10.0 * std::sqrt((double)m)), m < 1u << 18 ? 2048u : 3072u);
+}
 
-// The window's arrays in one buffer (about 170 bytes a switch, and a word per edge).
+// The window's arrays in one buffer (130 to 160 bytes a switch, and a word per edge).
 gesmc_status es_ensure_window(gesmc_ctx *c, uint32_t m, uint32_t W, EsWindow *out) {
     uint32_t cells = 1024;
     while (cells < 4 * W) cells <<= 1;
@@ -130,10 +141,10 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     hipStream_t s = (hipStream_t)stream;
     const uint32_t m = (uint32_t)m64;
     GESMC_TRY(es_ensure(c, m));
-    const uint32_t W = (uint32_t)std::min<uint64_t>(es_window(m), r);
-    const uint32_t passes = es_passes(m);
+    const uint32_t W = es_window(m), below = es_chain_below(m), passes = es_passes(m);
+    const bool windows = W > 0 && r >= below;
     EsWindow win{};
-    if (W > 0) GESMC_TRY(es_ensure_window(c, m, es_window(m), &win));
+    if (windows) GESMC_TRY(es_ensure_window(c, m, W, &win));
     const uint64_t T = es_slots(m), epoch = es_epoch(m);
     const uint32_t mask = (uint32_t)(T - 1);
     const uint32_t s0 = (uint32_t)seed, s1 = (uint32_t)(seed >> 32);
@@ -154,18 +165,20 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
             GESMC_TRY(launch(c, s, KID_ES_BUILD, m, k_es_insert_all, dim3(grid_stride_blocks(c, m)), dim3(kBlock),
                              0, (const unsigned long long *)c->es_E, m, c->es_H, mask, c->es_slot, c->err,
                              c->es_ctr));
-            if (ke > kb && W == 0)
-                GESMC_TRY(launch(c, s, KID_ES_CHAIN, ke - kb, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
-                                 c->es_slot, c->es_H, mask, m, s0, s1, kb, ke, k0, d_outcome, c->es_ctr, c->err,
-                                 (const uint32_t *)nullptr));
-            if (ke > kb && W > 0)  // uses of earlier epochs must read as none
+            if (windows && ke - kb >= below)  // uses of earlier epochs must read as none
                 GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                                  win.last, (uint64_t)m));
             uint32_t tag = 1;  // of the window's uses: 2 W a window, below 2 (epoch + W) in an epoch
             // (by offset: a counter near 2^64 must not wrap past the epoch's end)
-            for (uint64_t o = 0; W > 0 && o < ke - kb; tag += 2 * W, o += W) {
-                const uint64_t wb = kb + o;
-                const uint32_t nw = (uint32_t)std::min<uint64_t>(W, ke - wb);
+            for (uint64_t o = 0; o < ke - kb;) {
+                const uint64_t wb = kb + o, rest = ke - wb;
+                if (!windows || rest < below) {
+                    GESMC_TRY(launch(c, s, KID_ES_CHAIN, rest, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
+                                     c->es_slot, c->es_H, mask, m, s0, s1, wb, ke, k0, d_outcome, c->es_ctr, c->err,
+                                     (const uint32_t *)nullptr));
+                    break;
+                }
+                const uint32_t nw = (uint32_t)std::min<uint64_t>(W, rest);
                 const dim3 grid(ceil_div(nw, kBlock)), block(kBlock);
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, nw, k_es_win_draw, grid, block, 0, win, nw, passes, wb, m,
                                  s0, s1, tag));
@@ -178,11 +191,14 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
                     GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_decide, grid, block, 0, win, nw, t,
                                      (const uint32_t *)c->err));
                 }
-                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_commit, grid, block, 0, win, nw, passes, c->es_E, c->es_slot,
-                                 c->es_H, mask, d_outcome ? d_outcome + (wb - k0) : nullptr, c->es_ctr, c->err));
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_commit, grid, block, 0, win, nw, passes, c->es_E,
+                                 c->es_slot, c->es_H, mask, d_outcome ? d_outcome + (wb - k0) : nullptr, c->es_ctr,
+                                 c->err));
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
                                  c->es_slot, c->es_H, mask, m, s0, s1, wb, wb + nw, k0, d_outcome, c->es_ctr, c->err,
                                  (const uint32_t *)(win.ctl + passes)));
+                tag += 2 * W;
+                o += nw;
             }
             ++launches;
             if (ke - k0 >= r) break;

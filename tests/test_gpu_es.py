@@ -150,3 +150,25 @@ def test_es_full_size_powerlaw_n2p20(ctx):
 def test_es_counters_up_to_the_last(ctx, m, r):
     E = np.random.default_rng(m).permutation(graphgen.gnp(900, 0.02, 12))[:m]
     check_es(ctx, E, 900, 21, 2**64 - 1 - r, r, label="last counters", outcomes=True)
+
+
+# the least switches that make a window (10 sqrt(m), at most 2048), as a call of
+# their own and as the rest of an epoch after whole windows (of m // 4)
+@pytest.mark.parametrize("m,below", [(4096, 640), (6000, 774), (30011, 1732), (70001, 2048)])
+def test_es_short_runs_on_one_workgroup(ctx, m, below):
+    n = 60000
+    E = np.random.default_rng(m).permutation(graphgen.gnp(n, 6.0 / n, 5))[:m]
+    assert len(E) == m
+    W, seed = m // 4, 31
+    for whole in (0, 2):
+        for r in (1, below - 1, below, below + 1):
+            st = check_es(ctx, E, n, seed, 9, whole * W + r, label="short", outcomes=True)
+            # as one workgroup cuts them: a new superstep at the first edge index that comes again
+            i, j, _ = oracle.es_draws(seed, 9 + whole * W, r, m)
+            steps, seen = 1, set()
+            for a, b in zip(i.tolist(), j.tolist()):
+                if a in seen or b in seen or len(seen) >= 2048:
+                    steps, seen = steps + 1, set()
+                seen |= {a, b}
+            assert st["supersteps"] == whole + (steps if r < below else 1)
+            assert steps > 1 or r == 1
