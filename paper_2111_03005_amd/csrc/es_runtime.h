@@ -142,9 +142,15 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     const uint32_t m = (uint32_t)m64;
     GESMC_TRY(es_ensure(c, m));
     const uint32_t W = es_window(m), below = es_chain_below(m), passes = es_passes(m);
-    const bool windows = W > 0 && r >= below;
+    bool windows = W > 0 && r >= below;
     EsWindow win{};
-    if (windows) GESMC_TRY(es_ensure_window(c, m, W, &win));
+    if (windows) {
+        const gesmc_status st = es_ensure_window(c, m, W, &win);
+        if (st == GESMC_E_NOMEM)
+            windows = false;  // the chain on one workgroup needs no more than the edge set
+        else
+            GESMC_TRY(st);
+    }
     const uint64_t T = es_slots(m), epoch = es_epoch(m);
     const uint32_t mask = (uint32_t)(T - 1);
     const uint32_t s0 = (uint32_t)seed, s1 = (uint32_t)(seed >> 32);

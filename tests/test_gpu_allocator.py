@@ -108,3 +108,42 @@ def test_allocator_argument_checks():
     srv.close()
     ctx.set_allocator(a.alloc, a.free)
     ctx.close()
+
+
+class Refusing(Counting):
+    """Returns no memory for the k-th allocation alone."""
+
+    def __init__(self, k):
+        super().__init__()
+        self.k, self.asked = k, 0
+
+    def alloc(self, n):
+        self.asked += 1
+        return 0 if self.asked - 1 == self.k else super().alloc(n)
+
+
+def test_es_without_memory_for_windows():
+    """Only the edge list, its slots, the edge set and the counters are needed:
+    without memory for the windows (asked for last) the call runs on one workgroup."""
+    gesmc = _gpu()
+    n, m, r = 60000, 20000, 12000
+    E = np.random.default_rng(1).permutation(graphgen.gnp(n, 6.0 / n, 5))[:m]
+    rc, want, cnt, _ = oracle.es_run(E, n, 3, 0, r)
+    assert rc == 0
+    for k in range(5):
+        print("case allocation %d refused" % k, flush=True)
+        a = Refusing(k)
+        ctx = gesmc.Context(0)
+        ctx.set_allocator(a.alloc, a.free)
+        out = torch.full((m,), -1, dtype=torch.int64, device="cuda")
+        if k < 4:
+            with pytest.raises(gesmc.GesmcError) as ei:
+                ctx.run_es(to_dev(E), n, 3, r=r, out=out)
+            assert ei.value.status == gesmc.E_NOMEM and (out == -1).all()
+        for _ in range(1 if k == 4 else 2):  # (a failed call's context works, with windows or without)
+            _, st = ctx.run_es(to_dev(E), n, 3, r=r, out=out)
+            assert np.array_equal(out.cpu().numpy().view(np.uint64), want)
+            assert all(st[q] == cnt[q] for q in ("attempts", "legal", "rej_loop", "rej_exists"))
+        assert a.asked > 4
+        ctx.close()
+        assert a.live == {}
