@@ -393,7 +393,8 @@ gesmc_status gesmc_server_info_get(gesmc_server *srv, gesmc_server_info *out);
 typedef struct gesmc_es_stats {
     uint64_t attempts, legal, rej_loop, rej_exists;
     uint64_t supersteps;  /* ParES supersteps: windows, or on one workgroup runs of switches
-                             without a shared edge index, at most 1024 switches each           */
+                             without a shared edge index, at most 1024 switches each (there
+                             also for a window that its passes did not settle)                 */
     uint64_t rounds_sum;  /* decision rounds (a window: passes) over all supersteps            */
     uint32_t rounds_max;  /* most rounds in one superstep                                     */
     uint32_t epochs;      /* times the edge set was built                                     */

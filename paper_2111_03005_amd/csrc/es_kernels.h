@@ -43,6 +43,7 @@ constexpr uint32_t kEsCells = 2048;              // LDS cells of the tuples
 constexpr uint32_t kEsNone = 0xFFFFFFFFu;
 constexpr unsigned long long kEsEmpty = ~0ull;   // never a valid (min, max) key
 constexpr unsigned long long kEsTomb = ~0ull - 1;
+constexpr uint32_t kEsGateMax = 16;              // windows left to the chain after one that did not settle
 
 // Counters of one launch (device, cleared by the host's zero kernel).
 struct EsCounters {
@@ -244,14 +245,16 @@ struct EsTuples {
 // Switches k = kbeg .. kend - 1 of one graph (one workgroup, kEsThreads
 // threads).  E, slot_of and H are the graph's edge list, slots and edge set
 // (mask = slot count - 1).  outcome (nullable) receives the outcome code of
-// switch k at outcome[k - kbase].  unsettled (nullable): run only if it is set.
+// switch k at outcome[k - kbase].  unsettled (nullable): run only if it is set;
+// gate (with it) then says for how many windows more (k_es_win_draw).
 __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__restrict__ E,
                                                          uint32_t *__restrict__ slot_of,
                                                          unsigned long long *__restrict__ H, uint32_t mask,
                                                          uint32_t m, uint32_t s0, uint32_t s1, uint64_t kbeg,
                                                          uint64_t kend, uint64_t kbase, uint8_t *__restrict__ outcome,
                                                          EsCounters *__restrict__ ctr, uint32_t *__restrict__ err,
-                                                         const uint32_t *__restrict__ unsettled) {
+                                                         const uint32_t *__restrict__ unsettled,
+                                                         uint32_t *__restrict__ gate) {
     if (unsettled && *unsettled == 0) return;  // a window that k_es_win_commit wrote back
     __shared__ union {
         EsShared a;
@@ -463,6 +466,10 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
         atomicAdd(&ctr->rounds, (unsigned long long)c_rounds);
         atomicMax(&ctr->rounds_max, (unsigned long long)c_rmax);
         atomicAdd(&ctr->used_slots, (unsigned long long)c_fresh);
+        if (unsettled) {
+            if (gate[0] == 0) gate[0] = gate[1] = gate[1] ? min(2 * gate[1], kEsGateMax) : 1u;
+            else --gate[0];
+        }
     }
 }
 
@@ -481,14 +488,19 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
 // as the longest chain of switches that depend on each other's indices.
 // Kernels of a window: draws, links, 10 or 16 passes of two kernels (the ones
 // after the fixpoint return at once), commit.  A window without a fixpoint by
-// then is left to k_es_chain, which starts from the same state.
+// then, or with a key that so many switches erase or insert that the walks of
+// its event list would outlast the chain, is left to k_es_chain, which starts
+// from the same state; the windows after it are then left to it too, 1, 2, 4 ..
+// 16 of them before the next try.  (Dense graphs and power laws down to gamma
+// = 2.01 settle in 7 to 10 passes.  Two stars of 100,000 edges, whose windows
+// of 50,000 switches propose the edge between the centres 12,500 times, took 502
+// ns a switch when each window ran its passes to the end, 83 on one workgroup.)
 // A kernel may read a status or source that another workgroup changes while it
 // runs; the change is counted, so the last pass ran on settled data.
 // m = 6.67e6, r = m / 2: 112 ms on one workgroup, 4.0 in windows of 2^19
 // (random reads and atomics on edges, edge set and event lists).
 constexpr uint32_t kEsUse = 0x7FFFFFFFu;       // pred: no earlier use of the index
 constexpr uint32_t kEsLastUse = 0x80000000u;   // pred flag: no later use in the window
-constexpr uint32_t kEsWalk = 4096;
 constexpr uint32_t kEsPasses = 16;             // of a window at most
 constexpr uint32_t kEsCtrCopies = 32;          // spread counters of the commits
 
@@ -504,8 +516,11 @@ struct EsWindow {
     uint32_t *ctl;           // [0] pool nodes taken, [1 + t] pass t changed something
     uint32_t *touched;       // per pass a bit per cell: an event of the cell changed since the pass before
     uint32_t *last;          // per edge index: tag + its newest use linked so far
+    uint32_t *gate;          // of the call: [0] windows left out from here on, [1] how many the last time
     uint32_t cap;            // switches per window at most
     uint32_t cmask;          // cells - 1
+    uint32_t passes;         // at most; ctl[passes] set: left to k_es_chain
+    uint32_t walk;           // nodes of an event list at most
 };
 constexpr uint32_t kEsCtl = kEsPasses + 1;
 
@@ -581,12 +596,14 @@ __device__ __forceinline__ bool es_set_sources(const EsWindow &w, uint32_t q, un
 
 // Draws of switches k0 .. k0 + n - 1 and the per-index lists of their uses;
 // clears the window's event lists and control words.
-__global__ __launch_bounds__(kBlock) void k_es_win_draw(EsWindow w, uint32_t n, uint32_t passes, uint64_t k0,
-                                                        uint32_t m, uint32_t s0, uint32_t s1, uint32_t tag) {
+__global__ __launch_bounds__(kBlock) void k_es_win_draw(EsWindow w, uint32_t n, uint64_t k0, uint32_t m, uint32_t s0,
+                                                        uint32_t s1, uint32_t tag) {
     const uint32_t tid = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
+    const bool out = w.gate[0] != 0;
+    for (uint32_t c = tid; c < kEsCtl; c += stride) w.ctl[c] = out && c == w.passes ? 1u : 0u;
+    if (out) return;
     for (uint32_t c = tid; c <= w.cmask; c += stride) w.cell[c] = 0;
-    for (uint32_t c = tid; c < (passes - 1) * ((w.cmask + 1) / 32); c += stride) w.touched[c] = 0;
-    for (uint32_t c = tid; c < kEsCtl; c += stride) w.ctl[c] = 0;
+    for (uint32_t c = tid; c < (w.passes - 1) * ((w.cmask + 1) / 32); c += stride) w.touched[c] = 0;
     for (uint32_t q = tid; q < n; q += stride) {
         const EsDraw d = es_draw(k0 + q, m, s0, s1);
         w.ij[q] = make_uint2(d.i | (d.g ? 0x80000000u : 0u), d.j);
@@ -600,7 +617,7 @@ __global__ __launch_bounds__(kBlock) void k_es_win_link(EsWindow w, uint32_t n, 
                                                         const unsigned long long *__restrict__ E,
                                                         const unsigned long long *__restrict__ H, uint32_t mask,
                                                         uint32_t *__restrict__ err) {
-    if (*err) return;
+    if (*err || w.ctl[w.passes] != 0) return;
     const uint32_t stride = gridDim.x * kBlock;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
         const uint2 ij = w.ij[q];
@@ -637,7 +654,7 @@ __device__ __forceinline__ uint32_t es_present(const EsWindow &w, uint32_t q, un
     uint32_t best = 0, res = pres;  // 1 + the latest accepted earlier event's switch
     uint32_t x = w.cell[es_cell(w, key)];
     for (uint32_t c = 0; x != 0; ++c) {
-        if (c == kEsWalk) return 2;
+        if (c == w.walk) return 2;
         const uint32_t node = x - 1;
         x = w.link[node];
         const uint32_t ev = node < 4 * w.cap ? node : w.pool[node - 4 * w.cap];
@@ -657,7 +674,9 @@ __device__ __forceinline__ uint32_t es_present(const EsWindow &w, uint32_t q, un
 __global__ __launch_bounds__(kBlock) void k_es_win_sources(EsWindow w, uint32_t n, uint32_t t,
                                                            const unsigned long long *__restrict__ H, uint32_t mask,
                                                            uint32_t *__restrict__ err) {
-    if (*err || (t > 0 && w.ctl[t] == 0)) return;  // ctl[1 + t - 1]: the pass before changed nothing
+    // ctl[1 + t - 1]: the pass before changed nothing (t < passes, so ctl[passes]
+    // is set here by a window given up, or by this last pass's own changes)
+    if (*err || (t > 0 && w.ctl[t] == 0) || w.ctl[w.passes] != 0) return;
     const uint32_t stride = gridDim.x * kBlock;
     bool changed = false;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
@@ -685,7 +704,7 @@ __global__ __launch_bounds__(kBlock) void k_es_win_sources(EsWindow w, uint32_t 
 // Pass t, second half: the status of every switch whose sources are known.
 __global__ __launch_bounds__(kBlock) void k_es_win_decide(EsWindow w, uint32_t n, uint32_t t,
                                                           const uint32_t *__restrict__ err) {
-    if (*err || (t > 0 && w.ctl[t] == 0)) return;
+    if (*err || (t > 0 && w.ctl[t] == 0) || w.ctl[w.passes] != 0) return;
     const uint32_t stride = gridDim.x * kBlock;
     bool changed = false;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
@@ -695,10 +714,9 @@ __global__ __launch_bounds__(kBlock) void k_es_win_decide(EsWindow w, uint32_t n
         if (!es_touched(w, t, A) && !es_touched(w, t, B)) continue;
         const uint32_t a = es_present(w, q, A, w.pres[2 * q]);
         const uint32_t b = a == 1 ? 0u : es_present(w, q, B, w.pres[2 * q + 1]);
-        if (a == 2 || b == 2) {  // judged again, so the window does not settle
-            changed = true;
-            es_touch(w, t + 1, A);
-            es_touch(w, t + 1, B);
+        if (a == 2 || b == 2) {  // given up
+            w.ctl[w.passes] = 1;
+            break;
         }
         const uint8_t now = a == 1 || b == 1 ? ST_EXISTS : ST_LEGAL;
         if (now != sq) {
@@ -716,12 +734,11 @@ __global__ __launch_bounds__(kBlock) void k_es_win_decide(EsWindow w, uint32_t n
 // The outcomes of a window whose last pass changed nothing: counts, codes, and for each index its last
 // use's value; a changed edge leaves its old slot (a tombstone) and takes the
 // first free one of its chain.
-__global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n, uint32_t passes,
-                                                          unsigned long long *__restrict__ E,
+__global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n, unsigned long long *__restrict__ E,
                                                           uint32_t *__restrict__ slot_of, unsigned long long *H,
                                                           uint32_t mask, uint8_t *__restrict__ outcome,
                                                           EsCounters *__restrict__ ctr, uint32_t *__restrict__ err) {
-    if (*err || w.ctl[passes] != 0) return;
+    if (*err || w.ctl[w.passes] != 0) return;
     __shared__ uint32_t c[4];
     if (threadIdx.x < 4) c[threadIdx.x] = 0;
     __syncthreads();
@@ -773,7 +790,8 @@ __global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n
         if (c[3]) atomicAdd(&o->used_slots, (unsigned long long)c[3]);
         if (blockIdx.x == 0) {
             uint32_t rounds = 1;
-            while (rounds < passes && w.ctl[rounds]) ++rounds;
+            while (rounds < w.passes && w.ctl[rounds]) ++rounds;
+            w.gate[1] >>= 1;
             atomicAdd(&o->supersteps, 1ull);
             atomicAdd(&o->rounds, (unsigned long long)rounds);
             atomicMax(&o->rounds_max, (unsigned long long)rounds);

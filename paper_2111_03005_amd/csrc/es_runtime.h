@@ -33,6 +33,15 @@ uint32_t es_window(uint32_t m) {
     return std::min<uint32_t>(m < kEsSmallEdges ? m / 4 : m / 8, kEsWindowMax);
 }
 uint32_t es_passes(uint32_t m) { return m < kEsSmallEdges ? kEsPasses : 10u; }
+// Nodes of an event list that a judgement walks before its window is given up.
+// A walk is a chain of reads of 0.17 to 0.28 us a node and is repeated in seven
+// passes or more, while the window (m / 4 switches) takes 4 sqrt(m) us on the
+// chain: the two meet at about 2 sqrt(m) nodes.  Two stars of m / 2 edges each,
+// lists of m / 16, us per m / 2 switches on the chain, with lists of any length
+// below 4096, with this line: m = 8,192 870, 1542, 1041; 65,536 3429, 40116, 3803.
+// Power laws down to gamma = 2.01 stay below it but for one window in 16 at n =
+// 20,000.
+uint32_t es_walk(uint32_t m) { return std::min<uint32_t>((uint32_t)(2.0 * std::sqrt((double)m)), 4096u); }
 // Fewer switches than this (a short call, the rest of an epoch) go to the chain
 // on one workgroup: it takes about 16 / sqrt(m) us a switch, and 0.055 to 0.033
 // from m = 1.7e5 on, where its supersteps reach their 1024 switches and wait for
@@ -51,7 +60,7 @@ gesmc_status es_ensure_window(gesmc_ctx *c, uint32_t m, uint32_t W, EsWindow *ou
     while (cells < 4 * W) cells <<= 1;
     const uint64_t w = W;
     const uint64_t sizes[] = {w * 8,  w * 8,  w * 8,           w * 16, w * 16,     w * 2,
-                              w,      cells * 4ull, w * 32, w * 16, kEsCtl * 4ull, cells / 8 * (kEsPasses - 1ull), m * 4ull};
+                              w,      cells * 4ull, w * 32, w * 16, kEsCtl * 4ull, cells / 8 * (kEsPasses - 1ull), 8ull, m * 4ull};
     uint64_t total = 0;
     for (uint64_t b : sizes) total += (b + 255) & ~255ull;
     if (total > c->es_cap_w) {
@@ -80,9 +89,12 @@ gesmc_status es_ensure_window(gesmc_ctx *c, uint32_t m, uint32_t W, EsWindow *ou
     out->pool = (uint32_t *)take();
     out->ctl = (uint32_t *)take();
     out->touched = (uint32_t *)take();
+    out->gate = (uint32_t *)take();
     out->last = (uint32_t *)take();
     out->cap = W;
     out->cmask = cells - 1;
+    out->passes = es_passes(m);
+    out->walk = es_walk(m);
     return GESMC_OK;
 }
 
@@ -141,7 +153,7 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     hipStream_t s = (hipStream_t)stream;
     const uint32_t m = (uint32_t)m64;
     GESMC_TRY(es_ensure(c, m));
-    const uint32_t W = es_window(m), below = es_chain_below(m), passes = es_passes(m);
+    const uint32_t W = es_window(m), below = es_chain_below(m);
     bool windows = W > 0 && r >= below;
     EsWindow win{};
     if (windows) {
@@ -162,6 +174,7 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
         GESMC_TRY(launch(c, s, KID_LOAD, m, k_load, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                          (const unsigned long long *)d_in, m, n, c->es_slot, c->es_E, c->err, 0u));
     uint64_t launches = 0;
+    if (windows) GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(1), dim3(64), 0, win.gate, (uint64_t)2));
     if (m >= 2) {
         for (uint64_t kb = k0; kb == k0 || kb - k0 < r; kb += epoch) {
             const uint64_t ke = kb + std::min<uint64_t>(epoch, r - (kb - k0));
@@ -181,28 +194,28 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
                 if (!windows || rest < below) {
                     GESMC_TRY(launch(c, s, KID_ES_CHAIN, rest, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
                                      c->es_slot, c->es_H, mask, m, s0, s1, wb, ke, k0, d_outcome, c->es_ctr, c->err,
-                                     (const uint32_t *)nullptr));
+                                     (const uint32_t *)nullptr, (uint32_t *)nullptr));
                     break;
                 }
                 const uint32_t nw = (uint32_t)std::min<uint64_t>(W, rest);
                 const dim3 grid(ceil_div(nw, kBlock)), block(kBlock);
-                GESMC_TRY(launch(c, s, KID_ES_CHAIN, nw, k_es_win_draw, grid, block, 0, win, nw, passes, wb, m,
-                                 s0, s1, tag));
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, nw, k_es_win_draw, grid, block, 0, win, nw, wb, m, s0, s1,
+                                 tag));
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_link, grid, block, 0, win, nw, tag,
                                  (const unsigned long long *)c->es_E, (const unsigned long long *)c->es_H, mask,
                                  c->err));
-                for (uint32_t t = 0; t < passes; ++t) {
+                for (uint32_t t = 0; t < win.passes; ++t) {
                     GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_sources, grid, block, 0, win, nw, t,
                                      (const unsigned long long *)c->es_H, mask, c->err));
                     GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_decide, grid, block, 0, win, nw, t,
                                      (const uint32_t *)c->err));
                 }
-                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_commit, grid, block, 0, win, nw, passes, c->es_E,
+                GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_win_commit, grid, block, 0, win, nw, c->es_E,
                                  c->es_slot, c->es_H, mask, d_outcome ? d_outcome + (wb - k0) : nullptr, c->es_ctr,
                                  c->err));
                 GESMC_TRY(launch(c, s, KID_ES_CHAIN, 0, k_es_chain, dim3(1), dim3(kEsThreads), 0, c->es_E,
                                  c->es_slot, c->es_H, mask, m, s0, s1, wb, wb + nw, k0, d_outcome, c->es_ctr, c->err,
-                                 (const uint32_t *)(win.ctl + passes)));
+                                 (const uint32_t *)(win.ctl + win.passes), win.gate));
                 tag += 2 * W;
                 o += nw;
             }

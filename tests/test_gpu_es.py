@@ -152,6 +152,18 @@ def test_es_counters_up_to_the_last(ctx, m, r):
     check_es(ctx, E, 900, 21, 2**64 - 1 - r, r, label="last counters", outcomes=True)
 
 
+def chain_supersteps(seed, k0, r, m):
+    """Supersteps in which one workgroup runs r switches: a new one at the first
+    edge index that comes again, and after 1024 switches."""
+    i, j, _ = oracle.es_draws(seed, k0, r, m)
+    steps, seen = min(r, 1), set()
+    for a, b in zip(i.tolist(), j.tolist()):
+        if a in seen or b in seen or len(seen) >= 2048:
+            steps, seen = steps + 1, set()
+        seen |= {a, b}
+    return steps
+
+
 # the least switches that make a window (10 sqrt(m), at most 2048), as a call of
 # their own and as the rest of an epoch after whole windows (of m // 4)
 @pytest.mark.parametrize("m,below", [(4096, 640), (6000, 774), (30011, 1732), (70001, 2048)])
@@ -163,12 +175,46 @@ def test_es_short_runs_on_one_workgroup(ctx, m, below):
     for whole in (0, 2):
         for r in (1, below - 1, below, below + 1):
             st = check_es(ctx, E, n, seed, 9, whole * W + r, label="short", outcomes=True)
-            # as one workgroup cuts them: a new superstep at the first edge index that comes again
-            i, j, _ = oracle.es_draws(seed, 9 + whole * W, r, m)
-            steps, seen = 1, set()
-            for a, b in zip(i.tolist(), j.tolist()):
-                if a in seen or b in seen or len(seen) >= 2048:
-                    steps, seen = steps + 1, set()
-                seen |= {a, b}
+            steps = chain_supersteps(seed, 9 + whole * W, r, m)
             assert st["supersteps"] == whole + (steps if r < below else 1)
             assert steps > 1 or r == 1
+
+
+def two_stars(m, share):
+    """Two stars of share * m edges in all and disjoint edges, shuffled: in a
+    window of W switches the edge between the centres is proposed some
+    W share^2 / 4 times."""
+    h = int(m * share / 2)
+    ids = np.arange(2, 2 + 2 * m, dtype=np.uint64)
+    E = np.concatenate([ids[:h], (np.uint64(1) << np.uint64(32)) | ids[h:2 * h],
+                        (ids[2 * h::2] << np.uint64(32)) | ids[2 * h + 1::2]])[:m]
+    return np.random.default_rng(m).permutation(E)
+
+
+def check_two_stars(ctx, m, share, nwin):
+    W, seed, k0 = m // 4, 7, 100
+    st = check_es(ctx, two_stars(m, share), 2 * m + 2, seed, k0, nwin * W, label="two stars, share %g" % share,
+                  outcomes=True)
+    alone = sum(chain_supersteps(seed, k0 + q * W, W, m) for q in range(nwin))
+    print("windows %d, supersteps %d, all on one workgroup %d" % (nwin, st["supersteps"], alone), flush=True)
+    return st["supersteps"], alone
+
+
+@pytest.mark.parametrize("m,nwin", [(8192, 24), (65536, 9)])
+def test_es_windows_given_up(ctx, m, nwin):
+    steps, alone = check_two_stars(ctx, m, 1.0, nwin)
+    assert steps == alone  # no window settles
+    steps, _ = check_two_stars(ctx, m, 0.1, nwin)
+    assert steps == nwin   # every window does
+
+
+def test_es_windows_settled_and_not_in_one_epoch(ctx):
+    """Shares in steps of 1.5 %: the proposals of a window (164 to 520, the line
+    between 2 sqrt(m) = 512 and less, as an event may be listed twice) spread by
+    4 to 8 %, so there are shares at which some windows are given up."""
+    mixed = 0
+    for q in range(39):
+        steps, alone = check_two_stars(ctx, 65536, 0.2 * 1.015 ** q, 12)
+        assert 12 <= steps <= alone
+        mixed += 12 < steps < alone
+    assert mixed > 0
