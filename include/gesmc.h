@@ -533,8 +533,10 @@ uint32_t gesmc_tune_cache_size(void);
 #define GESMC_OPT_PROFILE_ONLY 7 /* kernel id whose launches are timed while profiling; -1 = every
                                     kernel (default).  Events between launches cost time, so timing
                                     one kernel disturbs the rest least                              */
-#define GESMC_OPT_ROUND_LIMIT 13  /* decision rounds a superstep may take (Alg. 1's loop, counted as in
-                                     gesmc_step_stats.rounds) before the call fails with GESMC_E_ROUNDS
+#define GESMC_OPT_ROUND_LIMIT 13  /* decision rounds a superstep may take (Alg. 1's loop: one for every
+                                     sweep over the undecided switches, however many passes of the
+                                     finishing workgroup gesmc_step_stats.rounds counts it as, so never
+                                     more than that) before the call fails with GESMC_E_ROUNDS
                                      and d_out untouched; 0 = no limit (default).  A debugging cap for
                                      the multi-kernel supersteps of GESMC_OPT_STRATEGY 0 (plain and
                                      batched); the LDS small-graph kernels do not count against it,

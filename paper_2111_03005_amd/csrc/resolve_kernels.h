@@ -1115,8 +1115,10 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
 
 // Remaining rounds in one workgroup; the next round's list counter is cleared
 // by the round that fills it.  Every pass of the workgroup over kChainFinish
-// switches of the list counts as a round (a later pass of the same sweep over
-// the list already sees what the earlier ones decided).  After kSweepAfter rounds with switches still
+// switches of the list counts as a round in ctr (a later pass of the same sweep over
+// the list already sees what the earlier ones decided); round_limit is charged
+// one for a whole sweep, as for a round of the whole chip, so that what it allows
+// does not depend on the workgroup's width.  After kSweepAfter rounds with switches still
 // undecided (long dependency chains: hub edges that many switches erase and
 // insert), the rest is decided by a sweep in ascending switch id: a switch
 // depends on smaller ids only, so chunks of kSweepChunk ids are taken in
@@ -1146,14 +1148,15 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
     __shared__ BlockCounts bc;
     __shared__ uint32_t s_n;
     const uint32_t tid = threadIdx.x;
+    unsigned long long charged = 0;  // rounds that count against round_limit (thread 0)
     if (tid == 0) {
         bc = BlockCounts{0, 0, 0, 0};
         s_n = min(*count_a, ell);
         if (nbslot) ctr->undecided_round1 = s_n;
         // a caller's round budget (0: none), counted over the superstep's rounds so
         // far (the multi-workgroup rounds before this kernel included)
-        const unsigned long long so_far = round_limit ? atomicAdd(&ctr->rounds, 0ull) : 0ull;
-        if (round_limit && (so_far > round_limit || (so_far == round_limit && s_n > 0))) {
+        charged = round_limit ? atomicAdd(&ctr->rounds, 0ull) : 0ull;
+        if (round_limit && (charged > round_limit || (charged == round_limit && s_n > 0))) {
             atomicOr(err, ERR_ROUNDS);
             s_n = 0;
         }
@@ -1224,8 +1227,8 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                 const uint32_t nn = l_n;
                 if (nn >= n) atomicOr(err, ERR_INTERNAL);  // the smallest undecided switch always decides
                 s_n = nn >= n ? 0 : nn;
-                const unsigned long long done = atomicAdd(&ctr->rounds, (unsigned long long)trips) + trips;
-                if (round_limit && s_n > 0 && done >= round_limit) {
+                atomicAdd(&ctr->rounds, (unsigned long long)trips);
+                if (round_limit && ++charged >= round_limit && s_n > 0) {
                     atomicOr(err, ERR_ROUNDS);
                     s_n = 0;
                 }
@@ -1272,8 +1275,8 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
             const uint32_t nn = min(*cnxt, ell);
             if (nn >= n) atomicOr(err, ERR_INTERNAL);  // the smallest undecided switch always decides
             s_n = nn >= n ? 0 : nn;
-            const unsigned long long done = atomicAdd(&ctr->rounds, (unsigned long long)trips) + trips;
-            if (round_limit && s_n > 0 && done >= round_limit) {
+            atomicAdd(&ctr->rounds, (unsigned long long)trips);
+            if (round_limit && ++charged >= round_limit && s_n > 0) {
                 atomicOr(err, ERR_ROUNDS);
                 s_n = 0;
             }
@@ -1289,13 +1292,9 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
     }
     if (n > 0) {
         __shared__ uint32_t s_wait, s_done, s_stop;
-        __shared__ unsigned long long s_rounds;
         const uint32_t nwords = ((ell + kSweepChunk - 1) / kSweepChunk + 31) / 32;
         for (uint32_t w = tid; w < nwords; w += kChainFinish) s_chunks[w] = 0;
-        if (tid == 0) {
-            s_rounds = atomicAdd(&ctr->rounds, 0ull);
-            s_stop = 0;
-        }
+        if (tid == 0) s_stop = 0;
         __syncthreads();
         for (uint32_t q = tid; q < n; q += kChainFinish) {
             const uint32_t k = cur[q];
@@ -1343,7 +1342,7 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                         if (W > 0 && D == 0) {
                             atomicOr(err, ERR_INTERNAL);
                             s_stop = 1;
-                        } else if (W > 0 && round_limit && s_rounds + added >= round_limit) {
+                        } else if (W > 0 && round_limit && charged + added >= round_limit) {
                             atomicOr(err, ERR_ROUNDS);
                             s_stop = 1;
                         }

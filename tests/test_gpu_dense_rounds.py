@@ -41,3 +41,73 @@ def test_dense_rounds_exact(n, p, fast, pack, pl):
                 assert all(s[k] == want[k] for k in ("attempts", "legal", "rej_loop", "rej_exists", "rej_pl"))
     finally:
         c.close()
+
+
+def alg1_rounds(E, n, seed, t):
+    """The round of Alg. 1 in which each switch of superstep t is decided, if
+    every round sees only what the rounds before it decided."""
+    ell = len(E) // 2
+    pi = np.asarray(oracle.permutation(len(E), seed, t)).astype(np.int64).tolist()
+    rc, _, _, codes = oracle.run(E, n, seed, t, 1, 0, outcomes=True)
+    assert rc == 0
+    codes = np.asarray(codes).reshape(-1).tolist()
+    uv = [(int(e) >> 32, int(e) & 0xFFFFFFFF) for e in E]
+    eraser = {uv[i]: p // 2 if p < 2 * ell else ell for p, i in enumerate(pi)}
+    inserters, rounds = {}, [0] * ell
+    for k in range(ell):
+        i, j = pi[2 * k], pi[2 * k + 1]
+        (u, v), (x, y) = uv[i], uv[j]
+        targets = ((u, y), (v, x)) if i < j else ((u, x), (v, y))
+        if codes[k] == 2:
+            continue
+        present, known = [], [0]  # rounds that show a target present; rounds of all it depends on
+        for a, b in targets:
+            key = (min(a, b), max(a, b))
+            e = eraser.get(key)
+            if e is not None and (e >= k or codes[e] == 2):
+                present.append(0)
+            elif e is not None:
+                known.append(rounds[e])
+                if codes[e] != 1:
+                    present.append(rounds[e])
+            for q in inserters.get(key, ()):
+                if e is None or q > e:
+                    known.append(rounds[q])
+                    if codes[q] == 1:
+                        present.append(rounds[q])
+            inserters.setdefault(key, []).append(k)
+        assert (codes[k] == 1) == (not present)
+        rounds[k] = 1 + (max(known) if codes[k] == 1 else min(present))
+    return rounds
+
+
+# undecided after round 1: about 1500 (the finisher's list in LDS) and 4200
+# (from memory), three and nine passes of its workgroup
+@pytest.mark.parametrize("n", [600, 1000])
+def test_round_limit_counts_sweeps(n):
+    """A limit of as many rounds as Alg. 1 needs is met, whatever number of
+    passes the finishing workgroup takes for a round."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2111_03005_amd as gesmc
+    E = graphgen.gnp(n, 0.1, 31)
+    need = max(alg1_rounds(E, n, 5, 0))
+    assert 2 <= need <= 8  # (later sweeps are cut into chunks of switches)
+    c = gesmc.Context(0)
+    try:
+        c.set_option(gesmc.OPT_FAST_ROUNDS, 0)
+        rc, exp, _, _ = oracle.run(E, n, 5, 0, 1, 0)
+        out, _, steps = c.run(to_dev(E), n, 5, r=1, steps=True)
+        print("needs %d rounds, %d undecided, %d passes" % (need, steps[0]["undecided_after_round1"],
+                                                            steps[0]["rounds"]), flush=True)
+        assert steps[0]["rounds"] > need
+        c.set_option(gesmc.OPT_ROUND_LIMIT, need)
+        out, _, _ = c.run(to_dev(E), n, 5, r=1, steps=True)
+        assert np.array_equal(out.cpu().numpy().view(np.uint64), exp)
+        c.set_option(gesmc.OPT_ROUND_LIMIT, 1)
+        sentinel = torch.full((len(E),), 7, dtype=torch.int64, device="cuda")
+        with pytest.raises(gesmc.GesmcError) as ei:
+            c.run(to_dev(E), n, 5, r=1, steps=True, out=sentinel)
+        assert ei.value.status == gesmc.E_ROUNDS and bool((sentinel == 7).all())
+    finally:
+        c.close()
