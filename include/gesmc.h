@@ -498,9 +498,9 @@ uint32_t gesmc_tune_cache_size(void);
 #define GESMC_OPT_BUCKET_AVG 1  /* largest mean records per sort bucket (64 .. 1152, default 1152)  */
 #define GESMC_OPT_SORT_CAP 2    /* records sorted in LDS per bucket (64 .. 1536, default 1536)     */
 #define GESMC_OPT_FAST_ROUNDS 3 /* multi-workgroup rounds before the 1-workgroup finisher (0 .. 64);
-                                   unset: 6 after a plain call on this context whose first round
-                                   left more than 4096 switches of a superstep undecided (hub
-                                   edges), else 2, or 0 below 2^16 switches a superstep            */
+                                   unset: 2, or 0 below 2^16 switches a superstep; a plain call
+                                   after one on this context whose first round left more than
+                                   4096 switches of a superstep undecided (hub edges): 6          */
 #define GESMC_OPT_PROFILE 4     /* 1: time every kernel launch with HIP events                      */
 #define GESMC_OPT_STRATEGY 5    /* dependency resolution: 0 = tuples sorted by edge key per hash
                                    partition in LDS (default); 1 = one open-addressing table in HBM

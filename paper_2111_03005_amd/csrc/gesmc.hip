@@ -1086,7 +1086,8 @@ gesmc_status decide_and_scatter(gesmc_ctx *c, hipStream_t s, const Plan &q, uint
 // Multi-workgroup list rounds before the finisher while
 // GESMC_OPT_FAST_ROUNDS is unset: kRoundsHubs after a plain call whose first
 // round left more than kRoundsHubsAbove switches of a superstep undecided
-// (adapt_rounds), else none below kRoundsFromSwitches switches (the few that
+// (adapt_rounds; not in a batch, whose graphs say nothing of each other and
+// whose captured schedule must not change with other calls), else none below kRoundsFromSwitches switches (the few that
 // are left cost the finisher less than an empty launch of 3 us: 41 at m =
 // 1.1e5) and kRoundsPlain from there on.  Hub graphs need 6 to 9 rounds
 // whatever their size, and a pass of the finisher takes kChainFinish switches:
@@ -1096,9 +1097,9 @@ gesmc_status decide_and_scatter(gesmc_ctx *c, hipStream_t s, const Plan &q, uint
 constexpr uint64_t kRoundsHubsAbove = 8 * kChainFinish;
 constexpr int kRoundsPlain = 2, kRoundsHubs = 6;
 constexpr uint32_t kRoundsFromSwitches = 1u << 16;
-int decision_rounds(const gesmc_ctx *c, uint32_t ell) {
+int decision_rounds(const gesmc_ctx *c, uint32_t ell, bool batch) {
     if (!c->fast_rounds_auto) return c->fast_rounds;
-    if (c->adapt_rounds > kRoundsPlain) return c->adapt_rounds;
+    if (!batch && c->adapt_rounds > kRoundsPlain) return c->adapt_rounds;
     return ell < kRoundsFromSwitches ? 0 : kRoundsPlain;
 }
 
@@ -1199,7 +1200,7 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
     }
     const uint32_t rblocks = std::max<uint32_t>(1, std::min<uint32_t>(ceil_div(p.ell, kBlock), c->num_cus * 4));
     int j = 0;
-    const int fast = decision_rounds(c, p.ell);
+    const int fast = decision_rounds(c, p.ell, bs != nullptr);
     for (; j < fast; ++j) {
         GESMC_TRY(launch(c, s, KID_DECIDE_CHAIN, 0, k_decide_chain, dim3(rblocks), dim3(kBlock), 0, si, sk, p.ell,
                          c->info, c->st, c->idx[0], c->key[0], (const uint32_t *)c->ulist[j % 2],
@@ -2184,6 +2185,8 @@ gesmc_status run_batch_impl(gesmc_ctx *c, void *stream, uint32_t G, const uint64
         mix(c->bucket_avg);
         mix(c->sort_cap);
         mix((uint64_t)c->fast_rounds);
+        mix(c->fast_rounds_auto);
+        mix(c->round_limit);
         mix(c->level1_cap);
         mix(c->fuse_emit);
         mix(c->small_graphs);

@@ -378,3 +378,48 @@ def test_small_graph_path_exact(pl):
         assert all(res[0][1][g][k] == res[1][1][g][k] for k in outcome), g
     for k in outcome[:5]:
         assert res[0][2][k] == res[1][2][k], k
+
+
+@pytest.mark.parametrize("option,value", [("OPT_FAST_ROUNDS", 2), ("OPT_ROUND_LIMIT", 50)])
+def test_batch_graph_follows_the_round_options(option, value):
+    """Setting a rounds option after a capture, also to the value that it had
+    unset, ends the captured schedule: the next call runs eagerly, and a limit of
+    one round fails a replay's shape.  A plain call on the context does not."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2111_03005_amd as gesmc
+    E, n = graphgen.gnp(600, 0.1, 31), 600
+    hubs, nh = graphgen.powerlaw_graph(20000, 2.01, 1, 19000, 3), 20000
+    c = gesmc.Context(0)
+    stream = torch.cuda.Stream()
+    try:
+        c.set_option(gesmc.OPT_GRAPH, 1)
+        c.set_option(gesmc.OPT_PROFILE, 1)
+        d_in = to_dev(E)
+        out = torch.empty_like(d_in)
+
+        def call(seed):
+            with torch.cuda.stream(stream):
+                c.run_batch(d_in, [0, len(E)], [n], [seed], [3], t0=[0], out=out, stream=stream)
+            stream.synchronize()
+            rc, exp, _, _ = oracle.run(E, n, seed, 0, 3, 0)
+            assert rc == 0 and np.array_equal(to_host(out), exp)
+            return c.profile()["k_load"][1]  # (launches timed by events: eager calls only)
+
+        c.run(to_dev(hubs), nh, 1, r=1)  # (sizes the buffers)
+        call(1)  # (allocates, so the shape's first call counts again)
+        a = call(2)
+        assert call(3) == a and call(10) == a
+        c.run(to_dev(hubs), nh, 1, r=1)
+        b = call(4)
+        assert call(5) == b
+        c.set_option(getattr(gesmc, option), value)
+        assert call(6) == b + 1
+        assert call(7) == b + 1 and call(8) == b + 1
+        if option == "OPT_ROUND_LIMIT":
+            c.set_option(gesmc.OPT_ROUND_LIMIT, 1)
+            with pytest.raises(gesmc.GesmcError) as ei:
+                call(9)
+            assert ei.value.status == gesmc.E_ROUNDS
+    finally:
+        c.close()
