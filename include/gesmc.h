@@ -429,9 +429,10 @@ gesmc_status gesmc_es_draws(gesmc_ctx *ctx, void *stream, uint64_t m, uint64_t s
  * wall time of the chain and its sampling.  Limits: 2 <= n <= 2^14 (dense
  * pair counters: 12 bytes per vertex pair and thinning value), 1 <= nthin
  * <= 16, every k >= 1.  The context keeps a call's device block of up to 4 GiB
- * for its next diagnostic; it is returned for a larger one, with the context, or
- * when another allocation of the context finds no memory.  Larger blocks are
- * freed before the call returns.
+ * for its next diagnostic; it is returned for a larger one, with the context,
+ * when another allocation of the context finds no memory, or by
+ * gesmc_set_allocator (also with no functions).  Larger blocks, and all of a
+ * caller-supplied allocator, are freed before the call returns.
  */
 typedef struct gesmc_mixing_result {
     uint32_t k;            /* thinning value                                */
@@ -559,7 +560,8 @@ gesmc_status gesmc_set_option(gesmc_ctx *ctx, int option, int64_t value);
  * Each buffer goes back to the allocator that made it: free_fn(ptr, user) of
  * the pair in force when it was allocated, called only after the device has
  * finished all queued work (hipMalloc buffers from before stay hipMalloc
- * buffers).  Both NULL: back to hipMalloc.  The functions run on the thread
+ * buffers), and a block kept for gesmc_mixing goes back at once.  Both NULL:
+ * back to hipMalloc.  The functions run on the thread
  * of the library call that allocates (a context's buffers grow on demand)
  * and must not call into the library.  GESMC_E_INVAL for one function given
  * without the other, or while a gesmc_server uses the context.  The small

@@ -2829,6 +2829,7 @@ gesmc_status gesmc_set_allocator(gesmc_ctx *c, gesmc_alloc_fn alloc, gesmc_free_
         set_error("the context serves a gesmc_server; destroy the server first");
         return GESMC_E_INVAL;
     }
+    release_mix_block(c);
     c->alloc_fn = alloc;
     c->free_fn = free_fn;
     c->alloc_user = user;

@@ -13,8 +13,10 @@ constexpr uint32_t kMixMaxN = 1u << 14;  // pair ids below 2^27
 // each other sooner than that wait.  n = 2^13, seven thinnings (2.9 GB), 400
 // calls in a row, ms at the median and the 90th percentile: K = 200 21.9 and
 // 163 without, 21.2 and 21.2 with it; K = 20 3.95 and 225, 3.27 and 3.30.
-// It is returned with the context, for a larger block, or as soon as another
-// allocation of the context finds no memory.
+// It is returned with the context, for a larger block, as soon as another
+// allocation of the context finds no memory, or by gesmc_set_allocator.  A block
+// of the caller's allocator goes back with the call: it is there to be shared,
+// and keeps what it gets itself.
 constexpr uint64_t kMixKeepBytes = 4ull << 30;
 
 struct MixBlock {
@@ -33,7 +35,7 @@ struct MixBlock {
         return GESMC_OK;
     }
     void keep() {
-        if (bytes > kMixKeepBytes) return;
+        if (bytes > kMixKeepBytes || c->alloc_fn) return;
         c->mix_blk = p;
         c->mix_bytes = bytes;
         p = nullptr;

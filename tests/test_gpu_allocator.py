@@ -147,3 +147,26 @@ def test_es_without_memory_for_windows():
         assert a.asked > 4
         ctx.close()
         assert a.live == {}
+
+
+def test_mixing_block_goes_back():
+    """The diagnostic's block (12 bytes a vertex pair and thinning value) is not
+    kept from a caller's allocator, and gesmc_set_allocator returns a kept one."""
+    gesmc = _gpu()
+    n = 6000
+    E = graphgen.gnp(n, 0.001, 3)
+    counters = 12 * (n * (n - 1) // 2)
+    a = Counting()
+    ctx = gesmc.Context(0)
+    d = to_dev(E)
+    want, _ = ctx.mixing(d, n, 1, 4, [1, 2])  # kept by the context
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    ctx.set_allocator(a.alloc, a.free)
+    assert torch.cuda.mem_get_info()[0] - free0 >= 2 * counters
+    for _ in range(2):
+        got, _ = ctx.mixing(d, n, 1, 4, [1, 2])
+        assert got == want
+        assert sum(a.live.values()) < counters
+    ctx.close()
+    assert a.live == {}
