@@ -1136,23 +1136,34 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
     // first tuple count pass (k_emit_counts), one workgroup per tile up to
     // kEmitSlotsMax
     const bool fused = c->fuse_emit && GESMC_FUSE_EMIT_COUNTS;
-    const bool scatter_next = GESMC_FUSE_SCATTER && count_next && fused && sorted == 1 && q.m == p.m &&
-                              p.ell > 0 && c->persist_mult == 0 && !alloc_forbidden();
+    bool scatter_next = GESMC_FUSE_SCATTER && count_next && fused && sorted == 1 && q.m == p.m && p.ell > 0 &&
+                        c->persist_mult == 0 && !alloc_forbidden();
     auto next_counts = [&](uint32_t *counts) {
         return NextCounts{counts, t + 1, k0, k1, 64 - (int)q.b1, (int)q.b1, q.tile, q.m,
                           bs ? bs->gr : nullptr, bs ? bs->pg : nullptr, bs ? bs->step + 1 : 0u, (int)q.bbits};
     };
     // per-block counts of emit and the first round go to slots [0, ge) and [ge, ge + gd)
     const uint32_t emit_tiles = make_plan(c, nslots).ntiles1, round_tiles = q.ntiles1;
+    const RadixWords rw = radix_words(q);
+    const uint64_t slot_words = 4 * (std::min<uint32_t>(kEmitSlotsMax, round_tiles) + (uint64_t)round_tiles);
+    if (scatter_next) {
+        // one buffer: outcome counts (16-byte slots), tile counts, chunk sums, offsets;
+        // without memory for it (nothing may be allocated under capture) the passes
+        // stay apart and need none
+        const uint64_t want = slot_words + rw.counts1 + rw.partial + 2 * kNoffTiles;
+        const gesmc_status st = c->capturing && c->cap_nbuf < want
+                                    ? GESMC_E_NOMEM
+                                    : ensure_words(c, &c->nbuf, &c->cap_nbuf, want);
+        if (st == GESMC_E_NOMEM)
+            scatter_next = false;
+        else
+            GESMC_TRY(st);
+    }
     const uint32_t ge = fused ? std::min<uint32_t>(kEmitSlotsMax, scatter_next ? round_tiles : emit_tiles)
                               : grid_stride_blocks(c, (uint64_t)p.ell + 1);
     const uint32_t gd = scatter_next ? round_tiles : grid_stride_blocks(c, p.ell);
     uint4 *slots = c->bslot;
     if (scatter_next) {
-        // one buffer: outcome counts (16-byte slots), tile counts, chunk sums, offsets
-        const RadixWords rw = radix_words(q);
-        const uint64_t slot_words = 4 * (ge + (uint64_t)gd);
-        GESMC_TRY(ensure_words(c, &c->nbuf, &c->cap_nbuf, slot_words + rw.counts1 + rw.partial + 2 * kNoffTiles));
         c->fslot = c->nbuf;
         c->ncounts = c->fslot + slot_words;
         c->npartial = c->ncounts + rw.counts1;

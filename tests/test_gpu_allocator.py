@@ -170,3 +170,62 @@ def test_mixing_block_goes_back():
         assert sum(a.live.values()) < counters
     ctx.close()
     assert a.live == {}
+
+
+class RefusingSize(Counting):
+    """Returns no memory for allocations of one size."""
+
+    def __init__(self, size=None):
+        super().__init__()
+        self.size, self.sizes = size, []
+
+    def alloc(self, n):
+        self.sizes.append(n)
+        return 0 if n == self.size else super().alloc(n)
+
+
+@pytest.mark.parametrize("form", ["run", "class", "batch", "batch_graph"])
+def test_each_buffer_refused(form):
+    """Without memory for one of its buffers a call fails cleanly or, where the
+    buffer only joins two passes into one, gives the same result with them apart."""
+    gesmc = _gpu()
+    n, r = 20000, 3
+    E = graphgen.gnp(n, 0.001, 4)
+    rc, want, _, _ = oracle.run(E, n, 1, 0, r)
+    assert rc == 0
+    stream = torch.cuda.Stream()
+
+    def call(a):
+        ctx = gesmc.Context(0)
+        try:
+            ctx.set_option(gesmc.OPT_GRAPH, 1 if form == "batch_graph" else 0)
+            ctx.set_allocator(a.alloc, a.free)
+            d, out = to_dev(E), torch.full((len(E),), -1, dtype=torch.int64, device="cuda")
+            for _ in range(4 if form == "batch_graph" else 1):
+                try:
+                    if form == "run":
+                        ctx.run(d, n, 1, r=r, out=out)
+                    elif form == "class":
+                        ctx.run_class(d, n, 1, 0, 0, r, out=out)
+                    else:
+                        with torch.cuda.stream(stream):
+                            ctx.run_batch(d, [0, len(E)], [n], [1], [r], out=out, stream=stream)
+                        stream.synchronize()
+                except gesmc.GesmcError as e:
+                    assert e.status == gesmc.E_NOMEM and (out == -1).all()
+                    return False
+                assert np.array_equal(out.cpu().numpy().view(np.uint64), want)
+                out.fill_(-1)
+                torch.cuda.synchronize()
+            return True
+        finally:
+            ctx.close()
+            assert a.live == {}
+
+    a = RefusingSize()
+    assert call(a)
+    survived = 0
+    for size in sorted(set(a.sizes)):
+        print("case %s without %d bytes" % (form, size), flush=True)
+        survived += call(RefusingSize(size))
+    assert survived > 0
