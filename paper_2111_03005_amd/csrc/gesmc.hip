@@ -1103,6 +1103,12 @@ int decision_rounds(const gesmc_ctx *c, uint32_t ell, bool batch) {
     return ell < kRoundsFromSwitches ? 0 : kRoundsPlain;
 }
 
+// Workgroups of the finisher after so many list rounds.  More than one cost a
+// superstep whose list turns out short up to 0.6 us (m = 1.1e5, 41 undecided:
+// 68.0 and 68.6); at most 8192 switches are 16 passes of one.
+constexpr uint32_t kFinishAlone = 1u << 13;
+uint32_t finish_blocks(uint32_t ell, int rounds) { return rounds == 0 && ell > kFinishAlone ? kFinishGrid : 1u; }
+
 // After a plain call of r supersteps (their counters in h_ctr).
 void adapt_decision_rounds(gesmc_ctx *c, uint32_t r) {
     uint64_t left = 0;
@@ -1219,10 +1225,11 @@ gesmc_status superstep_partitioned(gesmc_ctx *c, hipStream_t s, const Plan &p, u
                          &c->ucount[(j + 2) % 3], (uint4 *)nullptr, c->ctr_step, cls, NextCounts{},
                          c->wn, (const uint4 *)slots, j == 0 ? ge + gd : 0u, pos));
     }
-    GESMC_TRY(launch(c, s, KID_FINISH_CHAIN, 0, k_finish_chain, dim3(1), dim3(kChainFinish), 0, si, sk, p.ell,
+    GESMC_TRY(launch(c, s, KID_FINISH_CHAIN, 0, k_finish_chain, dim3(finish_blocks(p.ell, j)), dim3(kChainFinish), 0,
+                     si, sk, p.ell,
                      c->info, c->st, c->idx[0], c->key[0], c->ulist[j % 2], &c->ucount[j % 3],
                      c->ulist[(j + 1) % 2], &c->ucount[(j + 1) % 3], (const uint4 *)slots, j ? 0u : ge + gd,
-                     c->ctr_step, c->err, c->round_limit, cls, c->wn, pos));
+                     c->ctr_step, c->err, c->round_limit, cls, c->wn, pos, c->ucount + 3));
     if (bs && bs->acc)
         GESMC_TRY(launch(c, s, KID_MISC, 0, k_graph_stats, dim3(ceil_div(p.ell, kStatsChunk)), dim3(kBlock), 0,
                          (const uint8_t *)c->st, bs->gr, bs->ngraphs, p.ell, bs->acc));

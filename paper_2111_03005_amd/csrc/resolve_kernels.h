@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint32_t *__restrict__ s_
     __shared__ BlockCounts bc;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) bc = BlockCounts{0, 0, 0, 0};
-    if (blockIdx.x == 0 && tid < 3) ucount[tid] = 0;  // the undecided-list counters of the rounds
+    if (blockIdx.x == 0 && tid < 4) ucount[tid] = 0;  // the undecided-list counters of the rounds, arrivals
     __syncthreads();
     const uint32_t m = sa.m, ell = m >> 1;
     const uint32_t stride = gridDim.x * kBlock;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_counts(const uint32_t *__restri
     const uint32_t nd = 1u << dbits, dmask = nd - 1, tid = threadIdx.x;
     const uint32_t m = sa.m, ell = m >> 1;
     if (tid == 0) bc = BlockCounts{0, 0, 0, 0};
-    if (blockIdx.x == 0 && tid < 3) ucount[tid] = 0;  // the undecided-list counters of the rounds
+    if (blockIdx.x == 0 && tid < 4) ucount[tid] = 0;  // the undecided-list counters of the rounds, arrivals
     // nc.counts: nc.tile positions (2 nc.tile slots) a trip, which are whole tiles here
     const uint32_t per = nc.counts ? 2 * nc.tile / kTile : 1u, nnext = nc.counts ? 1u << nc.dbits : 0u;
     for (uint32_t w0 = blockIdx.x * per; w0 < nt; w0 += gridDim.x * per) {
@@ -1134,6 +1134,15 @@ constexpr uint32_t kSweepAfter = 8;
 constexpr uint32_t kSweepChunk = 1024;
 constexpr uint32_t kSweepWords = 16384;  // chunk marks: ids below 2^29 (m < 2^30)
 
+// The first sweep over a longer list than this (but one that fits LDS) is shared
+// by the launch's kFinishGrid workgroups, as a round of the whole chip, and the
+// last of them to arrive is the finishing workgroup; those of a shorter list leave
+// at once.  No list round runs before it on smaller graphs (decision_rounds), and
+// on a dense one most switches are still undecided: G(500, 0.9), m = 1.1e5, 20,000
+// of 56,000, us per superstep with one workgroup for all passes 399, shared 150,
+// after two list rounds 167; power law of gamma = 2.01, n = 40,000 707 and 520.
+constexpr uint32_t kFinishShared = 1024, kFinishGrid = 64;
+
 __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *__restrict__ s_idx,
                                                                const unsigned long long *__restrict__ s_key,
                                                                uint32_t ell, uint2 *info,
@@ -1144,24 +1153,83 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
                                                                uint32_t nbslot, StepCounters *ctr,
                                                                uint32_t *__restrict__ err, uint32_t round_limit,
                                                                uint32_t cls, Winners wn,
-                                                               const uint2 *__restrict__ pos) {
+                                                               const uint2 *__restrict__ pos,
+                                                               uint32_t *__restrict__ arrived) {
     __shared__ BlockCounts bc;
-    __shared__ uint32_t s_n;
+    __shared__ uint32_t s_n, s_first;
     const uint32_t tid = threadIdx.x;
     unsigned long long charged = 0;  // rounds that count against round_limit (thread 0)
+    if (tid == 0) s_first = min(*count_a, ell);
+    __syncthreads();
+    // (a count that the finishing workgroup of a short list has overwritten is shorter still)
+    const uint32_t first = s_first;
+    const bool share = gridDim.x > 1 && first > kFinishShared && !(first <= kFinishList && ell <= kFinishSwitches);
+    if (!share && blockIdx.x != 0) return;
     if (tid == 0) {
         bc = BlockCounts{0, 0, 0, 0};
-        s_n = min(*count_a, ell);
-        if (nbslot) ctr->undecided_round1 = s_n;
+        s_n = first;
+        if (nbslot && blockIdx.x == 0) ctr->undecided_round1 = first;
         // a caller's round budget (0: none), counted over the superstep's rounds so
         // far (the multi-workgroup rounds before this kernel included)
         charged = round_limit ? atomicAdd(&ctr->rounds, 0ull) : 0ull;
-        if (round_limit && (charged > round_limit || (charged == round_limit && s_n > 0))) {
+        if (round_limit && (charged > round_limit || (charged == round_limit && first > 0))) {
             atomicOr(err, ERR_ROUNDS);
             s_n = 0;
         }
     }
     __syncthreads();
+    uint32_t *cur = list_a, *nxt = list_b, *ccur = count_a, *cnxt = count_b;
+    if (share && s_n == 0 && blockIdx.x != 0) return;  // (every workgroup found the budget spent)
+    if (share && s_n > 0) {
+        __shared__ uint32_t s_here, s_base, s_last;
+        for (uint32_t q0 = blockIdx.x * kChainFinish; q0 < first; q0 += gridDim.x * kChainFinish) {
+            const uint32_t q = q0 + tid;
+            bool wait = false;
+            uint32_t k = 0;
+            if (tid == 0) s_here = 0;
+            if (q < first) {
+                k = list_a[q];
+                const uint8_t sk = k < ell ? st[k] : (uint8_t)ST_LEGAL;
+                if ((sk & kStOutcome) == ST_UNDECIDED) {
+                    const uint4 recs = target_records(info, k, sk);
+                    wait = commit_switch_chain(judge_switch_chain(k, recs, info, wn, GridStatus{st}), k, recs,
+                                               reinterpret_cast<const uint2 *>(s_idx)[k],
+                                               reinterpret_cast<const ulonglong2 *>(s_key)[k], wn, st, out_idx,
+                                               out_key, pos, &bc, cls);
+                }
+            }
+            __syncthreads();
+            const uint32_t slot = wait ? atomicAdd(&s_here, 1u) : 0u;
+            __syncthreads();
+            if (tid == 0 && s_here) s_base = atomicAdd(count_b, s_here);
+            __syncthreads();
+            if (wait) list_b[s_base + slot] = k;
+        }
+        flush_counts(&bc, ctr);
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(arrived, 1u) == gridDim.x - 1;
+        __syncthreads();
+        if (!s_last) return;
+        __threadfence();
+        if (tid == 0) {
+            *arrived = 0;
+            bc = BlockCounts{0, 0, 0, 0};
+            const uint32_t nn = min(atomicAdd(count_b, 0u), ell);
+            if (nn >= first) atomicOr(err, ERR_INTERNAL);  // the smallest undecided switch always decides
+            s_n = nn >= first ? 0 : nn;
+            atomicAdd(&ctr->rounds, (unsigned long long)((first + kChainFinish - 1) / kChainFinish));
+            if (round_limit && ++charged >= round_limit && s_n > 0) {
+                atomicOr(err, ERR_ROUNDS);
+                s_n = 0;
+            }
+        }
+        __syncthreads();
+        cur = list_b;
+        nxt = list_a;
+        ccur = count_b;
+        cnxt = count_a;
+    }
     if (nbslot) {  // fold the per-block counts of the emit and first round (no list round did; eight loads in flight)
         constexpr uint32_t kFold = 8;
         uint4 acc = make_uint4(0, 0, 0, 0);
@@ -1185,7 +1253,6 @@ __global__ __launch_bounds__(kChainFinish) void k_finish_chain(const uint32_t *_
         if (acc.z) atomicAdd(&bc.exists, acc.z);
         if (acc.w) atomicAdd(&bc.pl, acc.w);
     }
-    uint32_t *cur = list_a, *nxt = list_b, *ccur = count_a, *cnxt = count_b;
     uint32_t n = s_n, here = 0;
     __shared__ __align__(16) uint32_t s_chunks[kSweepWords];  // the sweep's chunk marks; statuses before it
     if (n > 0 && n <= kFinishList && ell <= kFinishSwitches) {

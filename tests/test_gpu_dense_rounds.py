@@ -111,3 +111,50 @@ def test_round_limit_counts_sweeps(n):
         assert ei.value.status == gesmc.E_ROUNDS and bool((sentinel == 7).all())
     finally:
         c.close()
+
+
+# the finisher's first sweep is shared by workgroups from 8193 switches on, if
+# its list is longer than 1024, or 2048 up to 16384 switches; every form of call,
+# with a hub-free call in between that leaves nothing to share
+@pytest.mark.parametrize("m", [16385, 16386, 16388, 32767, 32768, 32770, 90001])
+@pytest.mark.parametrize("p", [0.04, 0.12, 0.5, 0.95])
+def test_shared_sweep_exact(m, p):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2111_03005_amd as gesmc
+    n = int((2.1 * m / p) ** 0.5) + 3
+    E = np.random.default_rng(m).permutation(graphgen.gnp(n, p, 17))[:m]
+    assert len(E) == m
+    sparse = graphgen.gnp(30000, 1e-4, 2)
+    c = gesmc.Context(0)
+    try:
+        c.set_option(gesmc.OPT_FAST_ROUNDS, 0)
+        rc, exp, counts, codes = oracle.run(E, n, 6, 0, 3, 0, outcomes=True)
+        rc2, exp_s, _, _ = oracle.run(sparse, 30000, 6, 0, 3, 0)
+        assert rc == 0 and rc2 == 0
+        for form in ("run", "sparse", "class", "batch", "mixed batch"):
+            print("case shared m=%d p=%g %s" % (m, p, form), flush=True)
+            if form == "run":
+                out, st, steps = c.run(to_dev(E), n, 6, r=3, steps=True)
+                print("undecided", [s["undecided_after_round1"] for s in steps], "passes", [s["rounds"] for s in steps],
+                      flush=True)
+                for s, want in zip(steps, counts):
+                    assert all(s[k] == want[k] for k in ("attempts", "legal", "rej_loop", "rej_exists", "rej_pl"))
+            elif form == "sparse":
+                out, _ = c.run(to_dev(sparse), 30000, 6, r=3)
+                assert np.array_equal(out.cpu().numpy().view(np.uint64), exp_s)
+                continue
+            elif form == "class":
+                out, _, _, got = c.run_class(to_dev(E), n, 6, 0, 0, 3, outcomes=True)
+                assert np.array_equal(got.cpu().numpy(), np.asarray(codes).reshape(-1))
+            elif form == "batch":
+                out, _, _ = c.run_batch(to_dev(E), [0, m], [n], [6], [3])
+            else:
+                both = np.concatenate([E, sparse])
+                out, _, _ = c.run_batch(to_dev(both), [0, m, len(both)], [n, 30000], [6, 6], [3, 3])
+                out = out.cpu()
+                assert np.array_equal(out[m:].numpy().view(np.uint64), exp_s)
+                out = out[:m]
+            assert np.array_equal(out.cpu().numpy().view(np.uint64), exp)
+    finally:
+        c.close()
