@@ -586,6 +586,13 @@ Plan make_plan(const gesmc_ctx *c, uint32_t m, bool spread = true) {
     return p;
 }
 
+// Plan of a permutation of m records.  What fits one bucket stays one: the sort
+// of its cells is one workgroup's either way and three launches fewer (us at m =
+// 400 and 1000: 35 and 38 in one bucket, 42 and 43 spread; 5 supersteps of a
+// multi-edge class 118 and 146 at m = 1000).  Tuples are spread there too: their
+// lists are longer (directed, dense, m = 512, 20 supersteps: 893 us, 1004 in one).
+Plan perm_plan(const gesmc_ctx *c, uint32_t m) { return make_plan(c, m, m > c->bucket_avg); }
+
 // One-level passes whose tiles' counts a workgroup sums itself instead of
 // three scan launches before it (k_scatter's self_off): as long as a thread
 // reads at most kSelfScanRows rows of counts.
@@ -1483,7 +1490,7 @@ gesmc_status run_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint64_t
     if (m > 0)
         GESMC_TRY(launch(c, s, KID_LOAD, m, k_load, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                          (const unsigned long long *)d_in, m, n, c->idx[0], c->key[0], c->err, cls));
-    Plan p = make_plan(c, m);
+    Plan p = perm_plan(c, m);
     p.dig_in_key = digit_in_key(p, n);
     const uint32_t nslots = (uint32_t)c->tab_slots;
     // the graph classes run on the sorted tuples only (multi-edge classes
@@ -2747,7 +2754,7 @@ gesmc_status gesmc_permutation(gesmc_ctx *c, void *stream, uint64_t m64, uint64_
         GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(4), dim3(256), 0, c->err, (uint64_t)64));
         GESMC_TRY(launch(c, s, KID_MISC, 0, k_identity_records, dim3(ceil_div(m, kBlock)), dim3(kBlock), 0,
                          c->idx[0], c->key[0], m));
-        Plan p = make_plan(c, m);
+        Plan p = perm_plan(c, m);
         p.dig_in_key = digit_in_key(p, 0);  // the records' keys are their indices (top byte zero)
         int sorted = 0;
         GESMC_TRY(permute(c, s, p, t, (uint32_t)seed, (uint32_t)(seed >> 32), 0, &sorted, false));

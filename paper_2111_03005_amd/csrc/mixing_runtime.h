@@ -62,7 +62,7 @@ struct MixChain {
 gesmc_status mix_chain_open(gesmc_ctx *c, hipStream_t s, MixChain *q, const unsigned long long *E) {
     GESMC_TRY(ensure_capacity(c, q->m, true));
     GESMC_TRY(ensure_counters(c, kMixPiece));
-    q->p = make_plan(c, q->m);
+    q->p = perm_plan(c, q->m);
     q->p.dig_in_key = digit_in_key(q->p, q->n);
     q->ahead = GESMC_COUNT_AHEAD && q->p.bbits > 0 && q->p.b1 > 0 && q->p.ell > 0;
     q->piece0 = 0;

@@ -45,3 +45,27 @@ def test_one_level_exact(pool, m, pack, fuse):
         assert [s["legal"] for s in steps] == [x["legal"] for x in counts]
     finally:
         c.close()
+
+
+# up to one bucket a permutation takes no radix pass; above it takes one
+@pytest.mark.parametrize("m", [2, 300, 577, 1151, 1152, 1153, 1154, 2305])
+def test_permutation_of_one_bucket(pool, m):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2111_03005_amd as gesmc
+    E = np.random.default_rng(m).permutation(pool)[:m]
+    print("case one bucket m=%d" % m, flush=True)
+    c = gesmc.Context(0)
+    try:
+        c.set_option(gesmc.OPT_PROFILE, 1)
+        got = c.permutation(m, 7, 3)
+        assert np.array_equal(got.cpu().numpy().astype(np.uint64), oracle.permutation(m, 7, 3).astype(np.uint64))
+        assert ("k_scatter1" in c.profile()) == (m > 1152)
+        for cls in (0, 1, 3, 4):
+            c.set_option(gesmc.OPT_SMALL_GRAPHS, 0)
+            out, _, _, codes = c.run_class(to_dev(E), 60000, 3, cls, 1, 4, outcomes=True)
+            rc, exp, _, oc = oracle.run_class(E, 60000, 3, 1, 4, 0, cls, outcomes=True)
+            assert rc == 0 and np.array_equal(out.cpu().numpy().view(np.uint64), exp)
+            assert np.array_equal(codes.cpu().numpy(), np.asarray(oc).reshape(-1))
+    finally:
+        c.close()
