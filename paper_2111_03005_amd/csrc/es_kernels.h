@@ -47,7 +47,7 @@ constexpr uint32_t kEsGateMax = 16;              // windows left to the chain af
 
 // Counters of one launch (device, cleared by the host's zero kernel).
 struct EsCounters {
-    unsigned long long legal, rej_loop, rej_exists, supersteps, rounds, rounds_max, used_slots, pad;
+    unsigned long long legal, rej_loop, rej_exists, supersteps, rounds, rounds_max;
 };
 
 __device__ __forceinline__ uint64_t es_mulhi(uint64_t a, uint64_t b) { return __umul64hi(a, b); }
@@ -149,19 +149,15 @@ __device__ __forceinline__ void es_probe2(const unsigned long long *H, uint32_t 
 
 // Inserts `key` (absent once its superstep's erases are done) at the first
 // empty or retired slot of its chain from slot s on; returns the slot.
-// *fresh is set if it took an empty one.
 __device__ __forceinline__ uint32_t es_insert_from(unsigned long long *H, uint32_t mask, uint32_t s,
-                                                   unsigned long long key, bool *fresh, uint32_t *err) {
+                                                   unsigned long long key, uint32_t *err) {
     // a slot changes at most twice in a superstep (retired once, taken once),
     // so the lost races are bounded too
     for (uint32_t p = 0, tries = 0; p <= mask && tries < 2 * mask + 64; ++tries) {
         const unsigned long long cur = es_load64(H + s);
         if (cur == kEsEmpty || cur == kEsTomb) {
             const unsigned long long prev = es_cas(H + s, cur, key);
-            if (prev == cur) {
-                *fresh = cur == kEsEmpty;
-                return s;
-            }
+            if (prev == cur) return s;
             continue;  // taken meanwhile: look at the same slot again
         }
         s = (s + 1) & mask;
@@ -181,8 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_es_clear(unsigned long long *__restr
 // edge of the input (ERR_DUP).
 __global__ __launch_bounds__(kBlock) void k_es_insert_all(const unsigned long long *__restrict__ E, uint32_t m,
                                                           unsigned long long *__restrict__ H, uint32_t mask,
-                                                          uint32_t *__restrict__ slot_of, uint32_t *__restrict__ err,
-                                                          EsCounters *ctr) {
+                                                          uint32_t *__restrict__ slot_of, uint32_t *__restrict__ err) {
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += stride) {
         const unsigned long long key = E[i];
@@ -202,7 +197,6 @@ __global__ __launch_bounds__(kBlock) void k_es_insert_all(const unsigned long lo
         }
         if (!done) atomicOr(err, ERR_INTERNAL);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&ctr->used_slots, (unsigned long long)m);
 }
 
 // Copies the result to the caller's buffer unless an error was raised.
@@ -262,13 +256,13 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
     } sh;
     __shared__ uint32_t pred[2 * kEsThreads];  // INSERT tuple -> previous inserter's tuple of the same key
     __shared__ uint8_t st[kEsThreads];
-    __shared__ uint32_t s_len, s_more;
+    __shared__ uint32_t s_len;
     __shared__ unsigned long long s_start;
-    __shared__ uint32_t c_legal, c_loop, c_exists, c_rounds, c_steps, c_fresh, c_rmax;
+    __shared__ uint32_t c_legal, c_loop, c_exists, c_rounds, c_steps, c_rmax;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) {
         s_start = kbeg;
-        c_legal = c_loop = c_exists = c_rounds = c_steps = c_fresh = c_rmax = 0;
+        c_legal = c_loop = c_exists = c_rounds = c_steps = c_rmax = 0;
     }
     __syncthreads();
     // nothing to do, or the input failed its checks (the edge set may then be incomplete)
@@ -430,16 +424,14 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
                 const bool qb = !pr[1].found && pr[1].free_slot != kEsNone;
                 const unsigned long long ga = qa ? es_cas(H + pr[0].free_slot, pr[0].free_seen, T.A) : 0;
                 const unsigned long long gb = qb ? es_cas(H + pr[1].free_slot, pr[1].free_seen, T.B) : 0;
-                bool f1 = pr[0].free_seen == kEsEmpty, f2 = pr[1].free_seen == kEsEmpty;
                 uint32_t sa = pr[0].free_slot, sb = pr[1].free_slot;
                 if (!qa || ga != pr[0].free_seen)
-                    sa = es_insert_from(H, mask, qa ? sa : es_home(T.A, mask), T.A, &f1, err);
+                    sa = es_insert_from(H, mask, qa ? sa : es_home(T.A, mask), T.A, err);
                 if (!qb || gb != pr[1].free_seen)
-                    sb = es_insert_from(H, mask, qb ? sb : es_home(T.B, mask), T.B, &f2, err);
+                    sb = es_insert_from(H, mask, qb ? sb : es_home(T.B, mask), T.B, err);
                 slot_of[d.i] = sa;
                 slot_of[d.j] = sb;
                 atomicAdd(&c_legal, 1u);
-                if (f1 || f2) atomicAdd(&c_fresh, (uint32_t)f1 + (uint32_t)f2);
             } else if (sk == ST_LOOP) {
                 atomicAdd(&c_loop, 1u);
             } else {
@@ -465,7 +457,6 @@ __global__ __launch_bounds__(kEsThreads) void k_es_chain(unsigned long long *__r
         atomicAdd(&ctr->supersteps, (unsigned long long)c_steps);
         atomicAdd(&ctr->rounds, (unsigned long long)c_rounds);
         atomicMax(&ctr->rounds_max, (unsigned long long)c_rmax);
-        atomicAdd(&ctr->used_slots, (unsigned long long)c_fresh);
         if (unsettled) {
             if (gate[0] == 0) gate[0] = gate[1] = gate[1] ? min(2 * gate[1], kEsGateMax) : 1u;
             else --gate[0];
@@ -547,9 +538,9 @@ __device__ __forceinline__ void es_link_event(const EsWindow &w, uint32_t node, 
 }
 
 // Sources e1, e2 of switch q become known in pass t (or change, `again`): targets, their
-// presence before the window, the guess "accepted", and the events.  False if
-// the pool has no node left.
-__device__ __forceinline__ bool es_set_sources(const EsWindow &w, uint32_t q, unsigned long long e1,
+// presence before the window, the guess "accepted", and the events.  (Once the
+// pool has no node left, ctl[0] says so and no pass may end the window.)
+__device__ __forceinline__ void es_set_sources(const EsWindow &w, uint32_t q, unsigned long long e1,
                                                unsigned long long e2, const unsigned long long *H, uint32_t mask,
                                                bool again, uint32_t t, uint32_t *err) {
     const Targets T = switch_targets(e1, e2, (w.ij[q].x >> 31) != 0);
@@ -572,7 +563,6 @@ __device__ __forceinline__ bool es_set_sources(const EsWindow &w, uint32_t q, un
         w.pres[2 * q] = pr[0].found ? 1 : 0;
         w.pres[2 * q + 1] = pr[1].found ? 1 : 0;
     }
-    bool ok = true;
     for (uint32_t e = 0; e < 4; ++e) {
         // (an event that stays may count again: the status is back to "accepted")
         es_touch(w, t, key[e]);
@@ -582,16 +572,12 @@ __device__ __forceinline__ bool es_set_sources(const EsWindow &w, uint32_t q, un
         uint32_t node = 4 * q + e;
         if (again) {
             const uint32_t x = atomicAdd(&w.ctl[0], 1u);
-            if (x >= 4 * w.cap) {
-                ok = false;
-                break;
-            }
+            if (x >= 4 * w.cap) break;
             w.pool[x] = node;
             node = 4 * w.cap + x;
         }
         es_link_event(w, node, key[e]);
     }
-    return ok;
 }
 
 // Draws of switches k0 .. k0 + n - 1 and the per-index lists of their uses;
@@ -739,11 +725,11 @@ __global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n
                                                           uint32_t mask, uint8_t *__restrict__ outcome,
                                                           EsCounters *__restrict__ ctr, uint32_t *__restrict__ err) {
     if (*err || w.ctl[w.passes] != 0) return;
-    __shared__ uint32_t c[4];
-    if (threadIdx.x < 4) c[threadIdx.x] = 0;
+    __shared__ uint32_t c[3];
+    if (threadIdx.x < 3) c[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * kBlock;
-    uint32_t legal = 0, loop = 0, exists = 0, fresh = 0;
+    uint32_t legal = 0, loop = 0, exists = 0;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += stride) {
         const uint2 ij = w.ij[q];
         const uint8_t sq = w.st[q];
@@ -766,7 +752,6 @@ __global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n
                 const unsigned long long cur = __hip_atomic_load(H + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (cur == kEsEmpty || cur == kEsTomb) {
                     if (atomicCAS(H + s, cur, key) == cur) {
-                        fresh += cur == kEsEmpty;
                         slot_of[i] = s;
                         done = true;
                     }
@@ -780,14 +765,12 @@ __global__ __launch_bounds__(kBlock) void k_es_win_commit(EsWindow w, uint32_t n
     if (legal) atomicAdd(&c[0], legal);
     if (loop) atomicAdd(&c[1], loop);
     if (exists) atomicAdd(&c[2], exists);
-    if (fresh) atomicAdd(&c[3], fresh);
     __syncthreads();
     if (threadIdx.x == 0) {
         EsCounters *o = ctr + (blockIdx.x % kEsCtrCopies);
         if (c[0]) atomicAdd(&o->legal, (unsigned long long)c[0]);
         if (c[1]) atomicAdd(&o->rej_loop, (unsigned long long)c[1]);
         if (c[2]) atomicAdd(&o->rej_exists, (unsigned long long)c[2]);
-        if (c[3]) atomicAdd(&o->used_slots, (unsigned long long)c[3]);
         if (blockIdx.x == 0) {
             uint32_t rounds = 1;
             while (rounds < w.passes && w.ctl[rounds]) ++rounds;

@@ -182,8 +182,7 @@ gesmc_status run_es_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
             GESMC_TRY(launch(c, s, KID_ES_BUILD, T, k_es_clear, dim3(grid_stride_blocks(c, T)), dim3(kBlock), 0,
                              c->es_H, T));
             GESMC_TRY(launch(c, s, KID_ES_BUILD, m, k_es_insert_all, dim3(grid_stride_blocks(c, m)), dim3(kBlock),
-                             0, (const unsigned long long *)c->es_E, m, c->es_H, mask, c->es_slot, c->err,
-                             c->es_ctr));
+                             0, (const unsigned long long *)c->es_E, m, c->es_H, mask, c->es_slot, c->err));
             if (windows && ke - kb >= below)  // uses of earlier epochs must read as none
                 GESMC_TRY(launch(c, s, KID_MISC, 0, k_zero_words, dim3(grid_stride_blocks(c, m)), dim3(kBlock), 0,
                                  win.last, (uint64_t)m));

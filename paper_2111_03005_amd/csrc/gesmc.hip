@@ -647,7 +647,7 @@ size_t sort_lds_bytes(uint32_t cap) {
 // cells, scan words, keys, tags, list links; packed words with the cell
 // lists keep their tags in the words
 size_t resolve_lds_bytes(uint32_t cap, bool packed = false) {
-    return ((size_t)(1u << kCellBits) + kBlock + 2) * 4 + (size_t)cap * (packed && GESMC_RESOLVE_LISTS ? 10 : 14);
+    return (size_t)(1u << kCellBits) * 4 + (size_t)cap * (packed ? 10 : 14);
 }
 
 // Workgroups of a persistent kernel: as many as can be resident at once

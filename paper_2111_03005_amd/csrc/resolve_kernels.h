@@ -56,9 +56,6 @@ struct Winners {
 constexpr uint32_t kNoWinner = 0xFFFFFFFFu;
 constexpr uint32_t kListEnd = 0xFFFFu;  // end of a cell list in k_resolve (slots are < 2^16)
 constexpr uint32_t kEpochNone = 0xFFFFu;  // k_resolve: no list partition yet (epochs are 0 .. 0xFFFE)
-#ifndef GESMC_RESOLVE_LISTS
-#define GESMC_RESOLVE_LISTS 1
-#endif
 static_assert(kLdsCap < kListEnd, "k_resolve slots fit 16 bits");
 
 // ---------------------------------------------------------------------------
@@ -382,7 +379,7 @@ __device__ __forceinline__ void resolve_one(uint32_t tag, uint32_t first_tag, ui
 // LDS path: counting sort on kCellBits hash bits below the partition bits;
 // each tuple then reads its own cell.  Partitions above `cap` (hub
 // keys with many inserters) take an exact global-memory merge sort.
-// Dynamic LDS: 2^kCellBits cell words + kBlock + 2 words + cap * 14 bytes
+// Dynamic LDS: 2^kCellBits cell words + cap * 14 bytes
 // (keys, tags and the 16-bit cell-list links), or cap * 10 bytes for packed
 // words with the cell lists (the tags stay in the words).  kPacked: the tuples are
 // packed words (no tag array); pbits is then the second level's bits only,
@@ -401,8 +398,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     constexpr uint32_t kCells = 1u << kCellBits;
     uint32_t *cell = lds;
-    uint32_t *tmp = cell + kCells;
-    unsigned long long *sK = reinterpret_cast<unsigned long long *>(tmp + kBlock + 2);
+    unsigned long long *sK = reinterpret_cast<unsigned long long *>(cell + kCells);
     uint32_t *sT = reinterpret_cast<uint32_t *>(sK + cap);
     const uint32_t tid = threadIdx.x;
     const int sub_shift = 64 - kCellBits;
@@ -549,7 +545,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu
             }
             if (tid == 0) atomicAdd(&ctr->fallback_buckets, 1ull);
             __syncthreads();
-        } else if (c > 0 && GESMC_RESOLVE_LISTS) {
+        } else if (c > 0) {
             // Tuples stay in their own slots p (contiguous writes); each cell
             // keeps a list of its slots, linked by one LDS exchange per tuple.
             // Packed words stay whole in sK (key bits and tag code), with no
@@ -601,64 +597,6 @@ __global__ __launch_bounds__(kBlock, 7) void k_resolve(uint32_t *__restrict__ tu
                     first_tag = min(first_tag, ty);
                     if (ty & kTagInsert) first_ins = min(first_ins, ty);
                     if (ty < tx || (ty == tx && y < p)) {
-                        prev_tag = before ? max(prev_tag, ty) : ty;
-                        before = true;
-                    }
-                }
-                resolve_one(tx, first_tag, first_ins, before ? 1u : 0u, 0u, prev_tag, kx, f, pk, info, st4, wn, err,
-                            dup_bit, ge);
-            }
-        } else if (c > 0) {  // counting sort into cell order
-            for (uint32_t q = tid; q < kCells; q += kBlock) cell[q] = 0;
-            lds_barrier();
-            uint32_t r_cell[kSortMaxItems], r_rank[kSortMaxItems];
-#pragma unroll
-            for (int q = 0; q < kSortMaxItems; ++q) {
-                const uint32_t p = tid + q * kBlock;
-                if (p < c) {
-                    if (kPacked) {
-                        c_tag[q] = tag_of_code((uint32_t)(c_key[q] & code_mask), pk.kb);
-                        c_key[q] &= ~code_mask;
-                    }
-                    const uint64_t hsh = c_key[q];  // tuple words are tuple hashes
-                    r_cell[q] = (uint32_t)((pbits >= 64 ? 0ull : (hsh << pbits)) >> sub_shift);
-                    r_rank[q] = atomicAdd(&cell[r_cell[q]], 1u);
-                }
-            }
-            lds_barrier();
-            block_exclusive_scan(cell, kCells, tmp);
-#pragma unroll
-            for (int q = 0; q < kSortMaxItems; ++q) {
-                const uint32_t p = tid + q * kBlock;
-                if (p < c) {
-                    const uint32_t lp = cell[r_cell[q]] + r_rank[q];
-                    sK[lp] = c_key[q];
-                    sT[lp] = c_tag[q];
-                }
-            }
-            lds_barrier();
-            // All tuples of one key share a cell.  Each tuple reads its cell
-            // (independent LDS loads, no sorting) for what the walk over the
-            // sorted group would give: the group's smallest tag, whether a
-            // tuple precedes it in (key, tag, slot) order and the largest
-            // preceding tag.
-#pragma unroll
-            for (int q = 0; q < kSortMaxItems; ++q) {
-                const uint32_t p = tid + q * kBlock;
-                if (p >= c) continue;
-                const uint32_t cl = r_cell[q];
-                const uint32_t a = cell[cl], b = (cl + 1 < kCells) ? cell[cl + 1] : c;
-                const uint32_t me = a + r_rank[q];
-                const unsigned long long kx = c_key[q];
-                const uint32_t tx = c_tag[q];
-                uint32_t first_tag = tx, first_ins = tx, prev_tag = 0;
-                bool before = false;
-                for (uint32_t y = a; y < b; ++y) {
-                    if (y == me || sK[y] != kx) continue;
-                    const uint32_t ty = sT[y];
-                    first_tag = min(first_tag, ty);
-                    if (ty & kTagInsert) first_ins = min(first_ins, ty);
-                    if (ty < tx || (ty == tx && y < me)) {
                         prev_tag = before ? max(prev_tag, ty) : ty;
                         before = true;
                     }
