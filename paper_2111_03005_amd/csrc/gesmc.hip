@@ -1094,13 +1094,17 @@ gesmc_status decide_and_scatter(gesmc_ctx *c, hipStream_t s, const Plan &q, uint
 // GESMC_OPT_FAST_ROUNDS is unset: kRoundsHubs after a plain call whose first
 // round left more than kRoundsHubsAbove switches of a superstep undecided
 // (adapt_rounds; not in a batch, whose graphs say nothing of each other and
-// whose captured schedule must not change with other calls), else none below kRoundsFromSwitches switches (the few that
-// are left cost the finisher less than an empty launch of 3 us: 41 at m =
-// 1.1e5) and kRoundsPlain from there on.  Hub graphs need 6 to 9 rounds
+// whose captured schedule must not change with other calls), else none below
+// kRoundsFromSwitches switches and kRoundsPlain from there on.  The line is the
+// finisher's (kFinishSwitches: list and statuses in LDS below it).  us per
+// superstep at 0 and 2 rounds, 50 to 80 switches undecided: 16,500 switches 54.4
+// and 58.7, 50,000 65.5 and 66.7, 65,600 77.5 and 78.0, 131,500 91.7 and 91.9,
+// 525,000 148.4 and 147.7; power law of gamma = 2.2: 27,900 (326 undecided) 65.2
+// and 68.3, 55,900 (461) 74.5 and 76.7, 87,000 (722) 94.0 and 90.9, 483,000
+// (2,943) 165.4 and 154.8.  Hub graphs need 6 to 9 rounds
 // whatever their size, and a pass of the finisher takes kChainFinish switches:
 // n = 2^19, gamma = 2.05, 72,000 undecided, ms per superstep at 0, 2, 8 and
-// 64 rounds: 1.56, 0.39, 0.34, 0.47; n = 20000, gamma = 2.01, 5,700 undecided:
-// 0.30, 0.22, 0.22, 0.35.
+// 64 rounds (one finishing workgroup): 1.56, 0.39, 0.34, 0.47.
 constexpr uint64_t kRoundsHubsAbove = 8 * kChainFinish;
 constexpr int kRoundsPlain = 2, kRoundsHubs = 6;
 constexpr uint32_t kRoundsFromSwitches = 1u << 16;

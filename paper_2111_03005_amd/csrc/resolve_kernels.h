@@ -1064,13 +1064,16 @@ __global__ __launch_bounds__(kThreads) void k_decide_scatter(
 // are then final and only chains inside a chunk cost repeats.  Each repeat
 // counts as a round.
 constexpr int kChainFinish = 512;
-// Undecided switches, of so many in all, whose list and statuses go to LDS
-// (mixing on m = 1.4e4, 970 undecided: 47 -> 31 us; on 55,000 switches the copy
-// costs more than the two passes of 41 undecided ones save).
-constexpr uint32_t kFinishList = 2048, kFinishSwitches = 16384;
+// Undecided switches, of so many in all, whose list and statuses go to LDS: as
+// many as the sweep's array holds.  us per superstep without and with the copy:
+// 15,000 switches, 290 undecided 65.9 and 59.4; 22,600, 63 of them 58.0 and 56.1,
+// 410 69.9 and 63.0; 45,200, 55 64.1 and 63.1, 860 83.4 and 77.1; 60,000, 58
+// 69.6 and 68.9, 1,113 91.7 and 88.0.
+constexpr uint32_t kFinishList = 2048, kFinishSwitches = 65536;
 constexpr uint32_t kSweepAfter = 8;
 constexpr uint32_t kSweepChunk = 1024;
 constexpr uint32_t kSweepWords = 16384;  // chunk marks: ids below 2^29 (m < 2^30)
+static_assert(kFinishSwitches <= 4 * kSweepWords, "the statuses fit the chunk marks' array");
 
 // The first sweep over a longer list than this (but one that fits LDS) is shared
 // by the launch's kFinishGrid workgroups, as a round of the whole chip, and the

@@ -114,10 +114,10 @@ def test_round_limit_counts_sweeps(n):
 
 
 # the finisher's first sweep is shared by workgroups from 8193 switches on, if
-# its list is longer than 1024, or 2048 up to 16384 switches; every form of call,
+# its list is longer than 1024, or 2048 up to 65536 switches; every form of call,
 # with a hub-free call in between that leaves nothing to share
-@pytest.mark.parametrize("m", [16385, 16386, 16388, 32767, 32768, 32770, 90001])
-@pytest.mark.parametrize("p", [0.04, 0.12, 0.5, 0.95])
+@pytest.mark.parametrize("m", [16385, 16386, 16388, 32767, 32768, 32770, 90001, 131070, 131073, 131074])
+@pytest.mark.parametrize("p", [0.01, 0.04, 0.12, 0.5, 0.95])
 def test_shared_sweep_exact(m, p):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
