@@ -20,9 +20,12 @@ uint64_t es_slots(uint32_t m) {
 // Switches per window and passes over it; 0 switches (the chain on one
 // workgroup) below kEsWindowEdges edges, where a window's launches cost more
 // than the supersteps they replace.  Small graphs are bound by the launches, so
-// their windows take a larger share of m and the more passes that share needs
-// (m = 1.7e5, switches/s at m / 16, m / 8 and m / 4: 0.86e8, 1.2e8, 1.7e8;
-// m = 1.9e6: 4.7e8, 5.4e8, 5.2e8).
+// their windows take a larger share of m and the more passes that share needs.
+// Where the two shares cross depends on how many switches a pass changes.  us per
+// m / 2 switches at m / 8 with 10 passes and m / 4 with 16: sparse G(n, p) m =
+// 3.0e5 663 and 514, 1.0e6 943 and 814, 1.3e6 1011 and 927, 2.0e6 1326 and 1318;
+// gamma = 2.05 and 2.01 2.7e5 1312 and 1540, 9.7e5 1903 and 2361, 1.3e6 2261 and
+// 2889; G(n, 0.9) 5.4e5 1319 and 1495.  The line lies between the two.
 constexpr uint32_t kEsWindowEdges = 4096;
 constexpr uint32_t kEsSmallEdges = 1u << 20;
 // At most 2^19 switches: the event lists and keys of a window then still sit

@@ -218,3 +218,14 @@ def test_es_windows_settled_and_not_in_one_epoch(ctx):
         assert 12 <= steps <= alone
         mixed += 12 < steps < alone
     assert mixed > 0
+
+
+# the share of m that a window takes falls from a quarter to an eighth at 2^20 edges
+@pytest.mark.parametrize("m,share", [(1048575, 4), (1048576, 8), (1048577, 8), (2097153, 8)])
+def test_es_window_share(ctx, m, share):
+    n = 300000
+    E = np.random.default_rng(m).permutation(graphgen.gnp(n, 4.8e-5, 9))[:m]
+    assert len(E) == m
+    W = min(m // share, 1 << 19)
+    st = check_es(ctx, E, n, 8, 0, W + 5000, label="window share", outcomes=True)  # (one epoch: m // 2)
+    assert st["supersteps"] == 2
