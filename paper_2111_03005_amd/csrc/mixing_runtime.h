@@ -120,19 +120,20 @@ gesmc_status mixing_impl(gesmc_ctx *c, void *stream, const uint64_t *d_in, uint6
     hipStream_t s = (hipStream_t)stream;
     const uint32_t m = (uint32_t)m64, ell = m / 2;
     const uint64_t npairs = (uint64_t)n * (n - 1) / 2, words = (npairs + 31) / 32;
-    // one block: the state, the current-sample bitmap, and per thinning value
-    // the previous sample's list and bitmap, the tracked bitmap and the counters
+    // one block: the state, the current-sample bitmaps, the results, and per
+    // thinning value the previous sample's list and bitmap, the tracked bitmap
+    // and the counters, each on 256 bytes
     const uint64_t mm = std::max<uint32_t>(m, 1);
-    const uint64_t per_q = mm * 8 + words * 8 + npairs * sizeof(MixCount) + 256 * 3;
-    const uint64_t bytes = mm * 8 + 2 * (words * 4 + 256) + 64 + nthin * per_q + 256;
+    auto pad = [](uint64_t b) { return (b + 255) & ~255ull; };
+    const uint64_t lists = pad(mm * 8) + 2 * pad(words * 4);
+    const uint64_t bytes = lists + pad(64) + nthin * (lists + pad(npairs * sizeof(MixCount)));
     MixBlock block{c};
     GESMC_TRY(block.take(bytes));
     unsigned char *const blk = block.p;
     uint64_t off = 0;
     auto take = [&](uint64_t b) {
-        off = (off + 255) & ~255ull;
         unsigned char *p = blk + off;
-        off += b;
+        off += pad(b);
         return p;
     };
     auto *E = (unsigned long long *)take(mm * 8);

@@ -99,3 +99,15 @@ def test_mixing_calls_share_block(ctx):
     for n, p, thin in ((300, 0.1, [1, 2]), (1500, 0.006, [1, 2, 3, 4]), (200, 0.05, [3]), (1500, 0.006, [2])):
         for chain in (0, 1):
             check(ctx, graphgen.gnp(n, p, n), n, 7, 12, thin, chain, label="sequence")
+
+
+@pytest.mark.parametrize("chain", [0, 1])
+def test_mixing_after_a_larger_call(ctx, chain):
+    """Nothing of a call is left for the next one in the context's block: series
+    without a transition (k > K) count none, whatever the sizes before."""
+    big = graphgen.gnp(1500, 0.006, 8)
+    for n, m, thin in ((40, 200, [70] * 16), (92, 289, [90] * 16), (92, 257, [1] * 15 + [7]), (129, 2400, [50])):
+        E = np.random.default_rng(n).permutation(graphgen.gnp(n, min(1.0, 2.6 * m / n / n), n))[:m]
+        assert len(E) == m
+        ctx.mixing(to_dev(big), 1500, 3, 12, [1] * 16, chain=chain)
+        check(ctx, E, n, 7, 5, thin, chain, label="after a larger call")
