@@ -498,18 +498,20 @@ uint32_t gesmc_tune_cache_size(void);
  * that GESMC_OPT_ROUND_LIMIT can make a call fail). */
 #define GESMC_OPT_BUCKET_AVG 1  /* largest mean records per sort bucket (64 .. 1152, default 1152)  */
 #define GESMC_OPT_SORT_CAP 2    /* records sorted in LDS per bucket (64 .. 1536, default 1536)     */
-#define GESMC_OPT_FAST_ROUNDS 3 /* multi-workgroup rounds before the 1-workgroup finisher (0 .. 64);
-                                   unset: 2, or 0 below 2^16 switches a superstep; a plain call
-                                   after one on this context whose first round left more than
-                                   4096 switches of a superstep undecided (hub edges): 6          */
+#define GESMC_OPT_FAST_ROUNDS 3 /* multi-workgroup rounds in launches of their own before the finisher
+                                   (0 .. 64; at 0 the finisher's workgroups share a first sweep over a
+                                   long list, then one of them goes on); unset: 2, or 0 below 2^16
+                                   switches a superstep; a plain call after one on this context whose
+                                   first round left more than 4096 switches of a superstep undecided
+                                   (hub edges): 6                                                  */
 #define GESMC_OPT_PROFILE 4     /* 1: time every kernel launch with HIP events                      */
 #define GESMC_OPT_STRATEGY 5    /* dependency resolution: 0 = tuples sorted by edge key per hash
                                    partition in LDS (default); 1 = one open-addressing table in HBM
                                    rebuilt every superstep with device-scope atomics               */
 #define GESMC_OPT_PERSIST 6     /* workgroups of the tile/bucket kernels: resident count x value;
                                    0 = one workgroup per tile or bucket (default 0)                */
-#define GESMC_OPT_LEVEL1_BITS 8  /* digit bits of the first radix level (1 .. 10); 0 = half of the
-                                    bucket bits, rounded up (default)                              */
+#define GESMC_OPT_LEVEL1_BITS 8  /* digit bits of the first radix level (1 .. 10); 0 = all bucket bits
+                                    up to 10, else half of them (default)                          */
 #define GESMC_OPT_FUSE_EMIT 9      /* 1: the first tuple partition pass computes the switches' tuples from
                                       their pair records, and its count kernel also writes each
                                       switch's status and records (default); 0: a separate emit

@@ -13,8 +13,9 @@
 // a superstep here is also capped at one switch per thread.
 //
 // On graphs of at least 4096 edges windows of the sequence are resolved over the
-// whole chip (second half of this file).  Below, and for a window that does not
-// settle, one workgroup owns one graph for a whole launch and walks its switches:
+// whole chip (second half of this file).  Below, for too few switches to make a
+// window, and for one that does not settle, one workgroup owns one graph for a
+// whole launch and walks its switches:
 //   A. draws of the next kEsThreads switches; superstep boundary by
 //      insert_if_min over their edge indices in an LDS table (the smallest
 //      later switch that reuses an index is the first one left out);

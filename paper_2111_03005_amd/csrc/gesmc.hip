@@ -1376,8 +1376,9 @@ gesmc_status map_err(uint32_t e) {
 // (k_small_perm, one workgroup each; the first also clears the error word
 // and the counts), then the chain itself on one workgroup (k_small_plain),
 // which resumes from the previous piece's output.  The counts (legal, loop,
-// exists, P_L) go to error words 8 .. 15, so one copy brings back both; no
-// rounds are recorded.
+// exists, P_L) are summed in error words 8 .. 15, and the last launch writes
+// them and the error word to pinned host memory, so no copy follows; no rounds
+// are recorded.
 template <uint32_t kMax, uint32_t kThreads, bool kCompact>
 gesmc_status run_small_pieces(gesmc_ctx *c, hipStream_t s, int kid, const unsigned long long *in,
                               unsigned long long *out, uint32_t m, uint32_t n, uint32_t t0, uint32_t r, uint32_t pl,
